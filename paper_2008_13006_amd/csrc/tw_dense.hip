@@ -3,11 +3,22 @@
 // instruction, same operand roles, same epilogue as tw_gemm; B is ordinary row-major K x N.
 //
 // Workgroup: a (64 * MSW) x 256 block of C, 8 waves as 2 (rows) x 4 (columns), wave tile (32 * MSW) x 64;
-// MSW = 4 (256 rows) where that still gives every compute unit a block, else 2 or 1 (the paper's tiling
-// leaves the thread-block shape to the implementation, Sec. VI "Tiling").
-// K advances 64 at a time through two LDS buffers; global loads of step i+1 are in flight
-// while step i is multiplied.  The activation operand is read from LDS 16 bytes per lane, the
-// weight operand with transposing reads (ds_read_b64_tr_b16) of the row-major B tile.
+// MSW = 4 (256 rows), 2 or 1, chosen per call (the paper's tiling leaves the thread-block shape to the
+// implementation, Sec. VI "Tiling").  Workgroups are persistent and walk blocks of C.
+//
+// K advances 64 at a time through a ring of LDS buffers that loads fill DIRECTLY (buffer_load .. lds): a staged K step
+// costs no registers and no LDS write instructions, so a whole step of loads is in flight while another is
+// multiplied, and the ring runs on into the workgroup's next block of C: its first step lands during this one's
+// last steps and its epilogue.  Direct loads write 1 KB of consecutive LDS per wave instruction, so rows cannot be padded;
+// bank conflicts are avoided by WHICH 16-byte piece of a row a lane fetches instead (kept at slot piece ^ f(row)).
+// What bounds it: the matrix units under the card's power limit.  16384 x 768 x 3072 in fp16: 83 us (930 TFLOP/s; 95 us with
+// the operands staged through registers); without loads and stores 55, with the MFMAs alone 50 (1560 TFLOP/s), and
+// 72 us as it is on operands of zeros, where the clock stays up.  The loads cost 14 us of the 83 and the stores 15.
+// On 16384 x 3072 x 768 83 us (95), 8192 x 4096 x 1024 74 (88), 2048 x 3072 x 768 35 (57), 1500 x 1000 x 2000 16 (31).
+// Spreading a step's requests over its MFMAs instead of one burst behind the barrier: no gain on real operands.
+//
+// The operands of contraction slots 16*ks+16 .. are read from LDS before the MFMAs of slots 16*ks .. are issued,
+// across the K step's barrier too (it sits in front of the last 8 MFMAs of a step).
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -19,17 +30,18 @@ namespace {
 
 typedef short tw_i16x4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 512;
-constexpr int BN = 256, KB = 64;
-constexpr int A_PITCH = KB * 2 + 16;   // 144 B: 16-byte reads of 16 consecutive rows hit distinct banks
-constexpr int B_PITCH = BN * 2 + 64;   // 576 B: four consecutive K rows start 16 banks apart, as the transposing reads want
-constexpr int B_BYTES = KB * B_PITCH;  // 36864
+constexpr int BN = 256, KB = 64, KS = KB / 16;
+constexpr int B_BYTES = KB * BN * 2;   // 32768
 // MSW: 32-row blocks of a wave's tile; the workgroup's block has BM = 64 * MSW rows
 template <int MSW> constexpr int bm_of() { return 64 * MSW; }
-template <int MSW> constexpr int a_bytes_of() { return bm_of<MSW>() * A_PITCH; }            // 36864 for 256 rows
+template <int MSW> constexpr int a_bytes_of() { return bm_of<MSW>() * KB * 2; }             // 32768 for 256 rows
 template <int MSW> constexpr int buf_bytes_of() { return a_bytes_of<MSW>() + B_BYTES; }
-template <int MSW> constexpr int lds_bytes_of() {                                           // 147456 for 256 rows
-    return 2 * buf_bytes_of<MSW>() > 8 * TW_STAGE_BYTES ? 2 * buf_bytes_of<MSW>() : 8 * TW_STAGE_BYTES;
-}
+// Buffers of the ring: as many as fit (128, 144, 120 KB of LDS).  (Steps of 32 K positions in four or five buffers, with
+// three or four steps on their way, measured the same as two buffers of 64: what bounds the loop is not the latency.)
+template <int MSW> constexpr int stages_of() { return MSW == 4 ? 2 : 3; }
+template <int MSW> constexpr int lds_bytes_of() { return stages_of<MSW>() * buf_bytes_of<MSW>(); }
+constexpr int kDenseStage = 4096;   // bytes of a wave's staging area in the epilogue: the areas lie in the buffer of the last step
+static_assert(8 * kDenseStage <= buf_bytes_of<1>(), "the epilogue's staging areas fit one buffer of the ring");
 
 struct DenseParams {
     const unsigned short* A;
@@ -43,151 +55,298 @@ struct DenseParams {
     int stream;                   // rows of C start on 128-byte boundaries: whole lines go out as streaming stores
 };
 
-template <int MSW>
-struct Staged {
-    tw_u32x4 a[MSW];
-    tw_u32x4 b[4];
-};
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-template <bool NT = false>
-__device__ __forceinline__ tw_u32x4 load8_guard(const unsigned short* p, int valid) {
-    // valid >= 8: one 16-byte load; 0 < valid < 8: element-wise, zero filled; <= 0: zeros
-    if (valid >= 8) {
-        if constexpr (NT) return tw_load16_stream(p);
-        else return *(const tw_u32x4*)p;
-    }
-    unsigned short e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = i < valid ? p[i] : (unsigned short)0;
-    return tw_u32x4{e[0] | ((unsigned)e[1] << 16), e[2] | ((unsigned)e[3] << 16), e[4] | ((unsigned)e[5] << 16),
-                    e[6] | ((unsigned)e[7] << 16)};
+// Offsets at and above this are out of a buffer descriptor's range: such a lane fetches zeros.
+constexpr unsigned kRange = 0x80000000u;
+__device__ const unsigned tw_dense_zeros[4] = {0u, 0u, 0u, 0u};
+
+// 64 x 16 bytes from memory straight to 1 KB of LDS at `lds` (lane l's piece at lds + 16 l).  Written as assembly: the
+// compiler orders every later LDS read behind the completion of the builtin's load, whichever buffer it
+// fills.  There are no output registers; lds_wait() is the wait.  (m0 needs a wait state before its use.)
+template <bool NT>
+__device__ __forceinline__ void load_lds(tw_u32x4 srd, unsigned voff, unsigned lds) {
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" :: "s"(lds), "v"(voff), "s"(srd) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(voff), "s"(srd) : "memory", "m0");
+}
+__device__ __forceinline__ void load_lds_wide(const void* src, unsigned lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "memory", "m0");
+}
+// At most N of this wave's vector memory requests outstanding, no LDS request; then the workgroup meets.
+template <int N>
+__device__ __forceinline__ void lds_wait() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+__device__ __forceinline__ void lds_meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__device__ __forceinline__ tw_u32x4 descriptor(const unsigned short* base) {
+    const uint64_t a = (uint64_t)base;
+    return tw_u32x4{(unsigned)uni((int)(unsigned)a), (unsigned)uni((int)(unsigned)(a >> 32)) & 0xFFFFu, kRange, 0x00020000u};
 }
 
-// NTA: the activations are read by one column of blocks only (N <= 256), so they carry the streaming hint
-template <int MSW, bool NTA>
-__device__ __forceinline__ void global_fetch(const DenseParams& p, int m0, int n0, int k0, int tid, Staged<MSW>& st) {
-    // A tile: 64 * MSW rows x 8 pieces of 16 B; thread handles pieces id = tid + 512*i
-#pragma unroll
-    for (int i = 0; i < MSW; ++i) {
-        const int id = tid + kThreads * i;
-        const int r = id >> 3, u = id & 7;
-        int gm = m0 + r;
-        gm = gm < p.M ? gm : p.M - 1;
-        const int k = k0 + u * 8;
-        st.a[i] = load8_guard<NTA>(p.A + (long)gm * p.lda + k, p.K - k);
-    }
-    // B tile: 64 rows x 32 pieces
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int id = tid + kThreads * i;
-        const int r = id >> 5, u = id & 31;
-        const int k = k0 + r, n = n0 + u * 8;
-        if (k < p.K)
-            st.b[i] = load8_guard(p.B + (long)k * p.ldb + n, p.N - n);
-        else
-            st.b[i] = tw_u32x4{0u, 0u, 0u, 0u};
-    }
+// the t-th block of C: four row blocks are walked together, so that the workgroups of one XCD (neighbouring t) share
+// rows of A and columns of B in its L2
+__device__ __forceinline__ void block_of(const DenseParams& p, int t, int bm, int& m0, int& n0) {
+    const int per = 4 * p.nbn, g = t / per, rem = t - g * per;
+    const int gm = p.nbm - 4 * g < 4 ? p.nbm - 4 * g : 4;
+    const int nb = rem / gm;
+    m0 = (4 * g + rem - nb * gm) * bm;
+    n0 = nb * BN;
 }
 
-template <int MSW>
-__device__ __forceinline__ void lds_commit(unsigned char* buf, int tid, const Staged<MSW>& st) {
+// Adds the bias and applies the activation, in place, to a 32 x 64 block: lane l holds row l%32 and of acc[cb] the
+// columns 32*cb + 8*(r/4) + 4*(l/32) + r%4.  (One branch for the block, so that the plain epilogue is straight-line code.)
+template <int DT>
+__device__ __forceinline__ void add_bias_act(tw_f32x16 (&acc)[2], const unsigned short* bias, int act, int width, int h) {
 #pragma unroll
-    for (int i = 0; i < MSW; ++i) {
-        const int id = tid + kThreads * i;
-        const int r = id >> 3, u = id & 7;
-        *(tw_u32x4*)(buf + r * A_PITCH + u * 16) = st.a[i];
-    }
+    for (int cb = 0; cb < 2; ++cb) {
+        float b[16];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int id = tid + kThreads * i;
-        const int r = id >> 5, u = id & 31;
-        *(tw_u32x4*)(buf + a_bytes_of<MSW>() + r * B_PITCH + u * 16) = st.b[i];
+        for (int r = 0; r < 16; ++r) {
+            const int c = 32 * cb + 8 * (r / 4) + 4 * h + r % 4;
+            b[r] = bias != nullptr ? tw_to_f32<DT>(bias[c < width ? c : 0]) : 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[cb][r] = tw_activate(acc[cb][r] + b[r], act);
     }
 }
 
-template <int DT, int MSW, bool NTA>
+// Writes one 32 x 64 block of a wave's results to C[row0 .., col0 .. col0 + width) through the wave's staging area of
+// 32 rows x 128 bytes.  Column octet c of row r lies at slot c ^ (r/2 % 8) of the row, its two halves swapped in
+// rows 16..31: the 8-byte writes of 32 lanes (32 rows, one octet) and the 16-byte reads (8 rows, 8 octets) then both
+// use every bank once.  stream: whole 128-byte lines may be written with streaming stores.
+// The LDS executes a wave's instructions in order: fences for the compiler are enough.
+template <int DT>
+__device__ __forceinline__ void store_block(const tw_f32x16 (&acc)[2], unsigned char* stage, unsigned short* C, long ldc,
+                                            int row0, int M, int col0, int width, int lane, bool stream) {
+    const int mrow = lane & 31, h = lane >> 5;
+    asm volatile("" ::: "memory");
+    unsigned char* myrow = stage + mrow * 128 + (h ^ (mrow >> 4)) * 8;
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            tw_u32x2 v;
+            v.x = (unsigned)tw_cvt<DT>(acc[cb][4 * q]) | ((unsigned)tw_cvt<DT>(acc[cb][4 * q + 1]) << 16);
+            v.y = (unsigned)tw_cvt<DT>(acc[cb][4 * q + 2]) | ((unsigned)tw_cvt<DT>(acc[cb][4 * q + 3]) << 16);
+            *(tw_u32x2*)(myrow + (((4 * cb + q) ^ ((mrow >> 1) & 7)) << 4)) = v;
+        }
+    asm volatile("" ::: "memory");
+    // 8 lanes cover the 64 columns of a row, 8 rows per pass
+    const int j = lane & 7;
+    tw_u32x4 v[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int r = (lane >> 3) + 8 * p;
+        v[p] = *(const tw_u32x4*)(stage + r * 128 + ((j ^ ((r >> 1) & 7)) << 4));
+        if (p >= 2) v[p] = tw_u32x4{v[p].z, v[p].w, v[p].x, v[p].y};
+    }
+    asm volatile("" ::: "memory");
+    unsigned short* dst = C + (long)(row0 + (lane >> 3)) * ldc + col0 + 8 * j;
+    const int rows = M - row0 - (lane >> 3);
+    if (width == 64 && stream) {                               // wave-uniform
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            if (8 * p < rows) tw_store16_stream(dst + (long)(8 * p) * ldc, v[p]);
+    } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            if (8 * p >= rows) continue;
+            unsigned short* d = tw_opaque(dst) + (long)(8 * p) * ldc;
+            if (8 * j + 8 <= width) *(tw_u32x4_a2*)d = v[p];
+            else if (8 * j < width) {                          // the row's ragged end
+                const unsigned e[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+#pragma unroll
+                for (int i = 0; i < 7; ++i)
+                    if (8 * j + i < width) d[i] = (unsigned short)(e[i >> 1] >> (16 * (i & 1)));
+            }
+        }
+    }
+}
+
+// NTA: the activations are read by one column of blocks only (N <= 256), so they carry the streaming hint.
+// WIDE: row pitches for which a block's offsets do not fit a buffer descriptor (64-bit addresses per lane instead).
+template <int DT, int MSW, bool NTA, bool WIDE>
 __global__ __launch_bounds__(kThreads) void tw_dense_kernel(const DenseParams p) {
-    constexpr int BM = bm_of<MSW>(), A_BYTES = a_bytes_of<MSW>(), BUF_BYTES = buf_bytes_of<MSW>();
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int BM = bm_of<MSW>(), A_BYTES = a_bytes_of<MSW>(), BUF_BYTES = buf_bytes_of<MSW>(), NST = stages_of<MSW>();
+    constexpr int kLoads = MSW + 4;               // requests of a wave per K step
+    // 16-byte piece u of row r of A lies at slot u ^ fa(r) of the row: any 16 lanes that a 16-byte LDS read serves
+    // together then hit 16 different slots of the banks
+    auto fa = [](int r) { return (r >> 1) & 7; };
+    extern __shared__ __attribute__((aligned(128))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = uni(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     const int h = lane >> 5, l32 = lane & 31;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    // workgroups that land on the same XCD (ids equal modulo 8) get neighbouring blocks of C,
-    // so they share rows of A and columns of B in that XCD's L2
+    // workgroups that land on the same XCD (ids equal modulo 8) get neighbouring blocks of C
+    const int total = p.nbm * p.nbn, grid = (int)gridDim.x;
     int bid = blockIdx.x;
-    const int total = p.nbm * p.nbn;
-    if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
-    const int mb = bid / p.nbn, nb = bid - mb * p.nbn;
-    const int m0 = mb * BM, n0 = nb * BN;
-
-    tw_f32x16 acc[MSW][2];
-#pragma unroll
-    for (int ms = 0; ms < MSW; ++ms)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[ms][cb][r] = 0.f;
-
+    if ((grid & 7) == 0) bid = (bid & 7) * (grid >> 3) + (bid >> 3);
     const int nk = (p.K + KB - 1) / KB;
-    Staged<MSW> st;
-    global_fetch<MSW, NTA>(p, m0, n0, 0, tid, st);
-    lds_commit(smem, tid, st);
-    __syncthreads();
 
-    for (int kt = 0; kt < nk; ++kt) {
-        unsigned char* cur = smem + (kt & 1) * BUF_BYTES;
-        unsigned char* nxt = smem + ((kt + 1) & 1) * BUF_BYTES;
-        const bool more = kt + 1 < nk;
-        if (more) global_fetch<MSW, NTA>(p, m0, n0, (kt + 1) * KB, tid, st);
+    // What this lane fetches of a step.  A: request i brings rows 8*(wave + 8*i) + lane/8.  B: request i brings K rows
+    // 2*(wave + 8*i) + lane/32, slot lane%32 of a row holds piece slot ^ 4*(row % 4) ^ 2*(row/8 % 2): the rows of a
+    // transposing read then lie in different parts of the banks, whichever 32 lanes are served together.
+    const int ra = 8 * wave + (lane >> 3);
+    const int ua = (lane & 7) ^ fa(ra);
+    const int rb = 2 * wave + h;
+    const int ub = l32 ^ ((rb & 3) << 2) ^ (((rb >> 3) & 1) << 1);
 
-        const unsigned char* la = cur + (wm * 32 * MSW + l32) * A_PITCH + h * 16;
-        // weight operand by transposing reads of the row-major (K-major) B tile: in each 16-lane block,
-        // lane j addresses K row 8h + 4r + j/4 at the four columns 4*(j%4) .. of the block's 16 columns
-        const int j = lane & 15;
-        const unsigned char* lb = cur + A_BYTES + (8 * h + (j >> 2)) * B_PITCH +
-                                  (wn * 64 + ((lane >> 4) & 1) * 16 + (j & 3) * 4) * 2;
+    // the request cursor: step ck of block ct, running ahead of the multiplication
+    int ct = bid, ck = 0, cm0, cn0;
+    block_of(p, ct, BM, cm0, cn0);
+    auto issue = [&](int buf) {
+        const unsigned dst = lds0 + (unsigned)uni(buf) * BUF_BYTES;
+        const int k0 = ck * KB;
+        const bool live = ct < total;
+        const bool ka = live && k0 + ua * 8 < p.K, nbv = live && cn0 + ub * 8 < p.N;
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int ks = 0; ks < KB / 16; ++ks) {
-            tw_u16x8 w[2], a[MSW];
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const tw_i16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) tw_i16x4*)(lb + (ks * 16) * B_PITCH + cb * 64));
-                const tw_i16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) tw_i16x4*)(lb + (ks * 16 + 4) * B_PITCH + cb * 64));
-                w[cb] = tw_u16x8{(unsigned short)lo4[0], (unsigned short)lo4[1], (unsigned short)lo4[2],
-                                 (unsigned short)lo4[3], (unsigned short)hi4[0], (unsigned short)hi4[1],
-                                 (unsigned short)hi4[2], (unsigned short)hi4[3]};
+            for (int i = 0; i < MSW; ++i) {
+                const int r = ra + 64 * i;
+                const void* src = ka && cm0 + r < p.M ? (const void*)(p.A + (long)(cm0 + r) * p.lda + (k0 + ua * 8)) : (const void*)tw_dense_zeros;
+                load_lds_wide(src, dst + (unsigned)(wave + 8 * i) * 1024u);
             }
 #pragma unroll
-            for (int ms = 0; ms < MSW; ++ms) a[ms] = *(const tw_u16x8*)(la + ms * 32 * A_PITCH + ks * 32);
+            for (int i = 0; i < 4; ++i) {
+                const int r = rb + 16 * i;
+                const void* src = nbv && k0 + r < p.K ? (const void*)(p.B + (long)(k0 + r) * p.ldb + (cn0 + ub * 8)) : (const void*)tw_dense_zeros;
+                load_lds_wide(src, dst + A_BYTES + (unsigned)(wave + 8 * i) * 1024u);
+            }
+        } else {
+            const tw_u32x4 da = descriptor(p.A + (long)cm0 * p.lda + k0);
+            const tw_u32x4 db = descriptor(p.B + (long)k0 * p.ldb + cn0);
+            const unsigned lda2 = 2u * (unsigned)p.lda, ldb2 = 2u * (unsigned)p.ldb;
 #pragma unroll
-            for (int ms = 0; ms < MSW; ++ms)
+            for (int i = 0; i < MSW; ++i) {
+                const int r = ra + 64 * i;
+                load_lds<NTA>(da, ka && cm0 + r < p.M ? (unsigned)r * lda2 + ua * 16 : kRange, dst + (unsigned)(wave + 8 * i) * 1024u);
+            }
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb) acc[ms][cb] = tw_mfma<DT>(w[cb], a[ms], acc[ms][cb]);
+            for (int i = 0; i < 4; ++i) {
+                const int r = rb + 16 * i;
+                load_lds<false>(db, nbv && k0 + r < p.K ? (unsigned)r * ldb2 + ub * 16 : kRange, dst + A_BYTES + (unsigned)(wave + 8 * i) * 1024u);
+            }
         }
-        if (more) lds_commit(nxt, tid, st);
-        __syncthreads();
-    }
+        if (++ck == nk) {
+            ck = 0;
+            ct += grid;
+            if (ct < total) block_of(p, ct, BM, cm0, cn0);
+        }
+    };
 
-    // epilogue through per-wave staging areas laid over the (now idle) operand buffers
-    unsigned char* stage = smem + wave * TW_STAGE_BYTES;
-    const int col0 = n0 + wn * 64;
-    const int width = (p.N - col0) < 64 ? (p.N - col0) : 64;
-    if (width > 0) {
+    // where this lane's operands lie in a buffer
+    const int j = lane & 15;
+    const unsigned oa = (unsigned)(wm * 32 * MSW + l32) * 128u + (unsigned)((h ^ fa(l32)) << 4);
+    // weight operand by transposing reads of the K-major B tile: in each 16-lane block, lane j addresses K row
+    // 8h + 4r + j/4 at the four columns 4*(j%4) .. of the block's 16 columns
+    const unsigned ob = A_BYTES + (unsigned)(8 * h + (j >> 2)) * 512u +
+                        (unsigned)(((wn * 8 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ ((j >> 2) << 2) ^ (h << 1)) * 16 + (j & 1) * 8);
+    tw_u16x8 w[2][2], a[2][MSW];
+    auto fetch = [&](int slot, const unsigned char* buf, int ks) {
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const unsigned char* lb = buf + (ob ^ (unsigned)(cb * 64)) + ks * 16 * 512;
+            const tw_i16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) tw_i16x4*)(lb));
+            const tw_i16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) tw_i16x4*)(lb + 4 * 512));
+            w[slot][cb] = tw_u16x8{(unsigned short)lo4[0], (unsigned short)lo4[1], (unsigned short)lo4[2], (unsigned short)lo4[3],
+                                   (unsigned short)hi4[0], (unsigned short)hi4[1], (unsigned short)hi4[2], (unsigned short)hi4[3]};
+        }
+#pragma unroll
+        for (int ms = 0; ms < MSW; ++ms) a[slot][ms] = *(const tw_u16x8*)(buf + (oa ^ (unsigned)(ks << 5)) + ms * 4096);
+    };
+    // K % 8 columns of the last 16-byte piece of A's rows belong to the row's pitch: whatever they hold counts as zero
+    auto clear_tail = [&](unsigned char* buf, int kt) {
+        if (kt == nk - 1 && (p.K & 7) != 0) {                 // uniform
+            if (tid < BM) {
+                unsigned char* piece = buf + tid * 128 + ((((p.K & 63) >> 3) ^ fa(tid)) << 4);
+                for (int e = p.K & 7; e < 8; ++e) *(unsigned short*)(piece + 2 * e) = 0;
+            }
+            lds_meet();
+        }
+    };
+
+    tw_f32x16 acc[MSW][2];
+    auto multiply = [&](int slot) {
 #pragma unroll
         for (int ms = 0; ms < MSW; ++ms)
-            tw_store_block<DT, 2>(acc[ms], stage, p.C, p.ldc, m0 + wm * 32 * MSW + ms * 32, p.M, col0, width, lane,
-                                  p.bias, p.act, p.stream != 0);
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) acc[ms][cb] = tw_mfma<DT>(w[slot][cb], a[slot][ms], acc[ms][cb]);
+    };
+
+#pragma unroll
+    for (int i = 0; i < NST; ++i) issue(i);
+    int pos = 0;                                             // buffer of the current step
+    lds_wait<(NST - 1) * kLoads>();
+    clear_tail(smem, 0);
+    fetch(0, smem, 0);
+    for (int t = bid; t < total; t += grid) {
+        int m0, n0;
+        block_of(p, t, BM, m0, n0);
+#pragma unroll
+        for (int ms = 0; ms < MSW; ++ms)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[ms][cb][r] = 0.f;
+        for (int kt = 0;; ++kt) {
+            unsigned char* cur = smem + pos * BUF_BYTES;
+            const int npos = pos + 1 == NST ? 0 : pos + 1;
+            unsigned char* nxt = smem + npos * BUF_BYTES;
+#pragma unroll
+            for (int ks = 0; ks < KS - 1; ++ks) {
+                fetch((ks + 1) & 1, cur, ks + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(ks & 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (kt + 1 == nk) break;
+            // the next step has landed and every wave has read this one: its buffer takes the step after the ring's last
+            lds_wait<(NST - 2) * kLoads>();
+            issue(pos);
+            clear_tail(nxt, kt + 1);
+            fetch(0, nxt, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(1);
+            __builtin_amdgcn_sched_barrier(0);
+            pos = npos;
+        }
+        multiply(1);
+        lds_wait<(NST - 2) * kLoads>();
+        // epilogue through per-wave staging areas in the buffer of the last step; the next block's first steps are landing in the others
+        {
+            unsigned char* stage = smem + pos * BUF_BYTES + wave * kDenseStage;
+            const int col0 = n0 + wn * 64;
+            const int width = (p.N - col0) < 64 ? (p.N - col0) : 64;
+            if (width > 0) {
+#pragma unroll
+                for (int ms = 0; ms < MSW; ++ms) {
+                    if (p.bias != nullptr || p.act != TW_ACT_NONE)
+                        add_bias_act<DT>(acc[ms], p.bias != nullptr ? p.bias + col0 : nullptr, p.act, width, h);
+                    store_block<DT>(acc[ms], stage, p.C, p.ldc, m0 + wm * 32 * MSW + ms * 32, p.M, col0, width, lane, p.stream != 0);
+                }
+            }
+        }
+        if (t + grid >= total) break;
+        lds_meet();
+        issue(pos);
+        pos = pos + 1 == NST ? 0 : pos + 1;
+        clear_tail(smem + pos * BUF_BYTES, 0);
+        fetch(0, smem + pos * BUF_BYTES, 0);
     }
+    // requests of the ring may still be on their way to this workgroup's LDS
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 template <int MSW>
-const void* pick(tw_dtype dt, bool nta) {
-    if (dt == TW_F16) return nta ? (const void*)tw_dense_kernel<TW_F16, MSW, true> : (const void*)tw_dense_kernel<TW_F16, MSW, false>;
-    return nta ? (const void*)tw_dense_kernel<TW_BF16, MSW, true> : (const void*)tw_dense_kernel<TW_BF16, MSW, false>;
+const void* pick(tw_dtype dt, bool nta, bool wide) {
+    if (wide) return dt == TW_F16 ? (const void*)tw_dense_kernel<TW_F16, MSW, false, true> : (const void*)tw_dense_kernel<TW_BF16, MSW, false, true>;
+    if (dt == TW_F16) return nta ? (const void*)tw_dense_kernel<TW_F16, MSW, true, false> : (const void*)tw_dense_kernel<TW_F16, MSW, false, false>;
+    return nta ? (const void*)tw_dense_kernel<TW_BF16, MSW, true, false> : (const void*)tw_dense_kernel<TW_BF16, MSW, false, false>;
 }
 
 }  // namespace
@@ -238,17 +397,19 @@ extern "C" int tw_dense_gemm_bias_act(const void* A, int lda, const void* B, int
     if (blocks > 0x7fffffffL) return TW_ERR_UNSUPPORTED;
     const void* fn;
     int lds;
-    const bool nta = p.nbn == 1;
-    if (msw == 4) { fn = pick<4>(dt, nta); lds = lds_bytes_of<4>(); }
-    else if (msw == 2) { fn = pick<2>(dt, nta); lds = lds_bytes_of<2>(); }
-    else { fn = pick<1>(dt, nta); lds = lds_bytes_of<1>(); }
-    static std::atomic<unsigned char> lds_set[64][2][10];
-    const int slot = 2 * msw + (nta ? 1 : 0);
+    // offsets of a block (256 rows of A, 64 of B) must fit 31 bits for the kernels that address through a descriptor
+    const bool wide = 256L * lda >= (1L << 30) || 64L * ldb >= (1L << 30);
+    const bool nta = p.nbn == 1 && !wide;
+    if (msw == 4) { fn = pick<4>(dt, nta, wide); lds = lds_bytes_of<4>(); }
+    else if (msw == 2) { fn = pick<2>(dt, nta, wide); lds = lds_bytes_of<2>(); }
+    else { fn = pick<1>(dt, nta, wide); lds = lds_bytes_of<1>(); }
+    static std::atomic<unsigned char> lds_set[64][2][15];
+    const int slot = 3 * msw + (wide ? 2 : nta ? 1 : 0);
     if (!lds_set[dev][dt][slot].load(std::memory_order_acquire)) {
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return TW_ERR_HIP;
         lds_set[dev][dt][slot].store(1, std::memory_order_release);
     }
     void* args[] = {(void*)&p};
-    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(kThreads), args, lds, (hipStream_t)hip_stream) == hipSuccess
+    return hipLaunchKernel(fn, dim3((unsigned)(blocks < n_cu ? blocks : n_cu)), dim3(kThreads), args, lds, (hipStream_t)hip_stream) == hipSuccess
                ? TW_OK : TW_ERR_HIP;
 }

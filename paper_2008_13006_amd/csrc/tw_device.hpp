@@ -85,19 +85,6 @@ __device__ __forceinline__ float tw_activate(float x, int act) {
     return x;
 }
 
-// Orders this wave's LDS traffic: everything issued before is complete and visible to the
-// wave's other lanes afterwards.  Not a workgroup barrier.
-__device__ __forceinline__ void tw_wave_lds_sync() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Staging area of one wave in the epilogue.  The dense kernel uses it as 32 rows x 64 columns of
-// 16-bit values, rows 136 bytes apart (the 8 extra bytes spread rows over the LDS banks); the TW
-// kernel as 8 rows x 256 columns, rows 528 bytes apart.
-#define TW_STAGE_PITCH 136
-#define TW_STAGE_BYTES 4864
-#define TW_STAGE_COLS 64
 
 // 16-byte store with the streaming hint (the line is not kept in the L2 after the write).  For stores that
 // complete whole 128-byte lines of the output this is faster than the plain store: on the BERT-base FFN-up shape
@@ -122,70 +109,4 @@ __device__ __forceinline__ T* tw_opaque(T* p) {
 // packed weights, which every workgroup re-reads, out of the L2.
 __device__ __forceinline__ tw_u32x4 tw_load16_stream(const void* p) {
     return __builtin_nontemporal_load((const tw_u32x4*)p);
-}
-
-
-// Writes one 32-row block of a wave's results to C[row0.., col0 .. col0+width) through the wave's
-// LDS staging area, 64 columns at a time (used where result column c goes to column col0 + c).
-//   acc[cb][r]   fp32 results: lane l owns row (l%32) and column c = 32*cb + 8*(r/4) + 4*(l/32) + r%4
-// bias (may be null): element col0 + c is added to column c before the activation `act`.
-// stream: col0 and the rows of C are multiples of 64 elements from a 128-byte boundary, so a full window of 64
-// columns is a whole line per row and may be written with streaming stores.
-template <int DT, int NCB>
-__device__ __forceinline__ void tw_store_block(const tw_f32x16 (&acc)[NCB], unsigned char* stage, unsigned short* C,
-                                               long ldc, int row0, int M, int col0, int width, int lane,
-                                               const unsigned short* bias = nullptr, int act = 0, bool stream = false) {
-    const int mrow = lane & 31, h = lane >> 5;
-    unsigned char* myrow = stage + mrow * TW_STAGE_PITCH;
-    for (int w0 = 0; w0 < width; w0 += TW_STAGE_COLS) {
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c_lo = 32 * cb + 8 * q;          // wave-uniform: columns c_lo .. c_lo+7
-                if (c_lo < w0 || c_lo >= w0 + TW_STAGE_COLS) continue;
-                float x[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = acc[cb][4 * q + e];
-                if (bias != nullptr || act != 0) {           // wave-uniform
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int c = c_lo + 4 * h + e;
-                        const float b = (bias != nullptr && c < width) ? tw_to_f32<DT>(bias[col0 + c]) : 0.f;
-                        x[e] = tw_activate(x[e] + b, act);
-                    }
-                }
-                tw_u32x2 v;
-                v.x = (unsigned)tw_cvt<DT>(x[0]) | ((unsigned)tw_cvt<DT>(x[1]) << 16);
-                v.y = (unsigned)tw_cvt<DT>(x[2]) | ((unsigned)tw_cvt<DT>(x[3]) << 16);
-                *(tw_u32x2*)(myrow + (c_lo + 4 * h - w0) * 2) = v;
-            }
-        }
-        tw_wave_lds_sync();
-        // 8 lanes cover the 64 columns of a row with 16-byte pieces, 8 rows per pass
-        const int j = lane & 7;
-        const int left = width - w0;                 // columns of this window that exist (may exceed 64)
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int r = (lane >> 3) + 8 * p;
-            const int grow = row0 + r;
-            const tw_u32x2 lo = *(const tw_u32x2*)(stage + r * TW_STAGE_PITCH + j * 16);
-            const tw_u32x2 hi = *(const tw_u32x2*)(stage + r * TW_STAGE_PITCH + j * 16 + 8);
-            if (grow < M && 8 * j + 8 <= left) {
-                // whole 128-byte lines (the caller says whether rows of C start on line boundaries)
-                if (stream && left >= TW_STAGE_COLS) tw_store16_stream(C + (long)grow * ldc + col0 + w0 + 8 * j, tw_u32x4{lo.x, lo.y, hi.x, hi.y});
-                else *(tw_u32x4_a2*)tw_opaque(C + (long)grow * ldc + col0 + w0 + 8 * j) = tw_u32x4{lo.x, lo.y, hi.x, hi.y};
-            }
-        }
-        // ragged end of the row: fewer than 8 columns left in the last group, one row per lane
-        if (left < TW_STAGE_COLS && (left & 7) != 0) {
-            const int rem = left & 7, cbeg = left & ~7;
-            const int grow = row0 + mrow;
-            if (h == 0 && grow < M) {
-                unsigned short* dstp = C + (long)grow * ldc + col0 + w0 + cbeg;
-                for (int e = 0; e < rem; ++e) dstp[e] = *(const unsigned short*)(myrow + (cbeg + e) * 2);
-            }
-        }
-        tw_wave_lds_sync();
-    }
 }

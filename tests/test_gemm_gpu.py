@@ -268,6 +268,39 @@ def test_dense_gemm_small_cases(tw, case):
     assert bool(torch.isnan(Cbuf[:, N:].float()).all().item()), "wrote outside C"
 
 
+# name, M, K, N, type, extra pitch of A and B, bias + GELU: one K step and one position, K steps fewer than the ring has
+# buffers, a K tail whose last 16 bytes hold what the pitch holds, several blocks of C per workgroup (blocks of 256, 128
+# and 64 rows), row pitches beyond a buffer descriptor's range
+DENSE_RING = [("one", 1, 1, 1, "f16", 0, 0, False), ("k_step_1", 300, 64, 257, "bf16", 8, 8, True),
+              ("k_step_2_tail", 65, 67, 511, "f16", 0, 16, False), ("k_step_3_tail", 129, 190, 40, "bf16", 24, 0, True),
+              ("walk_256", 33000, 33, 520, "f16", 0, 0, False), ("walk_256_wide_n", 300, 130, 66000, "f16", 0, 0, True),
+              ("walk_k_step_3", 33001, 135, 257, "bf16", 8, 0, False),
+              ("pitch_of_a", 5, 300, 264, "f16", 1 << 23, 0, True), ("pitch_of_b", 70, 130, 264, "bf16", 0, 1 << 24, False)]
+
+
+@pytest.mark.parametrize("case", DENSE_RING, ids=[c[0] for c in DENSE_RING])
+def test_dense_gemm_ring(tw, case):
+    """Every element, and nothing outside C; the pitch of A, B and C holds NaN, which no result may see."""
+    name, M, K, N, dtype, pad_a, pad_b, fused = case
+    _say(f"tw_dense_gemm ring {name} M={M} K={K} N={N} {dtype}")
+    rng = np.random.default_rng(sum(map(ord, name)))
+    A_bits = W.f32_to_bits(rng.standard_normal((M, K), dtype=np.float32), dtype)
+    B_bits = W.f32_to_bits(rng.standard_normal((K, N), dtype=np.float32) * np.float32(0.05), dtype)
+    bbits = _bias_bits(N, dtype, 5)
+    td = torch.float16 if dtype == "f16" else torch.bfloat16
+    r8 = lambda x: (x + 7) // 8 * 8
+    A = torch.full((M, r8(K) + pad_a), float("nan"), dtype=td, device="cuda:0")[:, :K]
+    B = torch.full((K, r8(N) + pad_b), float("nan"), dtype=td, device="cuda:0")[:, :N]
+    A.copy_(tw.bits_to_tensor(A_bits, dtype)); B.copy_(tw.bits_to_tensor(B_bits, dtype))
+    Cbuf = torch.full((M, r8(N) + 8), float("nan"), dtype=td, device="cuda:0")
+    bias = tw.bits_to_tensor(bbits, dtype) if fused else None
+    tw.tw_dense_gemm_bias_act(A, B, bias, "gelu" if fused else "none", Cbuf[:, :N])
+    torch.cuda.synchronize()
+    post = (lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "gelu")) if fused else None
+    _compare_whole(Cbuf[:, :N], A_bits, B_bits, np.ones((K, N), np.uint8), dtype, what=name, post=post)
+    assert bool(torch.isnan(Cbuf[:, N:].float()).all().item()), "wrote outside C"
+
+
 # ------------------------------------------------------------------ the five workloads, full size
 def test_config1_full(tw):
     _say("config 1, every element")
