@@ -78,6 +78,7 @@ struct TwGemmParams {
     // tw_splitk_reduce_kernel adds them up in the order of the parts and stores C.  n_parts = 1: no split.
     int n_parts, chunks_per_part;
     float* partials;
+    int team_shift;             // tw_team_kernel: log2 of the waves that share a tile (8, 4 or 2)
 };
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -1730,6 +1731,93 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
     else store_tile<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, sub, sub + 1);
 }
 
+// K resident, row blocks of 32, few tiles per workgroup: a TEAM of 8, 4 or 2 waves shares a tile.
+// With few row blocks a workgroup of the kernel above has one to four tiles for its eight waves, and a launch takes as
+// long as one wave takes for its chain: item number, descriptor, A, K indices, a heavy tile's steps one after the other (24
+// steps, 3 requests of packed weights ahead), the epilogue.  Here the workgroup's number is its item (a launch is one round of
+// workgroups), a wave takes 1 / team of its tile's steps and requests their first operands BEFORE it waits for A,
+// and the fp32 sums meet in LDS: every wave leaves its own there, and pass by pass (column block by column block on
+// the transposed boundary) the team's waves add them in the order of the steps and store their share of the tile.
+// The order of the sums depends on the plan only, so repeated calls are bit-identical.
+template <int DT, int NCB, bool FUSED, bool TRANS>
+__global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p) {
+    constexpr int MS = 1;
+    constexpr bool PAIR = kPairResident;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uni(tid >> 6);
+    const int team = 1 << p.team_shift;
+    const int mb = (int)blockIdx.x / p.n_seg, seg = (int)blockIdx.x - mb * p.n_seg;
+    const int row0 = mb * p.row_step;
+    const int member = wave & (team - 1);
+    const int ti = seg + (wave >> p.team_shift) * p.n_seg;
+    const bool active = ti < p.T;                            // wave-uniform
+    const TileU d = fetch_tile(p, active ? ti : 0);
+    const int s0 = (d.nsteps * member) >> p.team_shift, s1 = (d.nsteps * (member + 1)) >> p.team_shift;
+    const bool steps = active && s0 < s1;
+    const unsigned char* goff = p.blob + p.off_goff + (long)d.first_step * 32;
+    const unsigned char* bvals = p.blob + p.off_bvals + (long)d.first_step * NCB * 1024;
+    unsigned dpos[NCB];
+    StepRegs<NCB> rg;
+    auto first_operands = [&] {
+        const unsigned* dp = (const unsigned*)(p.blob + p.off_dpos) + ((long)d.tile * 32 + (lane & 31)) * NCB;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) dpos[cb] = dp[cb];
+        prefetch_first_steps<NCB>(rg, goff, bvals, steps ? s0 : 0, steps ? s1 : 1, lane);
+    };
+    // A in one batch where it is short (768 columns), else in batches of twelve requests
+    auto stage_a = [&](auto batch) {
+        constexpr int B = decltype(batch)::value;
+        const int tasks = TRANS ? at_tasks<MS>(p.K) : a_tasks<MS, PAIR>(p.K);
+        constexpr int per = kWaves * (TRANS || !PAIR ? B : B / 2);
+        for (int t0 = wave; t0 < tasks || t0 == wave; t0 += per) {
+            ARegs<B> ar;
+            if constexpr (TRANS) at_issue<MS, B>(p, ar, row0, 0, p.K, t0, lane);
+            else a_issue<MS, B, PAIR>(p, ar, row0, 0, p.K, t0, lane);
+            if (t0 == wave) first_operands();
+            if constexpr (TRANS) at_commit<MS, B>(p, ar, smem, p.K, t0, lane);
+            else a_commit<MS, B, PAIR>(p, ar, smem, p.K, t0, lane);
+        }
+    };
+    if (p.K <= 768) stage_a(std::integral_constant<int, 6>{});
+    else stage_a(std::integral_constant<int, 12>{});
+    a_zero_row(p, smem, 32 * MS, tid);
+    __syncthreads();
+    tw_f32x16 acc[MS][NCB];
+    zero_acc<MS, NCB>(acc);
+    if (steps) run_steps<DT, MS, NCB>(acc, rg, smem, at_pitch_of<MS>(), goff, bvals, s0, s1, lane);
+    __syncthreads();                                         // everyone is done with A: the sums take its place
+    unsigned char* sums = smem + wave * (NCB * 4096);        // piece (cb, q) of a wave: 1 KB, 16 bytes a lane
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(tw_f32x4*)(sums + (cb * 4 + q) * 1024 + lane * 16) =
+                tw_f32x4{acc[0][cb][4 * q], acc[0][cb][4 * q + 1], acc[0][cb][4 * q + 2], acc[0][cb][4 * q + 3]};
+    __syncthreads();
+    // this wave's share: passes u0 .. u1 of eight rows (four in all), or column blocks on the transposed boundary
+    constexpr int UNITS = TRANS ? NCB : 4;
+    const int per = (UNITS + team - 1) >> p.team_shift;
+    const int u0 = member * per, u1 = u0 + per < UNITS ? u0 + per : UNITS;
+    const unsigned char* first = smem + (wave - member) * (NCB * 4096) + lane * 16;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int u = TRANS ? cb : q;
+            if (u < u0 || u >= u1) continue;                 // wave-uniform
+            tw_f32x4 v = *(const tw_f32x4*)(first + (cb * 4 + q) * 1024);
+            for (int i = 1; i < team; ++i) v += *(const tw_f32x4*)(first + i * (NCB * 4096) + (cb * 4 + q) * 1024);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[0][cb][4 * q + e] = v[e];
+        }
+    __syncthreads();                                         // the staging areas of the epilogue lie over the sums
+    if (!active || u0 >= u1) return;
+    unsigned char* stage = smem + p.stage_off + wave * kStageBytes;
+    if constexpr (TRANS) store_tile_t<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, u0, u1);
+    else store_tile<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, u0, u1);
+}
+
 }  // namespace
 
 // ---- kernel tables
@@ -1742,6 +1830,7 @@ namespace tw_parts {
 template <int DT, bool FUSED, bool EW> const void* pick_mode(int mode, int ms, int ncb, bool nta);     // row-major boundary
 template <int DT, bool FUSED, bool EW> const void* pick_mode_t(int mode, int ms, int ncb, bool nta);   // transposed boundary
 template <int DT, bool FUSED> const void* pick_reduce(int ncb, bool transposed);               // second kernel of split K
+template <int DT, bool FUSED> const void* pick_team(int ncb, bool transposed);                 // teams of waves per tile
 }  // namespace tw_parts
 
 #if !defined(TW_PART) || TW_PART != 0
@@ -1789,6 +1878,15 @@ const void* pick_reduce(int ncb, bool transposed) {
         default: return nullptr;
     }
 }
+template <int DT, bool FUSED>
+const void* pick_team(int ncb, bool transposed) {
+    switch (ncb) {
+        case 1: return transposed ? (const void*)tw_team_kernel<DT, 1, FUSED, true> : (const void*)tw_team_kernel<DT, 1, FUSED, false>;
+        case 2: return transposed ? (const void*)tw_team_kernel<DT, 2, FUSED, true> : (const void*)tw_team_kernel<DT, 2, FUSED, false>;
+        case 4: return transposed ? (const void*)tw_team_kernel<DT, 4, FUSED, true> : (const void*)tw_team_kernel<DT, 4, FUSED, false>;
+        default: return nullptr;
+    }
+}
 }  // namespace tw_parts
 #endif
 
@@ -1796,7 +1894,9 @@ const void* pick_reduce(int ncb, bool transposed) {
 #define TW_TABLES_EW(KW, DT, FUSED, EW)                                          \
     KW template const void* tw_parts::pick_mode<DT, FUSED, EW>(int, int, int, bool);  \
     KW template const void* tw_parts::pick_mode_t<DT, FUSED, EW>(int, int, int, bool);
-#define TW_TABLES_REDUCE(KW, DT, FUSED) KW template const void* tw_parts::pick_reduce<DT, FUSED>(int, bool);
+#define TW_TABLES_REDUCE(KW, DT, FUSED)                                           \
+    KW template const void* tw_parts::pick_reduce<DT, FUSED>(int, bool);          \
+    KW template const void* tw_parts::pick_team<DT, FUSED>(int, bool);
 #define TW_TABLES_ALL(KW, DT, FUSED) TW_TABLES_EW(KW, DT, FUSED, false) TW_TABLES_EW(KW, DT, FUSED, true) TW_TABLES_REDUCE(KW, DT, FUSED)
 #if TW_PART == 0
 TW_TABLES_ALL(extern, TW_F16, false) TW_TABLES_ALL(extern, TW_F16, true) TW_TABLES_ALL(extern, TW_BF16, false) TW_TABLES_ALL(extern, TW_BF16, true)
@@ -2040,6 +2140,7 @@ struct Plan {
     unsigned urow_off;   // transposed boundary, loading waves: LDS offset of their row lists (0: whole chunks are read)
     unsigned xbuf_off;   // row-major boundary, K resident, TEW blob with residual-only columns: LDS offset of the waves' areas for them
     int n_parts, chunks_per_part;   // split K (see TwGemmParams); n_parts = 1: none
+    int team_shift;                 // log2 of the waves that share a tile (tw_team_kernel), 0: none
     size_t partial_bytes;           // workspace the parts' fp32 results take, behind the counters
 };
 
@@ -2161,6 +2262,18 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     // (Not where the tiles add the residual-only columns of a TEW blob themselves: a split leaves those to the pass
     // of their own, which reads all of A once more - 92 against 46 us on the FFN-down of BERT-base at 512 rows.)
     pl.n_parts = 1; pl.chunks_per_part = h->n_chunks; pl.partial_bytes = 0;
+    // K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves share the tiles
+    // (tw_team_kernel).  Calls back to back in a graph, a wave per tile -> teams: 768 -> 3072 at 1 / 64 / 512 rows
+    // 8.2 / 9.9 / 10.3 -> 7.5 / 8.5 / 8.9 us, 768 -> 768 at 256 / 2048 rows 9.9 / 10.7 -> 8.5 / 8.9 us, transposed
+    // 768 -> 2304 at 512 tokens 8.2 -> 7.0 us, 1500 -> 800 at 100 tokens 11.5 -> 8.0 us.  With five tiles or more nearly every
+    // wave has a tile of its own.  (TEW blobs stay with a wave per tile: a tile's residual has steps of another kind.)
+    pl.team_shift = 0;
+    const int most = (T + nseg - 1) / nseg;                           // tiles of a workgroup at most
+    if (resident && msb == 1 && items <= n_cu && most <= kWaves / 2 && h->ew_nnz == 0) {
+        pl.team_shift = most <= 1 ? 3 : most <= 2 ? 2 : 1;
+        const unsigned sums = (unsigned)kWaves * h->ncb * 4096u;      // the waves' fp32 sums, over A and the staging areas
+        if (sums > pl.lds_bytes) pl.lds_bytes = sums;
+    }
     if (!resident && msb == 2 && h->n_chunks >= 2 && (pl.xbuf_off == 0 || transposed)) {
         const long nmb1 = (M + 63) / 64;
         const size_t tile_bytes = (size_t)2 * h->ncb * 4096;          // fp32 results of a tile: 64 rows x G columns
@@ -2218,6 +2331,11 @@ const void* pick_kernel_t(int dt, int mode, int ms, int ncb, bool fused, bool nt
 }
 const void* pick_kernel(int dt, int mode, int ms, int ncb, bool fused, bool nta, bool ew) {
     return ew ? pick_kernel_of<true>(dt, mode, ms, ncb, fused, nta) : pick_kernel_of<false>(dt, mode, ms, ncb, fused, nta);
+}
+const void* pick_team_kernel(int dt, int ncb, bool fused, bool transposed) {
+    using namespace tw_parts;
+    if (fused) return dt == TW_F16 ? pick_team<TW_F16, true>(ncb, transposed) : pick_team<TW_BF16, true>(ncb, transposed);
+    return dt == TW_F16 ? pick_team<TW_F16, false>(ncb, transposed) : pick_team<TW_BF16, false>(ncb, transposed);
 }
 const void* pick_reduce_kernel(int dt, int ncb, bool fused, bool transposed) {
     using namespace tw_parts;
@@ -2405,14 +2523,15 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     // streamed K: the activations carry the streaming hint only when one workgroup reads a row block's rows
     const bool nta = pl.mode == 0 || pl.n_seg == 1;
     const int kmode = split ? 3 : pl.mode;             // the kernel's MODE
-    const void* fn = pick_kernel(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+    const bool team = pl.team_shift > 0;
+    const void* fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, false) : pick_kernel(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
     if (!fn) return TW_ERR_UNSUPPORTED;
     const void* fn_reduce = nullptr;
     if (split) {
         fn_reduce = pick_reduce_kernel(h->dtype, h->ncb, fused_epilogue, false);
         if (!fn_reduce) return TW_ERR_UNSUPPORTED;
     }
-    const int variant = kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..7
+    const int variant = team ? 8 : kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..8
     const int kernel_id = (h->ew_nnz > 0 ? 240 : 0) + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant + (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
     rc = ensure_lds(dev, kernel_id, fn);
     if (rc) return rc;
@@ -2438,7 +2557,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     p.stream_stores = ((uintptr_t)C & 127) == 0 && (ldc & 63) == 0;
     p.off_xc_tile_ptr = h->off_xc_tile_ptr; p.off_xc_col = h->off_xc_col; p.off_xc_ptr = h->off_xc_ptr;
     p.off_xc_k = h->off_xc_k; p.off_xc_v = h->off_xc_v; p.xbuf_off = pl.xbuf_off;
-    p.n_parts = pl.n_parts; p.chunks_per_part = pl.chunks_per_part;
+    p.n_parts = pl.n_parts; p.chunks_per_part = pl.chunks_per_part; p.team_shift = pl.team_shift;
     p.partials = (float*)((unsigned char*)workspace + 256);
     const int grid = pl.n_items < n_cu ? pl.n_items : n_cu;
     void* args[] = {(void*)&p};
@@ -2497,14 +2616,15 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's
     const bool nta = pl.mode == 0 || pl.n_seg == 1;
     const int kmode = split ? 3 : pl.mode;             // the kernel's MODE
-    const void* fn = pick_kernel_t(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+    const bool team = pl.team_shift > 0;
+    const void* fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, true) : pick_kernel_t(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
     if (!fn) return TW_ERR_UNSUPPORTED;
     const void* fn_reduce = nullptr;
     if (split) {
         fn_reduce = pick_reduce_kernel(h->dtype, h->ncb, fused_epilogue, true);
         if (!fn_reduce) return TW_ERR_UNSUPPORTED;
     }
-    const int variant = kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..7
+    const int variant = team ? 8 : kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..8
     const int kernel_id = (h->ew_nnz > 0 ? 240 : 0) + 120 + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant + (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
     rc = ensure_lds(dev, kernel_id, fn);
     if (rc) return rc;
@@ -2531,7 +2651,7 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     p.off_xc_tile_ptr = h->off_xc_tile_ptr; p.off_xc_col = h->off_xc_col; p.off_xc_ptr = h->off_xc_ptr;
     p.off_xc_k = h->off_xc_k; p.off_xc_v = h->off_xc_v; p.xbuf_off = pl.xbuf_off;
     p.stream_stores = ((uintptr_t)Ct & 127) == 0 && (ldct & 63) == 0;
-    p.n_parts = pl.n_parts; p.chunks_per_part = pl.chunks_per_part;
+    p.n_parts = pl.n_parts; p.chunks_per_part = pl.chunks_per_part; p.team_shift = pl.team_shift;
     p.partials = (float*)((unsigned char*)workspace + 256);
     const unsigned lds_bytes = pl.lds_bytes;
     const int grid = pl.n_items < n_cu ? pl.n_items : n_cu;

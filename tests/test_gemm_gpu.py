@@ -301,6 +301,44 @@ def test_dense_gemm_ring(tw, case):
     assert bool(torch.isnan(Cbuf[:, N:].float()).all().item()), "wrote outside C"
 
 
+# name, M, K, N, G, type, keep, tiles of a workgroup at most: 8 and 4 waves to a tile; fewer steps than waves; the
+# longest resident K in several batches of A; one row; a last row block of one row; K that is no multiple of 8
+TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1), ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1),
+         ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1), ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1),
+         ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2), ("wide_spans", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1)]
+
+
+@pytest.mark.parametrize("case", TEAMS, ids=[c[0] for c in TEAMS])
+def test_teams_of_waves(tw, case):
+    """Waves that share a tile: every element on both boundaries, plain and with the fused epilogue, twice the same bits."""
+    name, M, K, N, G, dtype, keep, most = case
+    _say(f"teams {name} M={M} K={K} N={N} G={G} {dtype}")
+    spec = W.small_spec("team_" + name, M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.7 if name == "wide_spans" else 0.06, keep=keep,
+                        seed_offset=8800 + sum(map(ord, name)))
+    w = W.generate(spec)
+    wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
+    T = wt.info["T"]
+    assert pl["mode"] == 0 and pl["rows_per_block"] == 32 and pl["n_items"] == pl["grid"]
+    tiles = (T + pl["n_sets"] - 1) // pl["n_sets"]
+    assert tiles <= most and (most < 4 or tiles > 2) and (most != 2 or tiles == 2), (pl, T)
+    A = _device_A(tw, w.A, dtype)
+    At = torch.zeros((K, (M + 7) // 8 * 8), dtype=A.dtype, device="cuda:0")[:, :M]
+    At.copy_(A.t())
+    bbits = _bias_bits(N, dtype, 21)
+    bias, b64 = tw.bits_to_tensor(bbits, dtype), tw_ref.decode(bbits, dtype)
+    nan = lambda r, c: torch.full((r, (c + 7) // 8 * 8), float("nan"), dtype=A.dtype, device="cuda:0")[:, :c]
+    for act in (None, "gelu"):
+        post = None if act is None else (lambda ref: tw_ref.bias_act(ref, b64, act))
+        b, a = (None, "none") if act is None else (bias, act)
+        C, C2 = (tw.tw_gemm_bias_act(wt, A, b, a, nan(M, N)) for _ in range(2))
+        Ct, Ct2 = (tw.tw_gemm_t_bias_act(wt, At, b, a, nan(N, M)) for _ in range(2))
+        torch.cuda.synchronize()
+        assert torch.equal(C, C2) and torch.equal(Ct, Ct2)
+        _compare_whole(C, w.A, w.B, w.mask, dtype, what=name, post=post)
+        _compare_whole(Ct, w.A, w.B, w.mask, dtype, transposed=True, what=name + " transposed", post=post)
+
+
 # ------------------------------------------------------------------ the five workloads, full size
 def test_config1_full(tw):
     _say("config 1, every element")
