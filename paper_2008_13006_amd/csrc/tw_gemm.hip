@@ -491,9 +491,27 @@ __device__ __forceinline__ void apply_bias_act(tw_f32x16 (&acc)[MS][NCB], const 
         }
 }
 
+// The same for a wave that stores a part of the tile only: units u0 .. u1, passes of eight rows (ROWS) or column blocks.
+// The activation is bound by the vector ALU, and a wave of a team or of a split-K product's second kernel has one or two
+// of 4 to 8 units: with GELU on all of them 512 rows of 768 -> 2304 took 13.7 us, this way 11.0.
+template <int MS, int NCB, bool ROWS>
+__device__ __forceinline__ void apply_bias_act_part(tw_f32x16 (&acc)[MS][NCB], const EpiBias<NCB>& eb, int act, int u0, int u1) {
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int u = ROWS ? 4 * ms + q : cb;
+                if (u < u0 || u >= u1) continue;             // wave-uniform
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[ms][cb][4 * q + e] = tw_activate(acc[ms][cb][4 * q + e] + eb.col[cb], act);
+            }
+}
+
 // FUSED: the kernel variant with the fused epilogue (a bias and / or an activation); the plain variant
-// carries none of its code.
-template <int DT, int MS, int NCB, bool FUSED>
+// carries none of its code.  PART: a wave that stores a part of the tile.
+template <int DT, int MS, int NCB, bool FUSED, bool PART = false>
 __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d, tw_f32x16 (&acc)[MS][NCB],
                                            unsigned char* stage, const unsigned (&dpos)[NCB], int row0, int lane_in,
                                            unsigned short* xbuf = nullptr,
@@ -511,7 +529,8 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
     EpiBias<NCB> eb;
     if constexpr (FUSED) {
         fetch_epi_bias<DT, NCB>(p, d, dpos, eb, lane);
-        apply_bias_act<MS, NCB>(acc, eb, p.act);
+        if constexpr (PART) apply_bias_act_part<MS, NCB, true>(acc, eb, p.act, pass0, pass1);
+        else apply_bias_act<MS, NCB>(acc, eb, p.act);
     }
     const int h = lane >> 5, n = lane & 31;
     const int blk = lane >> 4, j = lane & 15;
@@ -821,7 +840,7 @@ __device__ __forceinline__ void stage_commit(const TwGemmParams& p, const ARegs<
 // The destination row of a staged row comes from the lane that owns that packed column
 // (ds_bpermute).  The pruned columns inside the tile's span are written as lines of zeros from the
 // packer's list.
-template <int DT, int MS, int NCB, bool FUSED>
+template <int DT, int MS, int NCB, bool FUSED, bool PART = false>
 __device__ __forceinline__ void store_tile_t(const TwGemmParams& p, const TileU& d, tw_f32x16 (&acc)[MS][NCB],
                                              unsigned char* stage, const unsigned (&dpos)[NCB], int m0, int lane_in,
                                              int cb0 = 0, int cb1 = NCB, const unsigned short* xbuf = nullptr) {
@@ -836,7 +855,8 @@ __device__ __forceinline__ void store_tile_t(const TwGemmParams& p, const TileU&
         for (int cb = 0; cb < NCB; ++cb)
             eb.col[cb] = (p.bias != nullptr && dpos[cb] != 0xFFFFFFFFu)
                              ? tw_to_f32<DT>(p.bias[(d.span_start & ~7) + (int)dpos[cb]]) : 0.f;
-        apply_bias_act<MS, NCB>(acc, eb, p.act);
+        if constexpr (PART) apply_bias_act_part<MS, NCB, false>(acc, eb, p.act, cb0, cb1);
+        else apply_bias_act<MS, NCB>(acc, eb, p.act);
     }
     const int n = lane & 31, h = lane >> 5, rr = lane / PPR, pc = lane % PPR;
     const int origin = d.span_start & ~7;
@@ -1727,8 +1747,8 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
                     for (int e = 0; e < 4; ++e) acc[ms][cb][4 * q + e] = s[TRANS ? msq : cb][e];
                 }
             }
-    if constexpr (TRANS) store_tile_t<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, sub, sub + 1);
-    else store_tile<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, sub, sub + 1);
+    if constexpr (TRANS) store_tile_t<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, sub, sub + 1);
+    else store_tile<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, sub, sub + 1);
 }
 
 // K resident, row blocks of 32, few tiles per workgroup: a TEAM of 8, 4 or 2 waves shares a tile.
@@ -1814,8 +1834,8 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
     __syncthreads();                                         // the staging areas of the epilogue lie over the sums
     if (!active || u0 >= u1) return;
     unsigned char* stage = smem + p.stage_off + wave * kStageBytes;
-    if constexpr (TRANS) store_tile_t<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, u0, u1);
-    else store_tile<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, u0, u1);
+    if constexpr (TRANS) store_tile_t<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, u0, u1);
+    else store_tile<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, u0, u1);
 }
 
 }  // namespace
