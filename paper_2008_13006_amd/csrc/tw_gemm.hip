@@ -2187,23 +2187,30 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
     return buffers * at_bytes(msb, k_chunk) + kWaves * kStageBytes + 16u;
 }
 
+// Estimate of an item with K resident, in microseconds: launch and first operands, bringing in 32 * msb rows of A while the
+// whole chip does, the packed weights of its tiles through the compute unit's vector L1 or the steps of a heavy tile
+// (half again as many as the mean) one after the other, whichever takes longer, and the stores.  Fitted to
+// K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item, both boundaries (within 20 % of most of 150 plans timed).
+double resident_item_us(const TwHeader* h, int msb, int tiles) {
+    constexpr double kStartUs = 5.0, kStageBytesPerUs = 20e3, kWeightBytesPerUs = 70e3, kStepUs = 0.1, kStoreBytesPerUs = 32e3;
+    const double steps = (double)h->total_steps / h->T;
+    const double weights = tiles * steps * h->ncb * 1024.0 / kWeightBytesPerUs;
+    const int team = msb > 1 || tiles > kWaves / 2 || h->ew_nnz > 0 ? 1 : tiles <= 1 ? 8 : tiles <= 2 ? 4 : 2;   // (tw_team_kernel)
+    const double chain = 1.5 * steps * kStepUs * ((tiles + kWaves - 1) / kWaves) / team;
+    return kStartUs + 64.0 * msb * h->K / kStageBytesPerUs + (weights > chain ? weights : chain) +
+           tiles * 64.0 * msb * h->G / kStoreBytesPerUs;
+}
+
 int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0) {
     const bool resident = h->n_chunks == 1;
     const int buffers = resident ? 1 : 2;
     if (lds_need(1, h->k_chunk, buffers) > kLdsLimit) return TW_ERR_UNSUPPORTED;
     const int T = h->T;
     // msb: 32-row blocks in a workgroup's row block; tpw: tiles a workgroup of the streamed kernel holds
+    int segs = 1;                // resident K: workgroups that share a row block's tiles
     auto items_for = [&](int msb, int tpw, int& n_mblocks, int& n_seg) {
         n_mblocks = (M + 32 * msb - 1) / (32 * msb);
-        if (resident) {
-            // split a row block's tiles over several workgroups only when there are too few row blocks
-            n_seg = 1;
-            if (n_mblocks < n_cu) n_seg = (n_cu + n_mblocks - 1) / n_mblocks;
-            if (n_seg > T) n_seg = T;
-            if (n_seg < 1) n_seg = 1;
-            return (long)n_mblocks * n_seg;
-        }
-        n_seg = (T + tpw - 1) / tpw;
+        n_seg = resident ? segs : (T + tpw - 1) / tpw;
         return (long)n_mblocks * n_seg;
     };
     int msb = 2, tpw = kWaves;
@@ -2211,8 +2218,40 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     if (lds_need(2, h->k_chunk, buffers) > kLdsLimit) msb = 1;
     pl.mode = resident ? 0 : 1;
     if (resident) {
-        // 64-row blocks halve the traffic of packed B, but only pay when they still fill the GPU
-        if (msb == 2 && items_for(2, tpw, nmb, nseg) < n_cu) msb = 1;
+        // 64-row blocks with all tiles when they give every compute unit an item.  With fewer the height of the row blocks
+        // and the workgroups per row block are what the estimate below finds fastest.  What it has to get right is
+        // the number of rounds: a second one costs as much as the first, nothing of it overlaps.  (Before, the tiles
+        // were shared out over ceil(units / row blocks) workgroups, which is up to twice as many as a round holds.)
+        // Back to back in a graph, before ->
+        // now: 768 -> 3072 at 1000 / 3000 / 12000 rows 13.1 -> 10.1, 34.5 -> 18.4, 54 -> 39.5 us; 768 -> 768 at 8192 15.8 -> 12.9;
+        // 1400 -> 2000 at 3000 37 -> 20; 1000 -> 1234 (G = 32) at 4321 36.5 -> 25.3; transposed 768 -> 2304 at 6000 tokens
+        // 35 -> 19.6, 500 -> 4000 (G = 32) at 5000 39 -> 23.0; 768 -> 3072 at 16384 and 17000 as before.
+        // (Kept as it was: 64-row blocks that make exactly one full round with a short K, the plan that the bit-exact tests
+        // pin; the estimate's choice takes 9.1 us there instead of 11.7, 256 -> 390 at 8192 rows.)
+        const long nmb_full = (M + 32L * msb - 1) / (32 * msb);
+        long segs_full = nmb_full < n_cu ? (n_cu + nmb_full - 1) / nmb_full : 1;
+        if (segs_full > T) segs_full = T;
+        if (msb == 2 && h->K <= 256 && nmb_full * segs_full == n_cu) {
+            segs = (int)segs_full;
+        } else if (nmb_full < n_cu || msb == 1) {
+            double best = 0.0;
+            const int top = msb;
+            for (int m = top; m >= 1; --m) {
+                const long blocks = (M + 32L * m - 1) / (32 * m);
+                // (sharing a row block's tiles out any further than this only adds rounds)
+                const long most_segs = blocks < n_cu ? 2 * n_cu / blocks + 1 : 3;
+                for (int sg = 1; sg <= T && sg <= most_segs; ++sg) {
+                    const int tiles = (T + sg - 1) / sg;
+                    if (sg > 1 && (T + sg - 2) / (sg - 1) == tiles) continue;     // (as many tiles with fewer workgroups)
+                    const double rounds = (double)((blocks * sg + n_cu - 1) / n_cu);
+                    const double cost = rounds * resident_item_us(h, m, tiles);
+                    if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
+                }
+            }
+            // in one round: a tile fewer for as many workgroups as there is room for
+            const long blocks = (M + 32L * msb - 1) / (32 * msb);
+            while (segs < T && blocks * (segs + 1) <= n_cu) ++segs;
+        }
     } else if (msb == 2) {
         // Streamed K, 64-row blocks.  Eight tiles per workgroup (a wave per tile) when that gives every compute
         // unit an item and there are more than four tiles.  Else four waves multiply and four only load A

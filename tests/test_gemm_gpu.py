@@ -301,11 +301,12 @@ def test_dense_gemm_ring(tw, case):
     assert bool(torch.isnan(Cbuf[:, N:].float()).all().item()), "wrote outside C"
 
 
-# name, M, K, N, G, type, keep, tiles of a workgroup at most: 8 and 4 waves to a tile; fewer steps than waves; the
+# name, M, K, N, G, type, keep, tiles of a workgroup at most: 8, 4 and 2 waves to a tile; fewer steps than waves; the
 # longest resident K in several batches of A; one row; a last row block of one row; K that is no multiple of 8
 TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1), ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1),
          ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1), ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1),
-         ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2), ("wide_spans", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1)]
+         ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2), ("wide_spans", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1),
+         ("two_waves", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4)]
 
 
 @pytest.mark.parametrize("case", TEAMS, ids=[c[0] for c in TEAMS])

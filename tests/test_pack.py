@@ -375,6 +375,25 @@ def test_plan_fills_the_last_round_on_the_row_major_boundary():
         assert tw.tw_gemm_plan(blob, M, n_cu=256, transposed=True)["rows_per_block"] == 64
 
 
+def test_plan_of_few_row_blocks_makes_one_round():
+    """K resident, fewer 64-row blocks than compute units: the tiles are shared out over no more workgroups than one
+    round holds wherever one round is possible, and every tile has a workgroup."""
+    for K, N, G, sizes in ((768, 3072, 128, (1, 31, 64, 500, 1000, 2048, 3000, 4321, 8000, 12000, 16000)), (1000, 1234, 32, (1, 33, 4321, 8000)),
+                           (1536, 700, 64, (5, 700, 3000, 8191)), (64, 96, 32, (1, 4000, 9000))):
+        spec = W.small_spec("plan_few", M=8, K=K, N=N, G=G, dtype="f16", col_prune=0.05, keep=("upow", 0.1, 0.5), seed_offset=77 + K)
+        w = W.generate(spec, with_A=False)
+        blob = tw.tw_pack(w.B, w.mask, G, "f16")
+        T = tw.tw_info(blob)["T"]
+        for M in sizes:
+            for n_cu in (64, 256, 304):
+                for tr in (False, True):
+                    pl = tw.tw_gemm_plan(blob, M, n_cu=n_cu, transposed=tr)
+                    assert pl["mode"] == 0 and 1 <= pl["n_sets"] <= T and pl["lds_bytes"] <= 160 * 1024
+                    assert pl["n_row_blocks"] * pl["rows_per_block"] >= M
+                    if (M + 31) // 32 <= n_cu:
+                        assert pl["n_items"] <= n_cu, (K, M, n_cu, tr, pl)
+
+
 def test_plan_limits_and_errors():
     rng = np.random.default_rng(3)
     for K, N, G in [(64, 256, 128), (1536, 128, 32), (1544, 128, 64), (3000, 300, 128)]:
