@@ -440,6 +440,15 @@ struct EpiBias {
     float fill[kWinLines];
 };
 
+// Bias of this lane's packed columns.
+template <int DT, int NCB>
+__device__ __forceinline__ void fetch_col_bias(const TwGemmParams& p, const TileU& d, const unsigned (&dpos)[NCB], float (&col)[NCB]) {
+    const int origin = d.span_start & ~7;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+        col[cb] = p.bias != nullptr && dpos[cb] != 0xFFFFFFFFu ? tw_to_f32<DT>(p.bias[origin + (int)dpos[cb]]) : 0.f;
+}
+
 // Reads what store_tile needs of the bias.
 template <int DT, int NCB>
 __device__ __forceinline__ void fetch_epi_bias(const TwGemmParams& p, const TileU& d, const unsigned (&dpos)[NCB],
@@ -491,26 +500,30 @@ __device__ __forceinline__ void apply_bias_act(tw_f32x16 (&acc)[MS][NCB], const 
         }
 }
 
-// The same for a wave that stores a part of the tile only: units u0 .. u1, passes of eight rows (ROWS) or column blocks.
-// The activation is bound by the vector ALU, and a wave of a team or of a split-K product's second kernel has one or two
-// of 4 to 8 units: with GELU on all of them 512 rows of 768 -> 2304 took 13.7 us, this way 11.0.
-template <int MS, int NCB, bool ROWS>
-__device__ __forceinline__ void apply_bias_act_part(tw_f32x16 (&acc)[MS][NCB], const EpiBias<NCB>& eb, int act, int u0, int u1) {
+// The same for pieces of four results, in the waves that store a part of a tile only (teams of waves, second kernel of a
+// split-K product): they have one or two of a tile's 4 to 8 units.  The activation is bound by the vector ALU: with
+// GELU on the accumulators of all units 512 rows of 768 -> 2304 took 13.7 us, this way 11.0.
+template <int NV>
+__device__ __forceinline__ void apply_bias_act4(tw_f32x4 (&v)[NV], const float (&bias)[NV], int act) {
+    if (act == TW_ACT_GELU) {                               // wave-uniform
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms)
+        for (int i = 0; i < NV; ++i)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
+            for (int e = 0; e < 4; ++e) v[i][e] = tw_gelu(v[i][e] + bias[i]);
+    } else {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int u = ROWS ? 4 * ms + q : cb;
-                if (u < u0 || u >= u1) continue;             // wave-uniform
+        for (int i = 0; i < NV; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[ms][cb][4 * q + e] = tw_activate(acc[ms][cb][4 * q + e] + eb.col[cb], act);
+            for (int e = 0; e < 4; ++e) {
+                const float x = v[i][e] + bias[i];
+                v[i][e] = act == TW_ACT_RELU && !(x > 0.f) ? 0.f : x;
             }
+    }
 }
 
 // FUSED: the kernel variant with the fused epilogue (a bias and / or an activation); the plain variant
-// carries none of its code.  PART: a wave that stores a part of the tile.
+// carries none of its code.  PART: a wave that stores a part of the tile; bias and activation have been applied (pruned
+// columns inside the span still take theirs here).
 template <int DT, int MS, int NCB, bool FUSED, bool PART = false>
 __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d, tw_f32x16 (&acc)[MS][NCB],
                                            unsigned char* stage, const unsigned (&dpos)[NCB], int row0, int lane_in,
@@ -529,8 +542,7 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
     EpiBias<NCB> eb;
     if constexpr (FUSED) {
         fetch_epi_bias<DT, NCB>(p, d, dpos, eb, lane);
-        if constexpr (PART) apply_bias_act_part<MS, NCB, true>(acc, eb, p.act, pass0, pass1);
-        else apply_bias_act<MS, NCB>(acc, eb, p.act);
+        if constexpr (!PART) apply_bias_act<MS, NCB>(acc, eb, p.act);
     }
     const int h = lane >> 5, n = lane & 31;
     const int blk = lane >> 4, j = lane & 15;
@@ -849,14 +861,13 @@ __device__ __forceinline__ void store_tile_t(const TwGemmParams& p, const TileU&
     constexpr int PPR = 4 * MS, RPI = 64 / PPR, PITCH = 64 * MS + 8;
     static_assert(32 * PITCH <= (int)kStageBytes, "transposed staging fits the wave's area");
     const int lane = fresh(lane_in);
-    if constexpr (FUSED) {   // bias of this lane's packed columns (rows of Ct), activation in place
+    if constexpr (FUSED && !PART) {   // bias of this lane's packed columns (rows of Ct), activation in place
         EpiBias<NCB> eb;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
             eb.col[cb] = (p.bias != nullptr && dpos[cb] != 0xFFFFFFFFu)
                              ? tw_to_f32<DT>(p.bias[(d.span_start & ~7) + (int)dpos[cb]]) : 0.f;
-        if constexpr (PART) apply_bias_act_part<MS, NCB, false>(acc, eb, p.act, cb0, cb1);
-        else apply_bias_act<MS, NCB>(acc, eb, p.act);
+        apply_bias_act<MS, NCB>(acc, eb, p.act);
     }
     const int n = lane & 31, h = lane >> 5, rr = lane / PPR, pc = lane % PPR;
     const int origin = d.span_start & ~7;
@@ -1725,13 +1736,42 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) dpos[cb] = dp[cb];
     }
-#pragma unroll 2
-    for (int part = 1; part < p.n_parts; ++part) {
-        tw_f32x4 v[NL];
+    // All parts of an ordinary plan are requested before the first is added, not two at a time (a round trip to memory
+    // for every two: 3072 -> 768 at 64 / 512 rows 12.4 / 19.8 -> 11.5 / 18.6 us, transposed 4608 -> 500 at 100 tokens 15.5 -> 11.4);
+    // past the last part the last one is requested again, and not added.
+    constexpr int kAhead = TRANS ? 4 : 7;
+    float col[NCB];
 #pragma unroll
-        for (int i = 0; i < NL; ++i) v[i] = *(const tw_f32x4*)(src + part * part_stride + off[i]);
+    for (int cb = 0; cb < NCB; ++cb) col[cb] = 0.f;
+    for (int part = 1; part < p.n_parts; part += kAhead) {
+        tw_f32x4 v[kAhead][NL];
 #pragma unroll
-        for (int i = 0; i < NL; ++i) s[i] += v[i];
+        for (int a = 0; a < kAhead; ++a) {
+            const int from = part + a < p.n_parts ? part + a : p.n_parts - 1;
+#pragma unroll
+            for (int i = 0; i < NL; ++i) v[a][i] = *(const tw_f32x4*)(src + from * part_stride + off[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FUSED)
+            if (part == 1) fetch_col_bias<DT, NCB>(p, d, dpos, col);      // (behind the parts' requests)
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+            if (part + a < p.n_parts) {                     // wave-uniform
+#pragma unroll
+                for (int i = 0; i < NL; ++i) s[i] += v[a][i];
+            }
+    }
+    if constexpr (FUSED) {
+        float b[NL];
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            b[i] = TRANS ? 0.f : col[TRANS ? 0 : i];
+            if constexpr (TRANS) {
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) b[i] = cb == sub ? col[cb] : b[i];
+            }
+        }
+        apply_bias_act4<NL>(s, b, p.act);
     }
     tw_f32x16 acc[MS][NCB];
     zero_acc<MS, NCB>(acc);
@@ -1815,6 +1855,8 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
             *(tw_f32x4*)(sums + (cb * 4 + q) * 1024 + lane * 16) =
                 tw_f32x4{acc[0][cb][4 * q], acc[0][cb][4 * q + 1], acc[0][cb][4 * q + 2], acc[0][cb][4 * q + 3]};
     __syncthreads();
+    float col[NCB];
+    if constexpr (FUSED) fetch_col_bias<DT, NCB>(p, d, dpos, col);
     // this wave's share: passes u0 .. u1 of eight rows (four in all), or column blocks on the transposed boundary
     constexpr int UNITS = TRANS ? NCB : 4;
     const int per = (UNITS + team - 1) >> p.team_shift;
@@ -1828,6 +1870,12 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
             if (u < u0 || u >= u1) continue;                 // wave-uniform
             tw_f32x4 v = *(const tw_f32x4*)(first + (cb * 4 + q) * 1024);
             for (int i = 1; i < team; ++i) v += *(const tw_f32x4*)(first + i * (NCB * 4096) + (cb * 4 + q) * 1024);
+            if constexpr (FUSED) {
+                tw_f32x4 v1[1] = {v};
+                const float b1[1] = {col[cb]};
+                apply_bias_act4<1>(v1, b1, p.act);
+                v = v1[0];
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[0][cb][4 * q + e] = v[e];
         }
