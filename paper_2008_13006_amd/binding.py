@@ -219,10 +219,12 @@ def _tdtype(dtype: str):
     return torch.float16 if dtype == "f16" else torch.bfloat16
 
 
-def _stream_ptr(stream=None) -> ctypes.c_void_p:
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream_ptr(stream=None) -> int:
+    # (the raw handle of the current device's current stream, without building a torch Stream object for it)
+    if stream is None:
+        c = _torch()._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def tw_gemm_workspace(blob: np.ndarray, M: int) -> int:
@@ -242,6 +244,7 @@ class TwWeight:
         self.blob = blob
         self.info = tw_info(blob)
         self.dtype = "f16" if self.info["dtype"] == TW_F16 else "bf16"
+        self.torch_dtype = _tdtype(self.dtype)
         self.blob_dev = torch.from_numpy(blob).to(device)
         assert self.blob_dev.data_ptr() % 256 == 0
         self.workspace = torch.zeros(256, dtype=torch.uint8, device=device)
@@ -249,11 +252,21 @@ class TwWeight:
         self._retired = []          # outgrown workspaces: kept, kernels already enqueued may still use them
         self._ws_need = {}          # M -> bytes the library wants (asked once per M)
 
+    @property
+    def blob(self) -> np.ndarray:
+        return self._blob
+
+    @blob.setter
+    def blob(self, value: np.ndarray):
+        # numpy takes longer to name an array's address than the library takes to check a call's arguments
+        self._blob, self._blob_ptr = value, value.ctypes.data
+
     def sibling(self):
         """Another TwWeight on the same host and device copy of the blob, with a workspace of its own."""
         torch = _torch()
         other = object.__new__(TwWeight)
         other.blob, other.info, other.dtype, other.blob_dev = self.blob, self.info, self.dtype, self.blob_dev
+        other.torch_dtype = self.torch_dtype
         other.workspace = torch.zeros(256, dtype=torch.uint8, device=self.workspace.device)
         other.ws_limit, other._retired, other._ws_need = self.ws_limit, [], {}
         return other
@@ -269,43 +282,47 @@ class TwWeight:
             torch = _torch()
             self._retired.append(self.workspace)
             self.workspace = torch.zeros(need, dtype=torch.uint8, device=self.workspace.device)
-        return ctypes.c_void_p(self.workspace.data_ptr()), need
+        return self.workspace.data_ptr(), need
 
     @classmethod
     def from_dense(cls, B_bits: np.ndarray, mask: np.ndarray, G: int, dtype: str, device="cuda:0"):
         return cls(tw_pack(B_bits, mask, G, dtype), device)
 
 
+def _row_operands(w: TwWeight, A, C):
+    """Checks A (and C where it is given) against the weight; (M, N)."""
+    info = w.info
+    assert A.is_cuda and A.dtype == w.torch_dtype and A.dim() == 2 and A.stride(1) == 1
+    M, K = A.shape
+    N = info["N"]
+    assert K == info["K"]
+    assert C is None or C.is_cuda and C.dtype == w.torch_dtype and C.shape == (M, N) and C.stride(1) == 1
+    return M, N
+
+
 def tw_gemm(w: TwWeight, A, C=None, stream=None):
     """C = A . (B * mask).  A: torch tensor [M, K] (f16/bf16, cuda, unit column stride)."""
-    torch = _torch()
-    assert A.is_cuda and A.dtype == _tdtype(w.dtype) and A.dim() == 2 and A.stride(1) == 1
-    M, K = A.shape
-    assert K == w.info["K"]
-    N = w.info["N"]
+    M, N = _row_operands(w, A, C)
     if C is None:
-        C = torch.empty((M, N), dtype=A.dtype, device=A.device)
-    assert C.is_cuda and C.dtype == A.dtype and C.shape == (M, N) and C.stride(1) == 1
-    lda = A.stride(0) if M > 1 else max(K, A.stride(0))
-    ldc = C.stride(0) if M > 1 else max(N, C.stride(0))
+        C = _torch().empty((M, N), dtype=A.dtype, device=A.device)
+    lda, ldc = A.stride(0), C.stride(0)
+    if M <= 1:
+        lda, ldc = max(w.info["K"], lda), max(N, ldc)
     ws, ws_bytes = w.workspace_for(M)
-    _check(_lib.tw_gemm(_np_ptr(w.blob), ctypes.c_void_p(w.blob_dev.data_ptr()), ctypes.c_void_p(A.data_ptr()),
-                        M, lda, ctypes.c_void_p(C.data_ptr()), ldc, ws, ws_bytes, _stream_ptr(stream)), "tw_gemm")
+    _check(_lib.tw_gemm(w._blob_ptr, w.blob_dev.data_ptr(), A.data_ptr(),
+                        M, lda, C.data_ptr(), ldc, ws, ws_bytes, _stream_ptr(stream)), "tw_gemm")
     return C
 
 
 def tw_gemm_static(w: TwWeight, A, C, stream=None):
     """tw_gemm without a workspace and without any allocation: the library's own per-GPU scratch array holds the
     scheduler's counters and the partial results of a split-K plan.  C must be given (the caller owns every buffer).  Calls must not overlap on one GPU."""
-    assert A.is_cuda and A.dtype == _tdtype(w.dtype) and A.dim() == 2 and A.stride(1) == 1
-    M, K = A.shape
-    N = w.info["N"]
-    assert K == w.info["K"]
-    assert C.is_cuda and C.dtype == A.dtype and C.shape == (M, N) and C.stride(1) == 1
-    lda = A.stride(0) if M > 1 else max(K, A.stride(0))
-    ldc = C.stride(0) if M > 1 else max(N, C.stride(0))
-    _check(_lib.tw_gemm_static(_np_ptr(w.blob), ctypes.c_void_p(w.blob_dev.data_ptr()), ctypes.c_void_p(A.data_ptr()),
-                               M, lda, ctypes.c_void_p(C.data_ptr()), ldc, _stream_ptr(stream)), "tw_gemm_static")
+    M, N = _row_operands(w, A, C)
+    lda, ldc = A.stride(0), C.stride(0)
+    if M <= 1:
+        lda, ldc = max(w.info["K"], lda), max(N, ldc)
+    _check(_lib.tw_gemm_static(w._blob_ptr, w.blob_dev.data_ptr(), A.data_ptr(),
+                               M, lda, C.data_ptr(), ldc, _stream_ptr(stream)), "tw_gemm_static")
     return C
 
 
@@ -317,7 +334,7 @@ def tw_gemm_t(w: TwWeight, At, Ct=None, stream=None):
 def tw_gemm_t_bias_act(w: TwWeight, At, bias=None, act="none", Ct=None, stream=None):
     """Ct = act(A . (B * mask) + bias)^T from At = A^T; bias: torch tensor [N] or None."""
     torch = _torch()
-    assert At.is_cuda and At.dtype == _tdtype(w.dtype) and At.dim() == 2 and At.stride(1) == 1
+    assert At.is_cuda and At.dtype == w.torch_dtype and At.dim() == 2 and At.stride(1) == 1
     K, M = At.shape
     assert K == w.info["K"]
     N = w.info["N"]
@@ -327,18 +344,18 @@ def tw_gemm_t_bias_act(w: TwWeight, At, bias=None, act="none", Ct=None, stream=N
     assert Ct.is_cuda and Ct.dtype == At.dtype and Ct.shape == (N, M) and Ct.stride(1) == 1
     ldat = At.stride(0) if K > 1 else max(M, At.stride(0))
     ldct = Ct.stride(0) if N > 1 else max(M, Ct.stride(0))
-    bptr = ctypes.c_void_p(0)
+    bptr = None
     if bias is not None:
         assert bias.is_cuda and bias.dtype == At.dtype and bias.shape == (N,) and bias.stride(0) == 1
-        bptr = ctypes.c_void_p(bias.data_ptr())
+        bptr = bias.data_ptr()
     ws, ws_bytes = w.workspace_for(M)
     if bias is None and _act_code(act) == TW_ACT_NONE:
-        _check(_lib.tw_gemm_t(_np_ptr(w.blob), ctypes.c_void_p(w.blob_dev.data_ptr()), ctypes.c_void_p(At.data_ptr()),
-                              M, ldat, ctypes.c_void_p(Ct.data_ptr()), ldct, ws, ws_bytes, _stream_ptr(stream)), "tw_gemm_t")
+        _check(_lib.tw_gemm_t(w._blob_ptr, w.blob_dev.data_ptr(), At.data_ptr(),
+                              M, ldat, Ct.data_ptr(), ldct, ws, ws_bytes, _stream_ptr(stream)), "tw_gemm_t")
     else:
-        _check(_lib.tw_gemm_t_bias_act(_np_ptr(w.blob), ctypes.c_void_p(w.blob_dev.data_ptr()),
-                                       ctypes.c_void_p(At.data_ptr()), M, ldat, bptr, _act_code(act),
-                                       ctypes.c_void_p(Ct.data_ptr()), ldct, ws, ws_bytes, _stream_ptr(stream)),
+        _check(_lib.tw_gemm_t_bias_act(w._blob_ptr, w.blob_dev.data_ptr(),
+                                       At.data_ptr(), M, ldat, bptr, _act_code(act),
+                                       Ct.data_ptr(), ldct, ws, ws_bytes, _stream_ptr(stream)),
                "tw_gemm_t_bias_act")
     return Ct
 
@@ -354,7 +371,7 @@ def tw_transpose(src, dst=None, stream=None):
     assert dst.shape == (cols, rows) and dst.dtype == src.dtype and dst.stride(1) == 1
     lds = src.stride(0) if rows > 1 else max(cols, src.stride(0))
     ldd = dst.stride(0) if cols > 1 else max(rows, dst.stride(0))
-    _check(_lib.tw_transpose(ctypes.c_void_p(src.data_ptr()), lds, rows, cols, ctypes.c_void_p(dst.data_ptr()), ldd,
+    _check(_lib.tw_transpose(src.data_ptr(), lds, rows, cols, dst.data_ptr(), ldd,
                              _stream_ptr(stream)), "tw_transpose")
     return dst
 
@@ -369,24 +386,20 @@ def _act_code(act) -> int:
 
 def tw_gemm_bias_act(w: TwWeight, A, bias=None, act="none", C=None, stream=None):
     """C = act(A . (B * mask) + bias).  bias: torch tensor [N] of A's dtype on the GPU, or None."""
-    torch = _torch()
-    assert A.is_cuda and A.dtype == _tdtype(w.dtype) and A.dim() == 2 and A.stride(1) == 1
-    M, K = A.shape
-    assert K == w.info["K"]
-    N = w.info["N"]
+    M, N = _row_operands(w, A, C)
     if C is None:
-        C = torch.empty((M, N), dtype=A.dtype, device=A.device)
-    assert C.is_cuda and C.dtype == A.dtype and C.shape == (M, N) and C.stride(1) == 1
-    bptr = ctypes.c_void_p(0)
+        C = _torch().empty((M, N), dtype=A.dtype, device=A.device)
+    bptr = None
     if bias is not None:
         assert bias.is_cuda and bias.dtype == A.dtype and bias.shape == (N,) and bias.stride(0) == 1
-        bptr = ctypes.c_void_p(bias.data_ptr())
-    lda = A.stride(0) if M > 1 else max(K, A.stride(0))
-    ldc = C.stride(0) if M > 1 else max(N, C.stride(0))
+        bptr = bias.data_ptr()
+    lda, ldc = A.stride(0), C.stride(0)
+    if M <= 1:
+        lda, ldc = max(w.info["K"], lda), max(N, ldc)
     ws, ws_bytes = w.workspace_for(M)
-    _check(_lib.tw_gemm_bias_act(_np_ptr(w.blob), ctypes.c_void_p(w.blob_dev.data_ptr()),
-                                 ctypes.c_void_p(A.data_ptr()), M, lda, bptr, _act_code(act),
-                                 ctypes.c_void_p(C.data_ptr()), ldc, ws, ws_bytes, _stream_ptr(stream)), "tw_gemm_bias_act")
+    _check(_lib.tw_gemm_bias_act(w._blob_ptr, w.blob_dev.data_ptr(),
+                                 A.data_ptr(), M, lda, bptr, _act_code(act),
+                                 C.data_ptr(), ldc, ws, ws_bytes, _stream_ptr(stream)), "tw_gemm_bias_act")
     return C
 
 
@@ -401,16 +414,16 @@ def tw_dense_gemm_bias_act(A, B, bias=None, act="none", C=None, stream=None):
     if C is None:
         C = torch.empty((M, N), dtype=A.dtype, device=A.device)
     assert C.shape == (M, N) and C.dtype == A.dtype and C.stride(1) == 1
-    bptr = ctypes.c_void_p(0)
+    bptr = None
     if bias is not None:
         assert bias.is_cuda and bias.dtype == A.dtype and bias.shape == (N,) and bias.stride(0) == 1
-        bptr = ctypes.c_void_p(bias.data_ptr())
+        bptr = bias.data_ptr()
     dt = TW_F16 if A.dtype == torch.float16 else TW_BF16
     lda = A.stride(0) if M > 1 else max(K, A.stride(0))
     ldb = B.stride(0) if K > 1 else max(N, B.stride(0))
     ldc = C.stride(0) if M > 1 else max(N, C.stride(0))
-    _check(_lib.tw_dense_gemm_bias_act(ctypes.c_void_p(A.data_ptr()), lda, ctypes.c_void_p(B.data_ptr()), ldb, bptr,
-                                       _act_code(act), ctypes.c_void_p(C.data_ptr()), ldc, M, N, K, dt,
+    _check(_lib.tw_dense_gemm_bias_act(A.data_ptr(), lda, B.data_ptr(), ldb, bptr,
+                                       _act_code(act), C.data_ptr(), ldc, M, N, K, dt,
                                        _stream_ptr(stream)), "tw_dense_gemm_bias_act")
     return C
 
@@ -430,8 +443,8 @@ def tw_dense_gemm(A, B, C=None, stream=None):
     lda = A.stride(0) if M > 1 else max(K, A.stride(0))
     ldb = B.stride(0) if K > 1 else max(N, B.stride(0))
     ldc = C.stride(0) if M > 1 else max(N, C.stride(0))
-    _check(_lib.tw_dense_gemm(ctypes.c_void_p(A.data_ptr()), lda, ctypes.c_void_p(B.data_ptr()), ldb,
-                              ctypes.c_void_p(C.data_ptr()), ldc, M, N, K, dt, _stream_ptr(stream)), "tw_dense_gemm")
+    _check(_lib.tw_dense_gemm(A.data_ptr(), lda, B.data_ptr(), ldb,
+                              C.data_ptr(), ldc, M, N, K, dt, _stream_ptr(stream)), "tw_dense_gemm")
     return C
 
 
