@@ -261,6 +261,19 @@ class TwWeight:
         # numpy takes longer to name an array's address than the library takes to check a call's arguments
         self._blob, self._blob_ptr = value, value.ctypes.data
 
+    # copy, deepcopy and pickle carry the array; its address belongs to the object that holds it and is read anew
+    def __getstate__(self):
+        state = dict(self.__dict__)
+        del state["_blob_ptr"]
+        state["blob"] = state.pop("_blob")
+        return state
+
+    def __setstate__(self, state):
+        state = dict(state)
+        self.blob = state.pop("blob")
+        self.__dict__.update(state)
+        self.torch_dtype = _tdtype(self.dtype)
+
     def sibling(self):
         """Another TwWeight on the same host and device copy of the blob, with a workspace of its own."""
         torch = _torch()

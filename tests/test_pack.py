@@ -1,8 +1,10 @@
 """Host side of the C-ABI library (no GPU needed): the library loads and exports what include/tw.h
 declares, tw_pack's integer arrays equal the oracle's tile structure bit for bit, pack -> unpack
 gives back B*mask and the mask bit for bit, and bad input is refused with the documented codes."""
+import copy
 import ctypes
 import os
+import pickle
 import re
 
 import numpy as np
@@ -432,3 +434,45 @@ def test_plan_limits_and_errors():
     with pytest.raises(tw.TwError) as e:
         tw.tw_gemm_plan(bad, 5)
     assert e.value.status == -3                            # TW_ERR_BUF: not a blob
+
+
+# ------------------------------------------------------------------ weights that a program copies
+def _host_weight(K, N, seed):
+    """A TwWeight whose "device" copy is a host tensor: enough for everything that enqueues nothing."""
+    w = W.generate(W.small_spec("copies", M=8, K=K, N=N, G=32, dtype="f16", col_prune=0.05, keep=("const", 0.4), seed_offset=seed), with_A=False)
+    blob = tw.tw_pack(w.B, w.mask, 32, "f16")
+    room = np.zeros(blob.size + 256, np.uint8)
+    at = -room.ctypes.data % 256
+    room[at:at + blob.size] = blob
+    return tw.TwWeight(room[at:at + blob.size], device="cpu")
+
+
+@pytest.mark.parametrize("how", ["copy", "deepcopy", "pickle", "sibling", "state of a plain attribute"])
+def test_a_copied_weight_names_its_own_blob(how):
+    """The library is given the address of the blob that the object holds, whichever way the object came to be, and
+    also after the object it was copied from is gone."""
+    src = _host_weight(64, 96, 1)
+    want = src.blob.copy()
+    if how == "copy":
+        w = copy.copy(src)
+    elif how == "deepcopy":
+        w = copy.deepcopy({"layer": [src]})["layer"][0]
+    elif how == "pickle":
+        w = pickle.loads(pickle.dumps(src))
+    elif how == "sibling":
+        w = src.sibling()
+    else:                                        # an object saved when `blob` was an ordinary attribute
+        w = object.__new__(tw.TwWeight)
+        w.__setstate__({"blob": src.blob.copy(), **{k: getattr(src, k) for k in ("info", "dtype", "blob_dev", "workspace", "ws_limit", "_retired", "_ws_need")}})
+    shared = how in ("copy", "sibling")
+    assert (w.blob is src.blob) == shared
+    assert w._blob_ptr == w.blob.ctypes.data and (w._blob_ptr == src._blob_ptr) == shared
+    del src
+    assert np.array_equal(w.blob, want) and bytes((ctypes.c_ubyte * want.size).from_address(w._blob_ptr)) == want.tobytes()
+    assert w.dtype == "f16" and w.torch_dtype == tw._tdtype("f16")
+    assert w.workspace_for(4)[1] >= 256
+    again = pickle.loads(pickle.dumps(w))        # and a copy of the copy
+    assert again._blob_ptr == again.blob.ctypes.data != w._blob_ptr
+    other = _host_weight(32, 64, 2).blob         # a blob that is put in place of it
+    w.blob = other
+    assert w._blob_ptr == other.ctypes.data
