@@ -222,8 +222,11 @@ def _tdtype(dtype: str):
 def _stream_ptr(stream=None) -> int:
     # (the raw handle of the current device's current stream, without building a torch Stream object for it)
     if stream is None:
-        c = _torch()._C
-        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        torch = _torch()
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:      # (names of torch's own that a version may lack)
+            return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 

@@ -476,3 +476,27 @@ def test_a_copied_weight_names_its_own_blob(how):
     other = _host_weight(32, 64, 2).blob         # a blob that is put in place of it
     w.blob = other
     assert w._blob_ptr == other.ctypes.data
+
+
+def test_current_stream_without_torchs_private_names(monkeypatch):
+    """The raw handle of the current stream comes from a private function of torch where it exists, else from the
+    public one."""
+    class Lacking:
+        class _C:
+            pass
+
+        class cuda:
+            @staticmethod
+            def current_stream():
+                return type("Stream", (), {"cuda_stream": 4711})()
+
+    class Having(Lacking):
+        class _C:
+            _cuda_getDevice = staticmethod(lambda: 3)
+            _cuda_getCurrentRawStream = staticmethod(lambda device: 1000 + device)
+
+    monkeypatch.setattr(tw, "_torch", lambda: Lacking)
+    assert tw._stream_ptr() == 4711
+    monkeypatch.setattr(tw, "_torch", lambda: Having)
+    assert tw._stream_ptr() == 1003
+    assert tw._stream_ptr(type("Stream", (), {"cuda_stream": 5})()) == 5
