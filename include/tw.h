@@ -250,7 +250,8 @@ int tw_transpose(const void* src, int ld_src, int rows, int cols, void* dst, int
 
 /* Dense reference C = A . B on the same MFMA pipeline (the paper's dense baseline, Sec. VI
  * "Tiling" / Sec. VII-A).  A: device M x K (lda % 8 == 0), B: device K x N row-major
- * (ldb % 8 == 0), C: device M x N (ldc % 8 == 0); bases 16-byte aligned. */
+ * (ldb % 8 == 0), C: device M x N (ldc % 8 == 0); bases 16-byte aligned.  Nothing is read behind the last
+ * element of A and of B: buffers of (M-1)*lda + K and (K-1)*ldb + N elements will do. */
 int tw_dense_gemm(const void* A, int lda, const void* B, int ldb, void* C, int ldc,
                   int M, int N, int K, tw_dtype dt, void* hip_stream);
 

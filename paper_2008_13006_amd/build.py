@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtw.so")
 SOURCES = ["tw_pack.cpp", "tw_gemm.hip", "tw_dense.hip"]
-HEADERS = ["tw_format.h", "tw_device.hpp", os.path.join("..", "..", "include", "tw.h")]
+HEADERS = ["tw_format.h", "tw_device.hpp", "tw_pieces.h", os.path.join("..", "..", "include", "tw.h")]
 
 
 def hipcc() -> str:

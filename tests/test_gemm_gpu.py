@@ -301,6 +301,36 @@ def test_dense_gemm_ring(tw, case):
     assert bool(torch.isnan(Cbuf[:, N:].float()).all().item()), "wrote outside C"
 
 
+# M, K, N, type, extra pitch of A and B: K, N and both no multiple of 8, one element, the ragged K rows and columns in the first and
+# in a later step and block, several blocks per workgroup, 64-bit addresses
+DENSE_ENDS = [(1, 1, 1, "f16", 0, 0), (65, 67, 511, "bf16", 0, 8), (1, 130, 264, "f16", 8, 0), (3, 64, 257, "bf16", 0, 0), (300, 129, 255, "f16", 0, 0),
+              (33000, 71, 523, "f16", 0, 0), (5, 131, 261, "bf16", 1 << 23, 0), (70, 131, 261, "f16", 0, 1 << 24)]
+
+
+@pytest.mark.parametrize("case", DENSE_ENDS, ids=["x".join(map(str, c[:3])) for c in DENSE_ENDS])
+def test_dense_gemm_of_buffers_without_a_last_pitch(tw, case):
+    """A and B in buffers that end right behind their last element: every element of C, bias and ReLU fused."""
+    M, K, N, dtype, pad_a, pad_b = case
+    _say(f"tw_dense_gemm, tight buffers {case}")
+    rng = np.random.default_rng(M + K + N)
+    A_bits = W.f32_to_bits(rng.standard_normal((M, K), dtype=np.float32), dtype)
+    B_bits = W.f32_to_bits(rng.standard_normal((K, N), dtype=np.float32) * np.float32(0.05), dtype)
+    bbits = _bias_bits(N, dtype, 6)
+    td = torch.float16 if dtype == "f16" else torch.bfloat16
+
+    def tight(bits, pad):
+        rows, cols = bits.shape
+        ld = (cols + 7) // 8 * 8 + pad
+        t = torch.full(((rows - 1) * ld + cols,), float("nan"), dtype=td, device="cuda:0").as_strided((rows, cols), (ld, 1))
+        return t.copy_(tw.bits_to_tensor(bits, dtype))
+
+    C = torch.full((M, (N + 7) // 8 * 8), float("nan"), dtype=td, device="cuda:0")[:, :N]
+    tw.tw_dense_gemm_bias_act(tight(A_bits, pad_a), tight(B_bits, pad_b), tw.bits_to_tensor(bbits, dtype), "relu", C)
+    torch.cuda.synchronize()
+    _compare_whole(C, A_bits, B_bits, np.ones((K, N), np.uint8), dtype, what=f"tight {case}",
+                   post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "relu"))
+
+
 # name, M, K, N, G, type, keep, tiles of a workgroup at most: 8, 4 and 2 waves to a tile; fewer steps than waves; the
 # longest resident K in several batches of A; one row; a last row block of one row; K that is no multiple of 8
 TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1), ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1),

@@ -500,3 +500,34 @@ def test_current_stream_without_torchs_private_names(monkeypatch):
     monkeypatch.setattr(tw, "_torch", lambda: Having)
     assert tw._stream_ptr() == 1003
     assert tw._stream_ptr(type("Stream", (), {"cuda_stream": 5})()) == 5
+
+
+# ------------------------------------------------------------------ what the dense kernel may read
+def test_dense_pieces_lie_inside_the_matrix(tmp_path):
+    """The rule by which the dense kernel fetches 16-byte pieces, over all small matrices: a fetched piece ends at or before
+    the last element, and what is not fetched is nothing but the ragged end of the last row."""
+    import subprocess
+    src = tmp_path / "pieces.c"
+    src.write_text("""
+#include <stdio.h>
+#include "tw_pieces.h"
+int main(void) {
+    for (int rows = 1; rows <= 5; ++rows)
+        for (int cols = 1; cols <= 40; ++cols) {
+            const int pitch8 = (cols + 7) / 8 * 8;
+            for (int ld = pitch8; ld <= pitch8 + 8; ld += 8)
+                for (int col = 0; col < ld + 64; col += 8) {
+                    const int n = tw_piece_rows(col, rows, cols);
+                    for (int r = 0; r < rows; ++r) {
+                        const long last = (long)(rows - 1) * ld + cols, from = (long)r * ld + col;
+                        if (r < n && from + 8 > last) return printf("read past the end: %d x %d, ld %d, row %d, column %d\\n", rows, cols, ld, r, col), 1;
+                        if (r >= n && col < cols && !(r == rows - 1 && cols - col < 8)) return printf("not read: %d x %d, row %d, column %d\\n", rows, cols, r, col), 1;
+                    }
+                }
+        }
+    return tw_piece_rows(2147483640, 1, 2147483647) != 0 || tw_piece_rows(2147483632, 3, 2147483647) != 3;
+}
+""")
+    exe = str(tmp_path / "pieces")
+    subprocess.run(["gcc", "-std=c99", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2008_13006_amd", "csrc"), str(src), "-o", exe], check=True)
+    assert subprocess.run([exe], capture_output=True, text=True).returncode == 0
