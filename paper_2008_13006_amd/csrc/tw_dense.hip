@@ -11,10 +11,11 @@
 // multiplied, and the ring runs on into the workgroup's next block of C: its first step lands during this one's
 // last steps and its epilogue.  Direct loads write 1 KB of consecutive LDS per wave instruction, so rows cannot be padded;
 // bank conflicts are avoided by WHICH 16-byte piece of a row a lane fetches instead (kept at slot piece ^ f(row)).
-// What bounds it: the matrix units under the card's power limit.  16384 x 768 x 3072 in fp16: 83 us (930 TFLOP/s; 95 us with
-// the operands staged through registers); without loads and stores 55, with the MFMAs alone 50 (1560 TFLOP/s), and
-// 72 us as it is on operands of zeros, where the clock stays up.  The loads cost 14 us of the 83 and the stores 15.
-// On 16384 x 3072 x 768 83 us (95), 8192 x 4096 x 1024 74 (88), 2048 x 3072 x 768 35 (57), 1500 x 1000 x 2000 16 (31).
+// What bounds it: the matrix units under the card's power limit.  16384 x 768 x 3072 in fp16: 81 us (950 TFLOP/s; 95 us with
+// the operands staged through registers).  Parts left out, measured at 83 us for the whole: without loads and stores 55, with
+// the MFMAs alone 50 (1560 TFLOP/s), and 72 us as it is on operands of zeros, where the clock stays up; the loads cost 14
+// us and the stores 15.  On 16384 x 3072 x 768 80 us (95 through registers), 8192 x 4096 x 1024 74 (88), 2048 x 3072 x 768 31
+// (57), 1500 x 1000 x 2000 14.5 (31).
 // Spreading a step's requests over its MFMAs instead of one burst behind the barrier: no gain on real operands.
 //
 // The operands of contraction slots 16*ks+16 .. are read from LDS before the MFMAs of slots 16*ks .. are issued,
@@ -59,6 +60,12 @@ struct DenseParams {
 };
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// The same value, as one the compiler cannot compute with ahead of time: addresses of the epilogue are then formed there
+// and not kept in registers (or in scratch memory) through the whole loop.
+__device__ __forceinline__ int fresh(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
 
 // Offsets at and above this are out of a buffer descriptor's range: such a lane fetches zeros.
 constexpr unsigned kRange = 0x80000000u;
@@ -99,20 +106,48 @@ __device__ __forceinline__ void block_of(const DenseParams& p, int t, int bm, in
     n0 = nb * BN;
 }
 
+// Hands the bias of the wave's 64 columns (`own`: this lane's column) round through its staging area: lane half h receives
+// the columns 32*cb + 8*q + 4*h + 0..3 as bias[cb][q].  Once per block of C, before the area takes results.
+__device__ __forceinline__ void spread_bias(unsigned short own, unsigned char* stage, int lane, tw_u32x2 (&bias)[2][4]) {
+    asm volatile("" ::: "memory");
+    *(unsigned short*)(stage + 2 * lane) = own;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bias[cb][q] = *(const tw_u32x2*)(stage + 64 * cb + 16 * q + 8 * (lane >> 5));
+    asm volatile("" ::: "memory");
+}
+
 // Adds the bias and applies the activation, in place, to a 32 x 64 block: lane l holds row l%32 and of acc[cb] the
-// columns 32*cb + 8*(r/4) + 4*(l/32) + r%4.  (One branch for the block, so that the plain epilogue is straight-line code.)
+// columns 32*cb + 8*(r/4) + 4*(l/32) + r%4.  The activation is chosen once per block, so that each choice is straight-line
+// code.  (A branch and a load of the bias for every element: 32 round trips to memory per block, each behind the
+// stores and the next block's requests: 16384 x 768 x 3072 took 121 us with a bias and 126 with GELU, this way 84 and
+// 100, 512 x 768 x 3072 14.7 and 15.3, this way 10.7 and 12.4; without a fused epilogue they take 84 and 10.3.)
 template <int DT>
-__device__ __forceinline__ void add_bias_act(tw_f32x16 (&acc)[2], const unsigned short* bias, int act, int width, int h) {
+__device__ __forceinline__ void add_bias_act(tw_f32x16 (&acc)[2], const tw_u32x2 (&bias)[2][4], int act) {
+    auto value = [&](int cb, int r) {
+        const unsigned two = bias[cb][r >> 2][(r >> 1) & 1];
+        return acc[cb][r] + tw_to_f32<DT>((unsigned short)(r & 1 ? two >> 16 : two));
+    };
+    if (act == TW_ACT_GELU) {                                // uniform
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        float b[16];
+        for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = 32 * cb + 8 * (r / 4) + 4 * h + r % 4;
-            b[r] = bias != nullptr ? tw_to_f32<DT>(bias[c < width ? c : 0]) : 0.f;
-        }
+            for (int r = 0; r < 16; ++r) acc[cb][r] = tw_gelu(value(cb, r));
+    } else if (act == TW_ACT_RELU) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[cb][r] = tw_activate(acc[cb][r] + b[r], act);
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float x = value(cb, r);
+                acc[cb][r] = x > 0.f ? x : 0.f;
+            }
+    } else {
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[cb][r] = value(cb, r);
     }
 }
 
@@ -345,19 +380,25 @@ __global__ __launch_bounds__(kThreads) void tw_dense_kernel(const DenseParams p)
             __builtin_amdgcn_sched_barrier(0);
             pos = npos;
         }
+        const int col0 = n0 + wn * 64;
+        const int width = (p.N - col0) < 64 ? (p.N - col0) : 64;
+        const bool fused = p.bias != nullptr || p.act != TW_ACT_NONE;
+        unsigned short own_bias = 0;                         // of the column col0 + lane, asked for ahead of the last MFMAs
+        const int elane = fresh(lane);
+        if (p.bias != nullptr && elane < width) own_bias = p.bias[col0 + elane];
+        __builtin_amdgcn_sched_barrier(0);
         multiply(1);
         lds_wait<(NST - 2) * kLoads>();
         // epilogue through per-wave staging areas in the buffer of the last step; the next block's first steps are landing in the others
         {
             unsigned char* stage = smem + pos * BUF_BYTES + wave * kDenseStage;
-            const int col0 = n0 + wn * 64;
-            const int width = (p.N - col0) < 64 ? (p.N - col0) : 64;
             if (width > 0) {
+                tw_u32x2 bias[2][4];
+                if (fused) spread_bias(own_bias, stage, elane, bias);
 #pragma unroll
                 for (int ms = 0; ms < MSW; ++ms) {
-                    if (p.bias != nullptr || p.act != TW_ACT_NONE)
-                        add_bias_act<DT>(acc[ms], p.bias != nullptr ? p.bias + col0 : nullptr, p.act, width, h);
-                    store_block<DT>(acc[ms], stage, p.C, p.ldc, m0 + wm * 32 * MSW + ms * 32, p.M, col0, width, lane, p.stream != 0);
+                    if (fused) add_bias_act<DT>(acc[ms], bias, p.act);
+                    store_block<DT>(acc[ms], stage, p.C, p.ldc, m0 + wm * 32 * MSW + ms * 32, p.M, col0, width, elane, p.stream != 0);
                 }
             }
         }
