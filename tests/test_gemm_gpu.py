@@ -268,20 +268,34 @@ def test_dense_gemm_small_cases(tw, case):
     assert bool(torch.isnan(Cbuf[:, N:].float()).all().item()), "wrote outside C"
 
 
-# name, M, K, N, type, extra pitch of A and B, bias + GELU: one K step and one position, K steps fewer than the ring has
-# buffers, a K tail whose last 16 bytes hold what the pitch holds, several blocks of C per workgroup (blocks of 256, 128
-# and 64 rows), row pitches beyond a buffer descriptor's range
-DENSE_RING = [("one", 1, 1, 1, "f16", 0, 0, False), ("k_step_1", 300, 64, 257, "bf16", 8, 8, True),
-              ("k_step_2_tail", 65, 67, 511, "f16", 0, 16, False), ("k_step_3_tail", 129, 190, 40, "bf16", 24, 0, True),
-              ("walk_256", 33000, 33, 520, "f16", 0, 0, False), ("walk_256_wide_n", 300, 130, 66000, "f16", 0, 0, True),
-              ("walk_k_step_3", 33001, 135, 257, "bf16", 8, 0, False),
-              ("pitch_of_a", 5, 300, 264, "f16", 1 << 23, 0, True), ("pitch_of_b", 70, 130, 264, "bf16", 0, 1 << 24, False)]
+# name, M, K, N, type, extra pitch of A and B, bias + GELU, then what the dispatch makes of it on 256 compute units: rows of a
+# block of C and the most blocks that a workgroup walks.  One K step and one position, K steps fewer than the ring has buffers,
+# a K tail whose last 16 bytes hold what the pitch holds, walks of each block height with one and with several K steps, plain
+# and fused, and row pitches beyond a buffer descriptor's range (64-bit addresses), with and without a walk
+DENSE_RING = [("one", 1, 1, 1, "f16", 0, 0, False, 64, 1), ("k_step_1", 300, 64, 257, "bf16", 8, 8, True, 64, 1),
+              ("k_step_2_tail", 65, 67, 511, "f16", 0, 16, False, 64, 1), ("k_step_3_tail", 129, 190, 40, "bf16", 24, 0, True, 64, 1),
+              ("walk_64", 1300, 130, 6144, "f16", 0, 0, False, 64, 2), ("walk_64_fused", 300, 200, 26000, "bf16", 0, 8, True, 64, 2),
+              ("walk_128_fused", 300, 130, 66000, "f16", 0, 0, True, 128, 4), ("walk_128", 33001, 135, 257, "bf16", 8, 0, False, 128, 3),
+              ("walk_256_k_step_1", 33000, 33, 520, "f16", 0, 0, False, 256, 2), ("walk_256_fused", 33000, 135, 520, "f16", 0, 0, True, 256, 2),
+              ("walk_256_fused_bf16", 33000, 135, 520, "bf16", 0, 0, True, 256, 2),
+              ("pitch_of_a", 5, 300, 264, "f16", 1 << 23, 0, True, 64, 1), ("pitch_of_b", 70, 130, 264, "bf16", 0, 1 << 24, False, 64, 1),
+              ("pitch_of_b_walk_64", 300, 130, 26000, "f16", 0, 1 << 24, True, 64, 2), ("pitch_of_b_walk_256", 33000, 72, 520, "bf16", 0, 1 << 24, False, 256, 2)]
+
+
+def _dense_blocks(M, N, n_cu):
+    """(rows of a block of C, blocks that a workgroup walks at most): the dispatch's choice between 256, 128 and 64 rows."""
+    def blocks(rows):
+        return -(-M // rows) * -(-N // 256)
+    costs = [(-(-blocks(rows) // n_cu) * rows * f, -rows) for rows, f in ((256, 1.0), (128, 1.25), (64, 1.8))]
+    rows = -min(costs)[1]
+    return rows, -(-blocks(rows) // n_cu)
 
 
 @pytest.mark.parametrize("case", DENSE_RING, ids=[c[0] for c in DENSE_RING])
 def test_dense_gemm_ring(tw, case):
     """Every element, and nothing outside C; the pitch of A, B and C holds NaN, which no result may see."""
-    name, M, K, N, dtype, pad_a, pad_b, fused = case
+    name, M, K, N, dtype, pad_a, pad_b, fused, rows, walk = case
+    assert _dense_blocks(M, N, torch.cuda.get_device_properties(0).multi_processor_count) == (rows, walk)
     _say(f"tw_dense_gemm ring {name} M={M} K={K} N={N} {dtype}")
     rng = np.random.default_rng(sum(map(ord, name)))
     A_bits = W.f32_to_bits(rng.standard_normal((M, K), dtype=np.float32), dtype)
