@@ -2274,14 +2274,8 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
         // now: 768 -> 3072 at 1000 / 3000 / 12000 rows 13.1 -> 10.1, 34.5 -> 18.4, 54 -> 39.5 us; 768 -> 768 at 8192 15.8 -> 12.9;
         // 1400 -> 2000 at 3000 37 -> 20; 1000 -> 1234 (G = 32) at 4321 36.5 -> 25.3; transposed 768 -> 2304 at 6000 tokens
         // 35 -> 19.6, 500 -> 4000 (G = 32) at 5000 39 -> 23.0; 768 -> 3072 at 16384 and 17000 as before.
-        // (Kept as it was: 64-row blocks that make exactly one full round with a short K, the plan that the bit-exact tests
-        // pin; the estimate's choice takes 9.1 us there instead of 11.7, 256 -> 390 at 8192 rows.)
         const long nmb_full = (M + 32L * msb - 1) / (32 * msb);
-        long segs_full = nmb_full < n_cu ? (n_cu + nmb_full - 1) / nmb_full : 1;
-        if (segs_full > T) segs_full = T;
-        if (msb == 2 && h->K <= 256 && nmb_full * segs_full == n_cu) {
-            segs = (int)segs_full;
-        } else if (nmb_full < n_cu || msb == 1) {
+        if (nmb_full < n_cu || msb == 1) {
             double best = 0.0;
             const int top = msb;
             for (int m = top; m >= 1; --m) {

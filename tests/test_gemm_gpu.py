@@ -1035,8 +1035,8 @@ def test_a_million_rows_byte_offsets_beyond_2_31(tw):
 EXACT = [
     # name, M, K, N, G, dtype, col_prune, keep, expected (mode, rows_per_block, tiles_per_set, k_parts) row-major / transposed
     ("resident_32rows", 150, 256, 384, 128, "f16", 0.05, ("upow", 0.1, 0.6), (0, 32, 0, 1), (0, 32, 0, 1)),
-    ("resident_64rows", 8192, 256, 390, 128, "f16", 0.05, ("upow", 0.1, 0.6), (0, 64, 0, 1), (0, 64, 0, 1)),
-    ("resident_64rows_bf16", 8192, 96, 200, 64, "bf16", 0.1, ("upow", 0.1, 0.5), (0, 64, 0, 1), (0, 64, 0, 1)),
+    ("resident_64rows", 16384, 256, 390, 128, "f16", 0.05, ("upow", 0.1, 0.6), (0, 64, 0, 1), (0, 64, 0, 1)),
+    ("resident_64rows_bf16", 16384, 96, 200, 64, "bf16", 0.1, ("upow", 0.1, 0.5), (0, 64, 0, 1), (0, 64, 0, 1)),
     ("resident_lowered_blocks", 17000, 256, 250, 128, "f16", 0.0, ("upow", 0.1, 0.6), (0, 40, 0, 1), (0, 64, 0, 1)),
     ("streamed_wave_per_tile", 16384, 1600, 380, 64, "f16", 0.05, ("upow", 0.02, 0.15), (1, 64, 8, 1), (1, 64, 8, 1)),
     ("streamed_sets_of_4", 16400, 1600, 250, 64, "f16", 0.0, ("upow", 0.02, 0.15), (2, 40, 4, 1), (2, 64, 4, 1)),

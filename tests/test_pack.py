@@ -396,6 +396,16 @@ def test_plan_of_few_row_blocks_makes_one_round():
                         assert pl["n_items"] <= n_cu, (K, M, n_cu, tr, pl)
 
 
+def test_plan_of_a_short_k_has_no_island():
+    """Where 64-row blocks would make exactly one round, a K of 256 or less gets the plan that its neighbours in M and K get."""
+    for K, N, G in ((256, 390, 128), (248, 390, 128), (264, 390, 128), (96, 200, 64)):
+        w = W.generate(W.small_spec("plan_short_k", M=8, K=K, N=N, G=G, dtype="f16", col_prune=0.05, keep=("upow", 0.1, 0.6), seed_offset=5), with_A=False)
+        blob = tw.tw_pack(w.B, w.mask, G, "f16")
+        for tr in (False, True):
+            plans = [tw.tw_gemm_plan(blob, M, n_cu=256, transposed=tr) for M in (8120, 8160, 8192)]
+            assert len({(p["mode"], p["rows_per_block"], p["n_sets"]) for p in plans}) == 1, plans
+
+
 def test_plan_limits_and_errors():
     rng = np.random.default_rng(3)
     for K, N, G in [(64, 256, 128), (1536, 128, 32), (1544, 128, 64), (3000, 300, 128)]:
