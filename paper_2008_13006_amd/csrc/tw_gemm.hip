@@ -2239,14 +2239,20 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
 // whole chip does, the packed weights of its tiles through the compute unit's vector L1 or the steps of a heavy tile
 // (half again as many as the mean) one after the other, whichever takes longer, and the stores.  Fitted to
 // K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item, both boundaries (within 20 % of most of 150 plans timed).
-double resident_item_us(const TwHeader* h, int msb, int tiles) {
+double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
     constexpr double kStartUs = 5.0, kStageBytesPerUs = 20e3, kWeightBytesPerUs = 70e3, kStepUs = 0.1, kStoreBytesPerUs = 32e3;
     const double steps = (double)h->total_steps / h->T;
     const double weights = tiles * steps * h->ncb * 1024.0 / kWeightBytesPerUs;
-    const int team = msb > 1 || tiles > kWaves / 2 || h->ew_nnz > 0 ? 1 : tiles <= 1 ? 8 : tiles <= 2 ? 4 : 2;   // (tw_team_kernel)
-    const double chain = 1.5 * steps * kStepUs * ((tiles + kWaves - 1) / kWaves) / team;
+    const double chain = 1.5 * steps * kStepUs * ((tiles + kWaves - 1) / kWaves) / (1 << team_shift);
     return kStartUs + 64.0 * msb * h->K / kStageBytesPerUs + (weights > chain ? weights : chain) +
            tiles * 64.0 * msb * h->G / kStoreBytesPerUs;
+}
+
+// K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves share the tiles
+// (tw_team_kernel).  log2 of the waves to a tile, 0: a wave per tile.
+int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu) {
+    if (msb != 1 || items > n_cu || most_tiles > kWaves / 2 || h->ew_nnz > 0) return 0;
+    return most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
 }
 
 int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0) {
@@ -2286,7 +2292,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                     const int tiles = (T + sg - 1) / sg;
                     if (sg > 1 && (T + sg - 2) / (sg - 1) == tiles) continue;     // (as many tiles with fewer workgroups)
                     const double rounds = (double)((blocks * sg + n_cu - 1) / n_cu);
-                    const double cost = rounds * resident_item_us(h, m, tiles);
+                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu));
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
                 }
             }
@@ -2363,15 +2369,12 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     // (Not where the tiles add the residual-only columns of a TEW blob themselves: a split leaves those to the pass
     // of their own, which reads all of A once more - 92 against 46 us on the FFN-down of BERT-base at 512 rows.)
     pl.n_parts = 1; pl.chunks_per_part = h->n_chunks; pl.partial_bytes = 0;
-    // K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves share the tiles
-    // (tw_team_kernel).  Calls back to back in a graph, a wave per tile -> teams: 768 -> 3072 at 1 / 64 / 512 rows
+    // Teams of waves.  Calls back to back in a graph, a wave per tile -> teams: 768 -> 3072 at 1 / 64 / 512 rows
     // 8.2 / 9.9 / 10.3 -> 7.5 / 8.5 / 8.9 us, 768 -> 768 at 256 / 2048 rows 9.9 / 10.7 -> 8.5 / 8.9 us, transposed
     // 768 -> 2304 at 512 tokens 8.2 -> 7.0 us, 1500 -> 800 at 100 tokens 11.5 -> 8.0 us.  With five tiles or more nearly every
     // wave has a tile of its own.  (TEW blobs stay with a wave per tile: a tile's residual has steps of another kind.)
-    pl.team_shift = 0;
-    const int most = (T + nseg - 1) / nseg;                           // tiles of a workgroup at most
-    if (resident && msb == 1 && items <= n_cu && most <= kWaves / 2 && h->ew_nnz == 0) {
-        pl.team_shift = most <= 1 ? 3 : most <= 2 ? 2 : 1;
+    pl.team_shift = resident ? team_of(h, msb, (T + nseg - 1) / nseg, items, n_cu) : 0;
+    if (pl.team_shift > 0) {
         const unsigned sums = (unsigned)kWaves * h->ncb * 4096u;      // the waves' fp32 sums, over A and the staging areas
         if (sums > pl.lds_bytes) pl.lds_bytes = sums;
     }

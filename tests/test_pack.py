@@ -406,6 +406,17 @@ def test_plan_of_a_short_k_has_no_island():
             assert len({(p["mode"], p["rows_per_block"], p["n_sets"]) for p in plans}) == 1, plans
 
 
+def test_plan_prices_teams_only_where_they_run():
+    """One narrow tile with many steps and more 32-row blocks than compute units: in several rounds nothing shares a tile, so
+    one round of 64-row blocks is the faster plan (two rounds with a wave per tile take 1.7 times as long)."""
+    w = W.generate(W.small_spec("plan_teams", M=8, K=900, N=32, G=32, dtype="f16", col_prune=0.0, keep=("const", 0.9), seed_offset=3), with_A=False)
+    blob = tw.tw_pack(w.B, w.mask, 32, "f16")
+    for M in (8202, 9000, 12000, 16253):
+        for tr in (False, True):
+            pl = tw.tw_gemm_plan(blob, M, n_cu=256, transposed=tr)
+            assert pl["rows_per_block"] == 64 and pl["n_items"] <= 256, (M, tr, pl)
+
+
 def test_plan_limits_and_errors():
     rng = np.random.default_rng(3)
     for K, N, G in [(64, 256, 128), (1536, 128, 32), (1544, 128, 64), (3000, 300, 128)]:
