@@ -148,7 +148,8 @@ int tw_gemm_workspace(const void* blob_host, int M, size_t* ws_bytes);
  * with n_cu compute units: the host-side decision only, no GPU call.  Sec. VI ("Load Imbalance Mitigation",
  * "Tiling") leaves the thread-block shape and the distribution of tiles to the implementation; this is this one's. */
 typedef struct tw_plan_t {
-    int32_t mode;            /* 0: the K extent of a row block stays in on-chip memory, waves pull whole tiles;
+    int32_t mode;            /* 0: the K extent of a row block stays in on-chip memory, waves pull whole tiles or, with
+                                   team_waves > 1, share them;
                                 1: K streamed in chunks, a wave per tile;
                                 2: K streamed, four waves multiply (a tile each), four only load A */
     int32_t rows_per_block;  /* rows of A (tokens) of a work item: 64 or 32; tw_gemm may take a multiple of 8
@@ -166,7 +167,9 @@ typedef struct tw_plan_t {
                                 workspace; a second kernel adds them in the order of the parts.  1: no split.  (What
                                 tw_gemm does with a workspace of tw_gemm_workspace bytes; with a smaller one it
                                 does not split.) */
-    int32_t reserved[6];
+    int32_t team_waves;      /* mode 0: waves of a workgroup that share a tile, each with a part of its K steps (8, 4 or 2);
+                                1: a wave has a tile to itself */
+    int32_t reserved[5];
 } tw_plan_t;
 /* Errors: TW_ERR_ARG (null pointer, negative M, n_cu <= 0), TW_ERR_BUF (not a blob of this format version),
  * TW_ERR_UNSUPPORTED (what tw_gemm / tw_gemm_t would refuse for this blob and M).  M = 0 or a blob without

@@ -2519,6 +2519,7 @@ extern "C" int tw_gemm_plan(const void* blob_host, int M, int n_cu, int transpos
     plan->lds_bytes = pl.lds_bytes;
     plan->row_lists = pl.urow_off != 0;
     plan->k_parts = pl.n_parts;
+    plan->team_waves = 1 << pl.team_shift;
     return TW_OK;
 }
 

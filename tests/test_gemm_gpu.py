@@ -367,6 +367,7 @@ def test_teams_of_waves(tw, case):
     assert pl["mode"] == 0 and pl["rows_per_block"] == 32 and pl["n_items"] == pl["grid"]
     tiles = (T + pl["n_sets"] - 1) // pl["n_sets"]
     assert tiles <= most and (most < 4 or tiles > 2) and (most != 2 or tiles == 2), (pl, T)
+    assert pl["team_waves"] == {1: 8, 2: 4, 4: 2}[most], pl
     A = _device_A(tw, w.A, dtype)
     At = torch.zeros((K, (M + 7) // 8 * 8), dtype=A.dtype, device="cuda:0")[:, :M]
     At.copy_(A.t())

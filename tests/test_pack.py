@@ -406,6 +406,24 @@ def test_plan_of_a_short_k_has_no_island():
             assert len({(p["mode"], p["rows_per_block"], p["n_sets"]) for p in plans}) == 1, plans
 
 
+def test_plan_says_where_waves_share_tiles():
+    """team_waves of the plan: 8, 4 or 2 with at most one, two, four tiles per workgroup, one round and 32-row blocks, else 1."""
+    w = W.generate(W.small_spec("plan_says", M=8, K=768, N=3072, G=128, dtype="f16", col_prune=0.05, keep=("upow", 0.1, 0.5), seed_offset=4), with_A=False)
+    blob = tw.tw_pack(w.B, w.mask, 128, "f16")
+    tew = tw.tw_pack_tew(w.B, w.mask, tw.tw_restore_ew(w.B, w.mask, 0.01, "f16"), 128, "f16")
+    T = tw.tw_info(blob)["T"]
+    for tr in (False, True):
+        for M, waves in ((1, 8), (300, 8), (500, 4), (1200, 2), (3000, 1), (16384, 1)):
+            pl = tw.tw_gemm_plan(blob, M, n_cu=256, transposed=tr)
+            assert pl["team_waves"] == waves, (M, tr, pl)
+            if waves > 1:
+                assert pl["mode"] == 0 and pl["rows_per_block"] == 32 and pl["n_items"] <= 256
+                assert -(-T // pl["n_sets"]) <= 8 // waves and pl["lds_bytes"] >= 8 * 4 * 4096
+            assert tw.tw_gemm_plan(tew, M, n_cu=256, transposed=tr)["team_waves"] == 1
+    long_k = W.generate(W.small_spec("plan_says_k", M=8, K=3072, N=256, G=128, dtype="f16", col_prune=0.0, keep=("const", 0.1), seed_offset=6), with_A=False)
+    assert tw.tw_gemm_plan(tw.tw_pack(long_k.B, long_k.mask, 128, "f16"), 64, n_cu=256)["team_waves"] == 1
+
+
 def test_plan_prices_teams_only_where_they_run():
     """One narrow tile with many steps and more 32-row blocks than compute units: in several rounds nothing shares a tile, so
     one round of 64-row blocks is the faster plan (two rounds with a wave per tile take 1.7 times as long)."""
