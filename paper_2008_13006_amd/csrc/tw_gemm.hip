@@ -2248,14 +2248,37 @@ double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
            tiles * 64.0 * msb * h->G / kStoreBytesPerUs;
 }
 
-// K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves share the tiles
+// K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves may share the tiles
 // (tw_team_kernel).  log2 of the waves to a tile, 0: a wave per tile.
-int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu) {
+// A team takes the heaviest tile's steps side by side and shares the epilogue out, and pays for it with the waves' sums
+// through LDS.  What it saves and costs, in microseconds, was measured against a wave per tile on the same plans (1300 calls,
+// K = 48 .. 1536, 1 to 8000 rows, both boundaries, plain / bias / GELU; the line is within 0.4 us of nearly all):
+// kTeamStepUs for every step of the heaviest tile, against kTeamUs, more with K > 768 (A then comes in in larger batches, which
+// a wave per tile does for every K).  A negative entry: the shared epilogue alone pays (GELU; the row-major one-block tile).
+// 140 -> 325 (G = 64) at 1072 rows, GELU, transposed: 6.5 us with a wave per tile, 7.0 with teams; 75 -> 545 (G = 128) at 1573
+// rows 8.6 and 10.2; 768 -> 768 (G = 128) at 256 rows 9.9 and 8.5.
+enum Epilogue { kEpiPlain = 0, kEpiCheap = 1, kEpiGelu = 2 };   // none; a bias and / or ReLU; GELU
+Epilogue epilogue_of(const void* bias, int act) {
+    return act == TW_ACT_GELU ? kEpiGelu : bias != nullptr || act != TW_ACT_NONE ? kEpiCheap : kEpiPlain;
+}
+int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bool transposed, Epilogue epi) {
     if (msb != 1 || items > n_cu || most_tiles > kWaves / 2 || h->ew_nnz > 0) return 0;
-    return most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
+    constexpr double kTeamStepUs[3] = {0.046, 0.055, 0.085};          // tiles of 1, 2, 4 column blocks
+    constexpr double kTeamUs[2][3][3] = {{{-0.9, -1.1, -1.5}, {0.5, 0.2, -0.9}, {1.05, 1.05, -0.4}},
+                                         {{0.8, 1.0, 0.8}, {1.1, 1.3, 0.75}, {1.0, 1.0, -0.65}}};
+    const int shift = most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
+    const int width = h->ncb >= 4 ? 2 : h->ncb - 1;
+    double cost = kTeamUs[transposed][width][epi];
+    if (transposed && shift < 3) cost -= 0.6;                         // (a tile's epilogue has fewer sums to add)
+    if (h->K > 768) cost += (transposed ? 0.55 : 1.5) + (shift == 1 ? 0.8 : 0.0);
+    const unsigned char* blob = (const unsigned char*)h;
+    const int32_t first = *(const int32_t*)(blob + h->off_sched_order);
+    const int heaviest = ((const TwTileDesc*)(blob + h->off_tile_desc))[first].nsteps;
+    return kTeamStepUs[width] * heaviest > cost ? shift : 0;
 }
 
-int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0) {
+int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0,
+              Epilogue epi = kEpiPlain) {
     const bool resident = h->n_chunks == 1;
     const int buffers = resident ? 1 : 2;
     if (lds_need(1, h->k_chunk, buffers) > kLdsLimit) return TW_ERR_UNSUPPORTED;
@@ -2292,7 +2315,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                     const int tiles = (T + sg - 1) / sg;
                     if (sg > 1 && (T + sg - 2) / (sg - 1) == tiles) continue;     // (as many tiles with fewer workgroups)
                     const double rounds = (double)((blocks * sg + n_cu - 1) / n_cu);
-                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu));
+                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, transposed, epi));
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
                 }
             }
@@ -2369,11 +2392,11 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     // (Not where the tiles add the residual-only columns of a TEW blob themselves: a split leaves those to the pass
     // of their own, which reads all of A once more - 92 against 46 us on the FFN-down of BERT-base at 512 rows.)
     pl.n_parts = 1; pl.chunks_per_part = h->n_chunks; pl.partial_bytes = 0;
-    // Teams of waves.  Calls back to back in a graph, a wave per tile -> teams: 768 -> 3072 at 1 / 64 / 512 rows
+    // Teams of waves (see team_of).  Calls back to back in a graph, a wave per tile -> teams: 768 -> 3072 at 1 / 64 / 512 rows
     // 8.2 / 9.9 / 10.3 -> 7.5 / 8.5 / 8.9 us, 768 -> 768 at 256 / 2048 rows 9.9 / 10.7 -> 8.5 / 8.9 us, transposed
     // 768 -> 2304 at 512 tokens 8.2 -> 7.0 us, 1500 -> 800 at 100 tokens 11.5 -> 8.0 us.  With five tiles or more nearly every
     // wave has a tile of its own.  (TEW blobs stay with a wave per tile: a tile's residual has steps of another kind.)
-    pl.team_shift = resident ? team_of(h, msb, (T + nseg - 1) / nseg, items, n_cu) : 0;
+    pl.team_shift = resident ? team_of(h, msb, (T + nseg - 1) / nseg, items, n_cu, transposed, epi) : 0;
     if (pl.team_shift > 0) {
         const unsigned sums = (unsigned)kWaves * h->ncb * 4096u;      // the waves' fp32 sums, over A and the staging areas
         if (sums > pl.lds_bytes) pl.lds_bytes = sums;
@@ -2620,7 +2643,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     const int n_cu = device_cus(dev);
     if (n_cu <= 0) return TW_ERR_HIP;
     Plan pl;
-    int rc = make_plan(h, M, n_cu, pl, false, ws_bytes);
+    int rc = make_plan(h, M, n_cu, pl, false, ws_bytes, epilogue_of(bias, (int)act));
     if (rc) return rc;
     const bool split = pl.n_parts > 1;
     const bool fused_epilogue = bias != nullptr || act != TW_ACT_NONE;
@@ -2715,7 +2738,7 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     const int n_cu = device_cus(dev);
     if (n_cu <= 0) return TW_ERR_HIP;
     Plan pl;
-    int rc = make_plan(h, M, n_cu, pl, /*transposed=*/true, ws_bytes);
+    int rc = make_plan(h, M, n_cu, pl, /*transposed=*/true, ws_bytes, epilogue_of(bias, (int)act));
     if (rc) return rc;
     const bool split = pl.n_parts > 1;
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's

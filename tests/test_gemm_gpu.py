@@ -345,29 +345,37 @@ def test_dense_gemm_of_buffers_without_a_last_pitch(tw, case):
                    post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "relu"))
 
 
-# name, M, K, N, G, type, keep, tiles of a workgroup at most: 8, 4 and 2 waves to a tile; fewer steps than waves; the
-# longest resident K in several batches of A; one row; a last row block of one row; K that is no multiple of 8
-TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1), ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1),
-         ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1), ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1),
-         ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2), ("wide_spans", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1),
-         ("two_waves", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4)]
+# name, M, K, N, G, type, keep, tiles of a workgroup at most, waves to a tile of the plain product on either boundary: 8, 4 and 2
+# waves; fewer steps than waves; the longest resident K in several batches of A; one row; a last row block of one row; K that
+# is no multiple of 8.  Tiles of few steps take a wave each in the plain product and a team with GELU (on both boundaries where
+# a tile has four column blocks, else row-major); both are run.
+TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1, (8, 8)),
+         ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1, (1, 1)), ("fewer_steps_narrow", 33, 40, 300, 32, "bf16", ("upow", 0.1, 1.0), 1, (8, 1)),
+         ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1, (8, 8)),
+         ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1, (1, 8)), ("one_row_heavy", 1, 771, 520, 128, "bf16", ("const", 0.8), 1, (8, 8)),
+         ("four_waves", 1000, 500, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, (4, 4)), ("four_waves_light", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, (1, 4)),
+         ("four_waves_64", 1000, 500, 700, 64, "bf16", ("upow", 0.1, 0.9), 2, (4, 4)),
+         ("wide_spans", 90, 400, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, (8, 8)), ("wide_spans_light", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, (1, 1)),
+         ("two_waves", 2600, 300, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (2, 2)), ("two_waves_light", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (1, 2)),
+         ("two_waves_64", 2600, 300, 700, 64, "f16", ("upow", 0.1, 0.9), 4, (2, 2))]
 
 
 @pytest.mark.parametrize("case", TEAMS, ids=[c[0] for c in TEAMS])
 def test_teams_of_waves(tw, case):
     """Waves that share a tile: every element on both boundaries, plain and with the fused epilogue, twice the same bits."""
-    name, M, K, N, G, dtype, keep, most = case
+    name, M, K, N, G, dtype, keep, most, waves = case
     _say(f"teams {name} M={M} K={K} N={N} G={G} {dtype}")
-    spec = W.small_spec("team_" + name, M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.7 if name == "wide_spans" else 0.06, keep=keep,
+    spec = W.small_spec("team_" + name, M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.7 if name.startswith("wide_spans") else 0.06, keep=keep,
                         seed_offset=8800 + sum(map(ord, name)))
     w = W.generate(spec)
     wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
-    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
     T = wt.info["T"]
-    assert pl["mode"] == 0 and pl["rows_per_block"] == 32 and pl["n_items"] == pl["grid"]
-    tiles = (T + pl["n_sets"] - 1) // pl["n_sets"]
-    assert tiles <= most and (most < 4 or tiles > 2) and (most != 2 or tiles == 2), (pl, T)
-    assert pl["team_waves"] == {1: 8, 2: 4, 4: 2}[most], pl
+    for tr in (False, True):
+        pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count, transposed=tr)
+        assert pl["mode"] == 0 and pl["rows_per_block"] == 32 and pl["n_items"] == pl["grid"]
+        tiles = (T + pl["n_sets"] - 1) // pl["n_sets"]
+        assert tiles <= most and (most < 4 or tiles > 2) and (most != 2 or tiles == 2), (pl, T)
+        assert pl["team_waves"] == waves[tr], (pl, T)
     A = _device_A(tw, w.A, dtype)
     At = torch.zeros((K, (M + 7) // 8 * 8), dtype=A.dtype, device="cuda:0")[:, :M]
     At.copy_(A.t())
