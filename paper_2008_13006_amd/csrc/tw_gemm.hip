@@ -2305,23 +2305,24 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
         // 35 -> 19.6, 500 -> 4000 (G = 32) at 5000 39 -> 23.0; 768 -> 3072 at 16384 and 17000 as before.
         const long nmb_full = (M + 32L * msb - 1) / (32 * msb);
         if (nmb_full < n_cu || msb == 1) {
+            // (only shares that give a workgroup fewer tiles than the one before: about 2 sqrt(T) of them)
             double best = 0.0;
-            const int top = msb;
-            for (int m = top; m >= 1; --m) {
+            for (int m = M <= 32 ? 1 : msb; m >= 1; --m) {
                 const long blocks = (M + 32L * m - 1) / (32 * m);
                 // (sharing a row block's tiles out any further than this only adds rounds)
                 const long most_segs = blocks < n_cu ? 2 * n_cu / blocks + 1 : 3;
-                for (int sg = 1; sg <= T && sg <= most_segs; ++sg) {
+                for (int sg = 1; sg <= most_segs;) {
                     const int tiles = (T + sg - 1) / sg;
-                    if (sg > 1 && (T + sg - 2) / (sg - 1) == tiles) continue;     // (as many tiles with fewer workgroups)
-                    const double rounds = (double)((blocks * sg + n_cu - 1) / n_cu);
+                    const long rounds = (blocks * sg + n_cu - 1) / n_cu;
                     const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, transposed, epi));
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
+                    if (tiles == 1) break;
+                    sg = (T + tiles - 2) / (tiles - 1);
                 }
             }
             // in one round: a tile fewer for as many workgroups as there is room for
             const long blocks = (M + 32L * msb - 1) / (32 * msb);
-            while (segs < T && blocks * (segs + 1) <= n_cu) ++segs;
+            if (blocks * segs <= n_cu) segs = (int)(n_cu / blocks < T ? n_cu / blocks : T);
         }
     } else if (msb == 2) {
         // Streamed K, 64-row blocks.  Eight tiles per workgroup (a wave per tile) when that gives every compute

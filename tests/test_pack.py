@@ -440,6 +440,31 @@ def test_plan_gives_teams_to_tiles_of_many_steps(case):
         assert pl["n_items"] <= 256 and pl["rows_per_block"] == 32 and pl["team_waves"] == waves, pl
 
 
+def test_plan_search_is_short():
+    """A weight of many narrow tiles on one row: the plan is made on every call, so its search may not walk all sharings."""
+    import time
+    N = 30522
+    w = W.generate(W.small_spec("plan_wide", M=8, K=768, N=N, G=32, dtype="f16", col_prune=0.0, keep=("const", 0.02), seed_offset=8), with_A=False)
+    wide = tw.tw_pack(w.B, w.mask, 32, "f16")
+    w = W.generate(W.small_spec("plan_narrow", M=8, K=768, N=64, G=32, dtype="f16", col_prune=0.0, keep=("const", 0.02), seed_offset=8), with_A=False)
+    narrow = tw.tw_pack(w.B, w.mask, 32, "f16")
+    assert tw.tw_info(wide)["T"] == 954
+
+    def us(blob):
+        out = tw.TwPlan()
+        args = (ctypes.c_void_p(blob.ctypes.data), 1, 256, 0, ctypes.byref(out))
+        best = 1e9
+        for _ in range(20):
+            t = time.perf_counter()
+            for _ in range(100):
+                tw._lib.tw_gemm_plan(*args)
+            best = min(best, time.perf_counter() - t)
+        return best * 1e4
+
+    # (954 sharings walked one by one: seven times the call with two)
+    assert us(wide) < 4 * us(narrow)
+
+
 def test_plan_prices_teams_only_where_they_run():
     """One narrow tile with many steps and more 32-row blocks than compute units: in several rounds nothing shares a tile, so
     one round of 64-row blocks is the faster plan (two rounds with a wave per tile take 1.7 times as long)."""
