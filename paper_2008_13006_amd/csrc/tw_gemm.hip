@@ -2239,6 +2239,11 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
 // whole chip does, the packed weights of its tiles through the compute unit's vector L1 or the steps of a heavy tile
 // (half again as many as the mean) one after the other, whichever takes longer, and the stores.  Fitted to
 // K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item, both boundaries (within 20 % of most of 150 plans timed).
+// kRoundMargin: one round of workgroups is left for several only for a tenth of its time.  Of 176 calls whose best estimate is a
+// second round 1 to 9 % below one round, one round was the faster by 8 % on average (0.85 to 1.4 times; 1065 -> 1927 at
+// 5370 rows 1.2).  Between two rounds and more the estimate needs no margin: the items are then pulled as they come and
+// more of them even out, so plans that it puts 0.1 to 10 % lower took 0.86 to 1.02 times as long row-major, 0.88 to 1.06 transposed.
+constexpr double kRoundMargin = 0.9;
 double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
     constexpr double kStartUs = 5.0, kStageBytesPerUs = 20e3, kWeightBytesPerUs = 70e3, kStepUs = 0.1, kStoreBytesPerUs = 32e3;
     const double steps = (double)h->total_steps / h->T;
@@ -2306,7 +2311,8 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
         const long nmb_full = (M + 32L * msb - 1) / (32 * msb);
         if (nmb_full < n_cu || msb == 1) {
             // (only shares that give a workgroup fewer tiles than the one before: about 2 sqrt(T) of them)
-            double best = 0.0;
+            double best = 0.0, one_round = 0.0;
+            int one_msb = msb, one_segs = 1;
             for (int m = M <= 32 ? 1 : msb; m >= 1; --m) {
                 const long blocks = (M + 32L * m - 1) / (32 * m);
                 // (sharing a row block's tiles out any further than this only adds rounds)
@@ -2316,10 +2322,12 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                     const long rounds = (blocks * sg + n_cu - 1) / n_cu;
                     const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, transposed, epi));
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
+                    if (rounds == 1 && (one_round == 0.0 || cost < one_round)) { one_round = cost; one_msb = m; one_segs = sg; }
                     if (tiles == 1) break;
                     sg = (T + tiles - 2) / (tiles - 1);
                 }
             }
+            if (one_round > 0.0 && best > kRoundMargin * one_round) { msb = one_msb; segs = one_segs; }
             // in one round: a tile fewer for as many workgroups as there is room for
             const long blocks = (M + 32L * msb - 1) / (32 * msb);
             if (blocks * segs <= n_cu) segs = (int)(n_cu / blocks < T ? n_cu / blocks : T);

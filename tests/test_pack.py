@@ -440,6 +440,21 @@ def test_plan_gives_teams_to_tiles_of_many_steps(case):
         assert pl["n_items"] <= 256 and pl["rows_per_block"] == 32 and pl["team_waves"] == waves, pl
 
 
+def test_plan_leaves_one_round_for_a_tenth_of_its_time():
+    """Plans whose best estimate is a second round less than a tenth below one round: one round (measured to be the faster);
+    with more rounds anyway, the better estimate counts, also by less."""
+    def plan(M, K, N, G, keep):
+        w = W.generate(W.small_spec("plan_margin", M=8, K=K, N=N, G=G, dtype="f16", col_prune=0.04, keep=keep, seed_offset=5), with_A=False)
+        blob = tw.tw_pack(w.B, w.mask, G, "f16")
+        return [tw.tw_gemm_plan(blob, M, n_cu=256, transposed=tr) for tr in (False, True)]
+
+    for M, K, N, G, keep in ((5370, 1065, 1927, 128, ("upow", 0.184, 0.874)), (4620, 1132, 2198, 128, ("const", 0.44)), (9189, 830, 2294, 64, ("upow", 0.228, 1.0))):
+        for pl in plan(M, K, N, G, keep):
+            assert pl["n_items"] <= 256, (M, K, N, pl)
+    for pl in plan(10774, 1073, 1439, 128, ("upow", 0.196, 0.931)):
+        assert pl["n_sets"] == 2 and pl["n_items"] == 674, pl
+
+
 def test_plan_search_is_short():
     """A weight of many narrow tiles on one row: the plan is made on every call, so its search may not walk all sharings."""
     import time
