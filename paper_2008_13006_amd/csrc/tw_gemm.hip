@@ -2274,8 +2274,9 @@ int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bo
     const int shift = most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
     const int width = h->ncb >= 4 ? 2 : h->ncb - 1;
     double cost = kTeamUs[transposed][width][epi];
-    if (transposed && shift < 3) cost -= 0.6;                         // (a tile's epilogue has fewer sums to add)
-    if (h->K > 768) cost += (transposed ? 0.55 : 1.5) + (shift == 1 ? 0.8 : 0.0);
+    const bool pair = shift == 1 && (!transposed || width == 2);      // two waves to a tile save the least
+    if (transposed && shift < 3) cost -= epi == kEpiGelu ? 1.2 : pair ? 0.3 : 0.7;   // (fewer sums to add for a result)
+    if (h->K > 768) cost += (transposed ? 0.55 : 1.5) + (pair ? 0.9 : 0.0);
     const unsigned char* blob = (const unsigned char*)h;
     const int32_t first = *(const int32_t*)(blob + h->off_sched_order);
     const int heaviest = ((const TwTileDesc*)(blob + h->off_tile_desc))[first].nsteps;

@@ -356,7 +356,7 @@ TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1, (8, 8)
          ("four_waves", 1000, 500, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, (4, 4)), ("four_waves_light", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, (1, 4)),
          ("four_waves_64", 1000, 500, 700, 64, "bf16", ("upow", 0.1, 0.9), 2, (4, 4)),
          ("wide_spans", 90, 400, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, (8, 8)), ("wide_spans_light", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, (1, 1)),
-         ("two_waves", 2600, 300, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (2, 2)), ("two_waves_light", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (1, 2)),
+         ("two_waves", 2600, 300, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (2, 2)), ("two_waves_light", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (1, 1)),
          ("two_waves_64", 2600, 300, 700, 64, "f16", ("upow", 0.1, 0.9), 4, (2, 2))]
 
 
