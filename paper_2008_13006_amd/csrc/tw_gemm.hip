@@ -1736,9 +1736,11 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) dpos[cb] = dp[cb];
     }
-    // All parts of an ordinary plan are requested before the first is added, not two at a time (a round trip to memory
-    // for every two: 3072 -> 768 at 64 / 512 rows 12.4 / 19.8 -> 11.5 / 18.6 us, transposed 4608 -> 500 at 100 tokens 15.5 -> 11.4);
-    // past the last part the last one is requested again, and not added.
+    // Seven parts more (four on the transposed boundary, where a piece has twice as many loads) are requested before the first
+    // of them is added, not two at a time (a round trip to memory for every two: 3072 -> 768 at 64 / 512 rows 12.4 / 19.8 ->
+    // 11.5 / 18.6 us, transposed 4608 -> 500 at 100 tokens 15.5 -> 11.4): all of a plan of up to eight parts at once (five; with more,
+    // in two batches).  Past the last part the last one is requested again, from the caches, and not added: a
+    // branch around those requests costs more than they do (4 to 12 parts: 0 to 4 % slower on 22 of 24 calls).
     constexpr int kAhead = TRANS ? 4 : 7;
     float col[NCB];
 #pragma unroll
