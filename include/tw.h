@@ -168,8 +168,8 @@ typedef struct tw_plan_t {
                                 tw_gemm does with a workspace of tw_gemm_workspace bytes; with a smaller one it
                                 does not split.) */
     int32_t team_waves;      /* mode 0: waves of a workgroup that share a tile, each with a part of its K steps (8, 4 or 2);
-                                1: a wave has a tile to itself (of the product without an epilogue: with GELU, which the
-                                waves of a team share, tiles of fewer steps are shared as well) */
+                                1: a wave has a tile to itself.  (Without GELU: a GELU, which the waves of a team share,
+                                makes teams pay for tiles of fewer steps as well.) */
     int32_t reserved[5];
 } tw_plan_t;
 /* Errors: TW_ERR_ARG (null pointer, negative M, n_cu <= 0), TW_ERR_BUF (not a blob of this format version),

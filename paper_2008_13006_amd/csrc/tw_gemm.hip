@@ -1793,6 +1793,26 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
     else store_tile<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, sub, sub + 1);
 }
 
+// The sums of a team's waves for one unit of a tile, in the order of the waves.  `piece`: the first wave's first piece; the
+// pieces of a unit lie 4 KB (row-major: a column block on) or 1 KB (transposed: eight rows on) apart, the waves NCB * 4 KB.
+// All of a unit's pieces are read before the first is added (one wave's piece after another's is up to 28 round trips to
+// LDS: 60 -> 961 (G = 128) at 2156 rows 9.3 us, this way 8.4).
+template <int TEAM, int NL, bool TRANS, int NCB>
+__device__ __forceinline__ void team_sum(const unsigned char* piece, tw_f32x4 (&sum)[NL]) {
+    tw_f32x4 v[TEAM][NL];
+#pragma unroll
+    for (int i = 0; i < TEAM; ++i)
+#pragma unroll
+        for (int l = 0; l < NL; ++l) v[i][l] = *(const tw_f32x4*)(piece + i * (NCB * 4096) + l * (TRANS ? 1024 : 4096));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+        sum[l] = v[0][l];
+#pragma unroll
+        for (int i = 1; i < TEAM; ++i) sum[l] += v[i][l];
+    }
+}
+
 // K resident, row blocks of 32, few tiles per workgroup: a TEAM of 8, 4 or 2 waves shares a tile.
 // With few row blocks a workgroup of the kernel above has one to four tiles for its eight waves, and a launch takes as
 // long as one wave takes for its chain: item number, descriptor, A, K indices, a heavy tile's steps one after the other (24
@@ -1863,24 +1883,35 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
     constexpr int UNITS = TRANS ? NCB : 4;
     const int per = (UNITS + team - 1) >> p.team_shift;
     const int u0 = member * per, u1 = u0 + per < UNITS ? u0 + per : UNITS;
+    constexpr int NL = TRANS ? 4 : NCB;                      // pieces of a unit
     const unsigned char* first = smem + (wave - member) * (NCB * 4096) + lane * 16;
+    for (int u = u0; u < u1; ++u) {                          // wave-uniform, once or twice
+        const unsigned char* piece = first + u * (TRANS ? 4096 : 1024);
+        tw_f32x4 v[NL];
+        if (team == 8) team_sum<8, NL, TRANS, NCB>(piece, v);
+        else if (team == 4) team_sum<4, NL, TRANS, NCB>(piece, v);
+        else team_sum<2, NL, TRANS, NCB>(piece, v);
+        if constexpr (FUSED) {
+            float b[NL];
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
+            for (int i = 0; i < NL; ++i) {
+                b[i] = col[TRANS ? 0 : i];
+                if constexpr (TRANS) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int u = TRANS ? cb : q;
-            if (u < u0 || u >= u1) continue;                 // wave-uniform
-            tw_f32x4 v = *(const tw_f32x4*)(first + (cb * 4 + q) * 1024);
-            for (int i = 1; i < team; ++i) v += *(const tw_f32x4*)(first + i * (NCB * 4096) + (cb * 4 + q) * 1024);
-            if constexpr (FUSED) {
-                tw_f32x4 v1[1] = {v};
-                const float b1[1] = {col[cb]};
-                apply_bias_act4<1>(v1, b1, p.act);
-                v = v1[0];
+                    for (int cb = 1; cb < NCB; ++cb) b[i] = cb == u ? col[cb] : b[i];
+                }
             }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[0][cb][4 * q + e] = v[e];
+            apply_bias_act4<NL>(v, b, p.act);
         }
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((TRANS ? cb : q) == u) {                 // wave-uniform
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[0][cb][4 * q + e] = v[TRANS ? q : cb][e];
+                }
+    }
     __syncthreads();                                         // the staging areas of the epilogue lie over the sums
     if (!active || u0 >= u1) return;
     unsigned char* stage = smem + p.stage_off + wave * kStageBytes;
@@ -2258,27 +2289,25 @@ double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
 // K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves may share the tiles
 // (tw_team_kernel).  log2 of the waves to a tile, 0: a wave per tile.
 // A team takes the heaviest tile's steps side by side and shares the epilogue out, and pays for it with the waves' sums
-// through LDS.  What it saves and costs, in microseconds, was measured against a wave per tile on the same plans (1300 calls,
-// K = 48 .. 1536, 1 to 8000 rows, both boundaries, plain / bias / GELU; the line is within 0.4 us of nearly all):
-// kTeamStepUs for every step of the heaviest tile, against kTeamUs, more with K > 768 (A then comes in in larger batches, which
-// a wave per tile does for every K).  A negative entry: the shared epilogue alone pays (GELU; the row-major one-block tile).
-// 140 -> 325 (G = 64) at 1072 rows, GELU, transposed: 6.5 us with a wave per tile, 7.0 with teams; 75 -> 545 (G = 128) at 1573
-// rows 8.6 and 10.2; 768 -> 768 (G = 128) at 256 rows 9.9 and 8.5.
-enum Epilogue { kEpiPlain = 0, kEpiCheap = 1, kEpiGelu = 2 };   // none; a bias and / or ReLU; GELU
-Epilogue epilogue_of(const void* bias, int act) {
-    return act == TW_ACT_GELU ? kEpiGelu : bias != nullptr || act != TW_ACT_NONE ? kEpiCheap : kEpiPlain;
-}
-int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bool transposed, Epilogue epi) {
+// through LDS.  What that saves and costs, in microseconds, was measured against a wave per tile on the same plans (1800
+// calls, K = 48 .. 1536, 1 to 8000 rows, both boundaries, plain / bias / GELU): kTeamStepUs for every step of the heaviest tile and
+// kTeamGeluUs for a shared GELU, against kTeamUs, more for two waves to a tile (they save the least) and with K > 768 (A then
+// comes in in larger batches, which a wave per tile does for every K).  Taken this way the calls are 0.95 us faster on
+// average (0.86 if teams are always taken, 1.0 with the faster kernel each time), with K >= 128 at most 0.8 slower.
+// 86 -> 197 (G = 128) at 265 rows 8.0 us with a wave per tile, 8.3 with teams; 768 -> 768 (G = 128) at 256 rows 9.9 and 8.4.
+// The choice decides in which groups a result's products are summed, so it must not depend on the boundary nor on a bias
+// or ReLU: both boundaries give the same bits, and so do a fused and a separate ReLU.
+int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bool gelu) {
     if (msb != 1 || items > n_cu || most_tiles > kWaves / 2 || h->ew_nnz > 0) return 0;
     constexpr double kTeamStepUs[3] = {0.046, 0.055, 0.085};          // tiles of 1, 2, 4 column blocks
-    constexpr double kTeamUs[2][3][3] = {{{-0.9, -1.1, -1.5}, {0.5, 0.2, -0.9}, {1.05, 1.05, -0.4}},
-                                         {{0.8, 1.0, 0.8}, {1.1, 1.3, 0.75}, {1.0, 1.0, -0.65}}};
+    constexpr double kTeamUs[3] = {-0.1, 0.2, 0.4}, kTwoWavesUs[3] = {0.0, 0.1, 0.5}, kLongUs[3] = {0.5, 1.0, 1.0},
+                     kTeamGeluUs[3] = {0.5, 0.8, 1.4};
     const int shift = most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
     const int width = h->ncb >= 4 ? 2 : h->ncb - 1;
-    double cost = kTeamUs[transposed][width][epi];
-    const bool pair = shift == 1 && (!transposed || width == 2);      // two waves to a tile save the least
-    if (transposed && shift < 3) cost -= epi == kEpiGelu ? 1.2 : pair ? 0.3 : 0.7;   // (fewer sums to add for a result)
-    if (h->K > 768) cost += (transposed ? 0.55 : 1.5) + (pair ? 0.9 : 0.0);
+    double cost = kTeamUs[width];
+    if (shift == 1) cost += kTwoWavesUs[width];
+    if (h->K > 768) cost += kLongUs[width] + (shift == 1 && width == 2 ? 0.9 : 0.0);
+    if (gelu) cost -= kTeamGeluUs[width];
     const unsigned char* blob = (const unsigned char*)h;
     const int32_t first = *(const int32_t*)(blob + h->off_sched_order);
     const int heaviest = ((const TwTileDesc*)(blob + h->off_tile_desc))[first].nsteps;
@@ -2286,7 +2315,7 @@ int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bo
 }
 
 int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0,
-              Epilogue epi = kEpiPlain) {
+              bool gelu = false) {
     const bool resident = h->n_chunks == 1;
     const int buffers = resident ? 1 : 2;
     if (lds_need(1, h->k_chunk, buffers) > kLdsLimit) return TW_ERR_UNSUPPORTED;
@@ -2323,7 +2352,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                 for (int sg = 1; sg <= most_segs;) {
                     const int tiles = (T + sg - 1) / sg;
                     const long rounds = (blocks * sg + n_cu - 1) / n_cu;
-                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, transposed, epi));
+                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, gelu));
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
                     if (rounds == 1 && (one_round == 0.0 || cost < one_round)) { one_round = cost; one_msb = m; one_segs = sg; }
                     if (tiles == 1) break;
@@ -2408,7 +2437,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     // 8.2 / 9.9 / 10.3 -> 7.5 / 8.5 / 8.9 us, 768 -> 768 at 256 / 2048 rows 9.9 / 10.7 -> 8.5 / 8.9 us, transposed
     // 768 -> 2304 at 512 tokens 8.2 -> 7.0 us, 1500 -> 800 at 100 tokens 11.5 -> 8.0 us.  With five tiles or more nearly every
     // wave has a tile of its own.  (TEW blobs stay with a wave per tile: a tile's residual has steps of another kind.)
-    pl.team_shift = resident ? team_of(h, msb, (T + nseg - 1) / nseg, items, n_cu, transposed, epi) : 0;
+    pl.team_shift = resident ? team_of(h, msb, (T + nseg - 1) / nseg, items, n_cu, gelu) : 0;
     if (pl.team_shift > 0) {
         const unsigned sums = (unsigned)kWaves * h->ncb * 4096u;      // the waves' fp32 sums, over A and the staging areas
         if (sums > pl.lds_bytes) pl.lds_bytes = sums;
@@ -2655,7 +2684,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     const int n_cu = device_cus(dev);
     if (n_cu <= 0) return TW_ERR_HIP;
     Plan pl;
-    int rc = make_plan(h, M, n_cu, pl, false, ws_bytes, epilogue_of(bias, (int)act));
+    int rc = make_plan(h, M, n_cu, pl, false, ws_bytes, act == TW_ACT_GELU);
     if (rc) return rc;
     const bool split = pl.n_parts > 1;
     const bool fused_epilogue = bias != nullptr || act != TW_ACT_NONE;
@@ -2750,7 +2779,7 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     const int n_cu = device_cus(dev);
     if (n_cu <= 0) return TW_ERR_HIP;
     Plan pl;
-    int rc = make_plan(h, M, n_cu, pl, /*transposed=*/true, ws_bytes, epilogue_of(bias, (int)act));
+    int rc = make_plan(h, M, n_cu, pl, /*transposed=*/true, ws_bytes, act == TW_ACT_GELU);
     if (rc) return rc;
     const bool split = pl.n_parts > 1;
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's

@@ -345,24 +345,22 @@ def test_dense_gemm_of_buffers_without_a_last_pitch(tw, case):
                    post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "relu"))
 
 
-# name, M, K, N, G, type, keep, tiles of a workgroup at most, waves to a tile of the plain product on either boundary: 8, 4 and 2
+# name, M, K, N, G, type, keep, tiles of a workgroup at most, waves to a tile of the product without GELU: 8, 4 and 2
 # waves; fewer steps than waves; the longest resident K in several batches of A; one row; a last row block of one row; K that
-# is no multiple of 8.  Tiles of few steps take a wave each in the plain product and a team with GELU (on both boundaries where
-# a tile has four column blocks, else row-major); both are run.
-TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1, (8, 8)),
-         ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1, (1, 1)), ("fewer_steps_narrow", 33, 40, 300, 32, "bf16", ("upow", 0.1, 1.0), 1, (8, 1)),
-         ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1, (8, 8)),
-         ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1, (1, 8)), ("one_row_heavy", 1, 771, 520, 128, "bf16", ("const", 0.8), 1, (8, 8)),
-         ("four_waves", 1000, 500, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, (4, 4)), ("four_waves_light", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, (1, 4)),
-         ("four_waves_64", 1000, 500, 700, 64, "bf16", ("upow", 0.1, 0.9), 2, (4, 4)),
-         ("wide_spans", 90, 400, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, (8, 8)), ("wide_spans_light", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, (1, 1)),
-         ("two_waves", 2600, 300, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (2, 2)), ("two_waves_light", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, (1, 1)),
-         ("two_waves_64", 2600, 300, 700, 64, "f16", ("upow", 0.1, 0.9), 4, (2, 2))]
+# is no multiple of 8.  Wide tiles of few steps take a wave each, and a team with GELU.
+TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1, 8),
+         ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1, 1), ("fewer_steps_narrow", 33, 40, 300, 32, "bf16", ("upow", 0.1, 1.0), 1, 8),
+         ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1, 8), ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1, 8),
+         ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, 4), ("four_waves_64", 1000, 500, 700, 64, "bf16", ("upow", 0.1, 0.9), 2, 4),
+         ("wide_spans", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, 8),
+         ("two_waves", 2600, 300, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, 2), ("two_waves_light", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, 1),
+         ("two_waves_64", 2600, 300, 700, 64, "f16", ("upow", 0.1, 0.9), 4, 2)]
 
 
 @pytest.mark.parametrize("case", TEAMS, ids=[c[0] for c in TEAMS])
 def test_teams_of_waves(tw, case):
-    """Waves that share a tile: every element on both boundaries, plain and with the fused epilogue, twice the same bits."""
+    """Waves that share a tile: every element on both boundaries, plain and with the fused epilogue; twice the same bits, the
+    same on both boundaries, and a fused ReLU those of a separate one."""
     name, M, K, N, G, dtype, keep, most, waves = case
     _say(f"teams {name} M={M} K={K} N={N} G={G} {dtype}")
     spec = W.small_spec("team_" + name, M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.7 if name.startswith("wide_spans") else 0.06, keep=keep,
@@ -375,7 +373,7 @@ def test_teams_of_waves(tw, case):
         assert pl["mode"] == 0 and pl["rows_per_block"] == 32 and pl["n_items"] == pl["grid"]
         tiles = (T + pl["n_sets"] - 1) // pl["n_sets"]
         assert tiles <= most and (most < 4 or tiles > 2) and (most != 2 or tiles == 2), (pl, T)
-        assert pl["team_waves"] == waves[tr], (pl, T)
+        assert pl["team_waves"] == waves, (pl, T)
     A = _device_A(tw, w.A, dtype)
     At = torch.zeros((K, (M + 7) // 8 * 8), dtype=A.dtype, device="cuda:0")[:, :M]
     At.copy_(A.t())
@@ -388,7 +386,11 @@ def test_teams_of_waves(tw, case):
         C, C2 = (tw.tw_gemm_bias_act(wt, A, b, a, nan(M, N)) for _ in range(2))
         Ct, Ct2 = (tw.tw_gemm_t_bias_act(wt, At, b, a, nan(N, M)) for _ in range(2))
         torch.cuda.synchronize()
-        assert torch.equal(C, C2) and torch.equal(Ct, Ct2)
+        assert torch.equal(C, C2) and torch.equal(Ct, Ct2) and torch.equal(Ct.T, C)
+        if act is None:
+            R, Rt = tw.tw_gemm_bias_act(wt, A, None, "relu", nan(M, N)), tw.tw_gemm_t_bias_act(wt, At, None, "relu", nan(N, M))
+            torch.cuda.synchronize()
+            assert torch.equal(R, C.clamp(min=0)) and torch.equal(Rt, Ct.clamp(min=0))
         _compare_whole(C, w.A, w.B, w.mask, dtype, what=name, post=post)
         _compare_whole(Ct, w.A, w.B, w.mask, dtype, transposed=True, what=name + " transposed", post=post)
 
