@@ -1793,24 +1793,29 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
     else store_tile<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, sub, sub + 1);
 }
 
-// The sums of a team's waves for one unit of a tile, in the order of the waves.  `piece`: the first wave's first piece; the
-// pieces of a unit lie 4 KB (row-major: a column block on) or 1 KB (transposed: eight rows on) apart, the waves NCB * 4 KB.
-// All of a unit's pieces are read before the first is added (one wave's piece after another's is up to 28 round trips to
-// LDS: 60 -> 961 (G = 128) at 2156 rows 9.3 us, this way 8.4).
-template <int TEAM, int NL, bool TRANS, int NCB>
-__device__ __forceinline__ void team_sum(const unsigned char* piece, tw_f32x4 (&sum)[NL]) {
-    tw_f32x4 v[TEAM][NL];
+// The sums of a team's waves for PER units of a tile, in the order of the waves.  `piece`: the first wave's first piece of the
+// first unit; the pieces of a unit lie 4 KB (row-major: a column block on) or 1 KB (transposed: eight rows on) apart, the units
+// 1 KB or 4 KB, the waves NCB * 4 KB.  All pieces are read before the first is added (one wave's piece after another's is up
+// to 28 round trips to LDS: 60 -> 961 (G = 128) at 2156 rows 9.3 us, this way 8.4).
+template <int TEAM, int PER, int NL, bool TRANS, int NCB>
+__device__ __forceinline__ void team_sum(const unsigned char* piece, tw_f32x4 (&sum)[PER][NL]) {
+    tw_f32x4 v[TEAM][PER][NL];
 #pragma unroll
     for (int i = 0; i < TEAM; ++i)
 #pragma unroll
-        for (int l = 0; l < NL; ++l) v[i][l] = *(const tw_f32x4*)(piece + i * (NCB * 4096) + l * (TRANS ? 1024 : 4096));
+        for (int k = 0; k < PER; ++k)
+#pragma unroll
+            for (int l = 0; l < NL; ++l)
+                v[i][k][l] = *(const tw_f32x4*)(piece + i * (NCB * 4096) + k * (TRANS ? 4096 : 1024) + l * (TRANS ? 1024 : 4096));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        sum[l] = v[0][l];
+    for (int k = 0; k < PER; ++k)
 #pragma unroll
-        for (int i = 1; i < TEAM; ++i) sum[l] += v[i][l];
-    }
+        for (int l = 0; l < NL; ++l) {
+            sum[k][l] = v[0][k][l];
+#pragma unroll
+            for (int i = 1; i < TEAM; ++i) sum[k][l] += v[i][k][l];
+        }
 }
 
 // K resident, row blocks of 32, few tiles per workgroup: a TEAM of 8, 4 or 2 waves shares a tile.
@@ -1885,33 +1890,39 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
     const int u0 = member * per, u1 = u0 + per < UNITS ? u0 + per : UNITS;
     constexpr int NL = TRANS ? 4 : NCB;                      // pieces of a unit
     const unsigned char* first = smem + (wave - member) * (NCB * 4096) + lane * 16;
-    for (int u = u0; u < u1; ++u) {                          // wave-uniform, once or twice
-        const unsigned char* piece = first + u * (TRANS ? 4096 : 1024);
-        tw_f32x4 v[NL];
-        if (team == 8) team_sum<8, NL, TRANS, NCB>(piece, v);
-        else if (team == 4) team_sum<4, NL, TRANS, NCB>(piece, v);
-        else team_sum<2, NL, TRANS, NCB>(piece, v);
+    auto add_up = [&](auto team_size) {
+        constexpr int TEAM = decltype(team_size)::value, PER = (UNITS + TEAM - 1) / TEAM;
+        tw_f32x4 v[PER][NL];
+        if (u0 < UNITS) team_sum<TEAM, PER, NL, TRANS, NCB>(first + u0 * (TRANS ? 4096 : 1024), v);
         if constexpr (FUSED) {
-            float b[NL];
 #pragma unroll
-            for (int i = 0; i < NL; ++i) {
-                b[i] = col[TRANS ? 0 : i];
-                if constexpr (TRANS) {
+            for (int k = 0; k < PER; ++k) {
+                float b[NL];
 #pragma unroll
-                    for (int cb = 1; cb < NCB; ++cb) b[i] = cb == u ? col[cb] : b[i];
+                for (int l = 0; l < NL; ++l) {
+                    b[l] = col[TRANS ? 0 : l];
+                    if constexpr (TRANS) {
+#pragma unroll
+                        for (int cb = 1; cb < NCB; ++cb) b[l] = cb == u0 + k ? col[cb] : b[l];
+                    }
                 }
+                apply_bias_act4<NL>(v[k], b, p.act);
             }
-            apply_bias_act4<NL>(v, b, p.act);
         }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if ((TRANS ? cb : q) == u) {                 // wave-uniform
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[0][cb][4 * q + e] = v[TRANS ? q : cb][e];
-                }
-    }
+                for (int k = 0; k < PER; ++k)
+                    if ((TRANS ? cb : q) == u0 + k) {        // wave-uniform
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[0][cb][4 * q + e] = v[k][TRANS ? q : cb][e];
+                    }
+    };
+    if (team == 8) add_up(std::integral_constant<int, 8>{});
+    else if (team == 4) add_up(std::integral_constant<int, 4>{});
+    else add_up(std::integral_constant<int, 2>{});
     __syncthreads();                                         // the staging areas of the epilogue lie over the sums
     if (!active || u0 >= u1) return;
     unsigned char* stage = smem + p.stage_off + wave * kStageBytes;
@@ -2289,18 +2300,18 @@ double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
 // K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves may share the tiles
 // (tw_team_kernel).  log2 of the waves to a tile, 0: a wave per tile.
 // A team takes the heaviest tile's steps side by side and shares the epilogue out, and pays for it with the waves' sums
-// through LDS.  What that saves and costs, in microseconds, was measured against a wave per tile on the same plans (1800
+// through LDS.  What that saves and costs, in microseconds, was measured against a wave per tile on the same plans (2400
 // calls, K = 48 .. 1536, 1 to 8000 rows, both boundaries, plain / bias / GELU): kTeamStepUs for every step of the heaviest tile and
 // kTeamGeluUs for a shared GELU, against kTeamUs, more for two waves to a tile (they save the least) and with K > 768 (A then
-// comes in in larger batches, which a wave per tile does for every K).  Taken this way the calls are 0.95 us faster on
-// average (0.86 if teams are always taken, 1.0 with the faster kernel each time), with K >= 128 at most 0.8 slower.
-// 86 -> 197 (G = 128) at 265 rows 8.0 us with a wave per tile, 8.3 with teams; 768 -> 768 (G = 128) at 256 rows 9.9 and 8.4.
+// comes in in larger batches, which a wave per tile does for every K).  Teams taken by this line or always, the calls are 1.15
+// us faster on average (1.18 with the faster kernel each time), but always taken some lose 1.6 us, by the line 0.9.
+// 997 -> 204 (G = 128) at 28 rows 9.0 us with a wave per tile, 9.8 with teams; 768 -> 768 (G = 128) at 256 rows 9.9 and 7.7.
 // The choice decides in which groups a result's products are summed, so it must not depend on the boundary nor on a bias
 // or ReLU: both boundaries give the same bits, and so do a fused and a separate ReLU.
 int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bool gelu) {
     if (msb != 1 || items > n_cu || most_tiles > kWaves / 2 || h->ew_nnz > 0) return 0;
     constexpr double kTeamStepUs[3] = {0.046, 0.055, 0.085};          // tiles of 1, 2, 4 column blocks
-    constexpr double kTeamUs[3] = {-0.1, 0.2, 0.4}, kTwoWavesUs[3] = {0.0, 0.1, 0.5}, kLongUs[3] = {0.5, 1.0, 1.0},
+    constexpr double kTeamUs[3] = {-0.1, 0.0, 0.2}, kTwoWavesUs[3] = {0.0, 0.1, 0.5}, kLongUs[3] = {0.5, 1.0, 1.0},
                      kTeamGeluUs[3] = {0.5, 0.8, 1.4};
     const int shift = most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
     const int width = h->ncb >= 4 ? 2 : h->ncb - 1;

@@ -349,9 +349,9 @@ def test_dense_gemm_of_buffers_without_a_last_pitch(tw, case):
 # waves; fewer steps than waves; the longest resident K in several batches of A; one row; a last row block of one row; K that
 # is no multiple of 8.  Wide tiles of few steps take a wave each, and a team with GELU.
 TEAMS = [("eight_waves", 97, 768, 600, 128, "f16", ("upow", 0.1, 0.6), 1, 8),
-         ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1, 1), ("fewer_steps_narrow", 33, 40, 300, 32, "bf16", ("upow", 0.1, 1.0), 1, 8),
+         ("fewer_steps_than_waves", 33, 40, 300, 64, "bf16", ("upow", 0.1, 1.0), 1, 8), ("fewer_steps_narrow", 33, 40, 300, 32, "bf16", ("upow", 0.1, 1.0), 1, 8),
          ("longest_k", 65, 1536, 256, 32, "f16", ("upow", 0.05, 0.9), 1, 8), ("one_row", 1, 771, 520, 128, "bf16", ("const", 0.5), 1, 8),
-         ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, 4), ("four_waves_64", 1000, 500, 700, 64, "bf16", ("upow", 0.1, 0.9), 2, 4),
+         ("fewer_steps_wide", 33, 24, 300, 128, "f16", ("upow", 0.1, 1.0), 1, 1), ("four_waves", 1000, 200, 1200, 128, "f16", ("upow", 0.1, 0.6), 2, 4), ("four_waves_64", 1000, 500, 700, 64, "bf16", ("upow", 0.1, 0.9), 2, 4),
          ("wide_spans", 90, 256, 1400, 128, "f16", ("upow", 0.1, 0.6), 1, 8),
          ("two_waves", 2600, 300, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, 2), ("two_waves_light", 2600, 96, 1200, 128, "bf16", ("upow", 0.1, 0.9), 4, 1),
          ("two_waves_64", 2600, 300, 700, 64, "f16", ("upow", 0.1, 0.9), 4, 2)]
