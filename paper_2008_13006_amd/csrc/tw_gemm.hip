@@ -2283,11 +2283,16 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
 // whole chip does, the packed weights of its tiles through the compute unit's vector L1 or the steps of a heavy tile
 // (half again as many as the mean) one after the other, whichever takes longer, and the stores.  Fitted to
 // K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item, both boundaries (within 20 % of most of 150 plans timed).
-// kRoundMargin: one round of workgroups is left for several only for a tenth of its time.  Of 176 calls whose best estimate is a
-// second round 1 to 9 % below one round, one round was the faster by 8 % on average (0.85 to 1.4 times; 1065 -> 1927 at
-// 5370 rows 1.2).  Between two rounds and more the estimate needs no margin: the items are then pulled as they come and
-// more of them even out, so plans that it puts 0.1 to 10 % lower took 0.86 to 1.02 times as long row-major, 0.88 to 1.06 transposed.
+// kRoundMargin: with K > kMarginK one round of workgroups is left for several only for a tenth of its time (a second round
+// brings all of A in again, at more than the estimate has for it).  Of 128 calls whose best estimate is a second round 1 to
+// 9 % below one round, one round was the faster by 14 % on average (0.90 to 1.42 times; 1065 -> 1927 at 5370 rows 1.2); TEW blobs
+// alike.  Of 64 such calls with shorter K the second round was the faster by 2 % (0.85 to 1.17), of TEW blobs by 12 %: 678 ->
+// 2304 (G = 32) at 8338 rows 76 us, 85 in one round.  Between two rounds and more the estimate needs no margin: the items
+// are then pulled as they come and more of them even out, so plans that it puts 0.1 to 10 % lower took 0.86 to 1.02
+// times as long row-major, 0.88 to 1.06 transposed.
 constexpr double kRoundMargin = 0.9;
+constexpr int kMarginK = 768;
+
 double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
     constexpr double kStartUs = 5.0, kStageBytesPerUs = 20e3, kWeightBytesPerUs = 70e3, kStepUs = 0.1, kStoreBytesPerUs = 32e3;
     const double steps = (double)h->total_steps / h->T;
@@ -2370,7 +2375,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                     sg = (T + tiles - 2) / (tiles - 1);
                 }
             }
-            if (one_round > 0.0 && best > kRoundMargin * one_round) { msb = one_msb; segs = one_segs; }
+            if (one_round > 0.0 && best > kRoundMargin * one_round && h->K > kMarginK) { msb = one_msb; segs = one_segs; }
             // in one round: a tile fewer for as many workgroups as there is room for
             const long blocks = (M + 32L * msb - 1) / (32 * msb);
             if (blocks * segs <= n_cu) segs = (int)(n_cu / blocks < T ? n_cu / blocks : T);

@@ -456,6 +456,14 @@ def test_plan_leaves_one_round_for_a_tenth_of_its_time():
         assert pl["n_sets"] == 2 and pl["n_items"] == 674, pl
 
 
+def test_plan_of_a_short_k_takes_the_better_estimate():
+    """The margin for one round is asked where a second round brings much of A in again, not of a short K."""
+    w = W.generate(W.small_spec("plan_short", M=8, K=678, N=2304, G=32, dtype="f16", col_prune=0.055, keep=("const", 0.42), seed_offset=5), with_A=False)
+    tew = tw.tw_pack_tew(w.B, w.mask, tw.tw_restore_ew(w.B, w.mask, 0.0123, "f16"), 32, "f16")
+    for blob in (tew, tw.tw_pack(w.B, w.mask, 32, "f16")):
+        assert tw.tw_gemm_plan(blob, 8338, n_cu=256)["n_items"] > 256
+
+
 def test_plan_search_is_short():
     """A weight of many narrow tiles on one row: the plan is made on every call, so its search may not walk all sharings."""
     import time
