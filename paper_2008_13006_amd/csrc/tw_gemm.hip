@@ -1716,7 +1716,6 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
     const int sub = unit % SUB, mt = unit / SUB;
     const int mb = mt / p.T, ti = mt - mb * p.T;
     const int row0 = mb * p.row_step;
-    const TileU d = fetch_tile(p, ti);
     const long part_stride = (long)p.n_mblocks * p.T * (MS * NCB * 1024);
     const float* src = p.partials + ((long)mb * p.T + ti) * (long)(MS * NCB * 1024) + lane * 4;
     // load i of the piece: row-major (ms, q) = sub, cb = i; transposed cb = sub, (ms, q) = i
@@ -1726,26 +1725,48 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
         const int msq = TRANS ? i : sub, cb = TRANS ? sub : i;
         off[i] = (((msq >> 2) * NCB + cb) * 4 + (msq & 3)) * 256;
     }
-    // (the first part is requested before anything waits for the tile's descriptor)
+    // The first parts (as many as a hundred registers or so hold: 8 with four loads to a piece, 12 with two, 16 with one, 5 on the
+    // transposed boundary with eight) are requested before anything waits, for the tile's descriptor or for one of them;
+    // further parts follow in batches.  Past the last part the last one is requested again, from the caches, and not
+    // added (branches around those requests cost more than they do; half as many requests go out for half as many parts).
+    // Two parts at a time, a round trip to memory for every two: 3072 -> 768 at 64 / 512 rows 12.3 / 17.4 us, this way 11.0 /
+    // 16.7, transposed 4608 -> 500 at 100 tokens 13.7, this way 11.3.
+    constexpr int kFirst = TRANS ? 5 : NL == 4 ? 8 : NL == 2 ? 12 : 16, kAhead = TRANS ? 4 : 7;
     tw_f32x4 s[NL];
-#pragma unroll
-    for (int i = 0; i < NL; ++i) s[i] = *(const tw_f32x4*)(src + off[i]);
+    TileU d;
     unsigned dpos[NCB];
-    {
+    float col[NCB];
+    auto fetch_columns = [&] {
+        d = fetch_tile(p, ti);
         const unsigned* dp = (const unsigned*)(p.blob + p.off_dpos) + ((long)d.tile * 32 + (lane & 31)) * NCB;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) dpos[cb] = dp[cb];
-    }
-    // Seven parts more (four on the transposed boundary, where a piece has twice as many loads) are requested before the first
-    // of them is added, not two at a time (a round trip to memory for every two: 3072 -> 768 at 64 / 512 rows 12.4 / 19.8 ->
-    // 11.5 / 18.6 us, transposed 4608 -> 500 at 100 tokens 15.5 -> 11.4): all of a plan of up to eight parts at once (five; with more,
-    // in two batches).  Past the last part the last one is requested again, from the caches, and not added: a
-    // branch around those requests costs more than they do (4 to 12 parts: 0 to 4 % slower on 22 of 24 calls).
-    constexpr int kAhead = TRANS ? 4 : 7;
-    float col[NCB];
+    };
+    if constexpr (FUSED) fetch_columns();                   // (the bias follows from them: they must not wait for the parts)
+    auto first_parts = [&](auto batch) {
+        constexpr int B = decltype(batch)::value;
+        tw_f32x4 v[B][NL];
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) col[cb] = 0.f;
-    for (int part = 1; part < p.n_parts; part += kAhead) {
+        for (int a = 0; a < B; ++a) {
+            const int from = a < p.n_parts ? a : p.n_parts - 1;
+#pragma unroll
+            for (int i = 0; i < NL; ++i) v[a][i] = *(const tw_f32x4*)(src + from * part_stride + off[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FUSED) fetch_col_bias<DT, NCB>(p, d, dpos, col);
+        else fetch_columns();
+#pragma unroll
+        for (int i = 0; i < NL; ++i) s[i] = v[0][i];
+#pragma unroll
+        for (int a = 1; a < B; ++a)
+            if (a < p.n_parts) {                            // wave-uniform
+#pragma unroll
+                for (int i = 0; i < NL; ++i) s[i] += v[a][i];
+            }
+    };
+    if (p.n_parts <= (kFirst + 1) / 2) first_parts(std::integral_constant<int, (kFirst + 1) / 2>{});
+    else first_parts(std::integral_constant<int, kFirst>{});
+    for (int part = kFirst; part < p.n_parts; part += kAhead) {
         tw_f32x4 v[kAhead][NL];
 #pragma unroll
         for (int a = 0; a < kAhead; ++a) {
@@ -1754,8 +1775,6 @@ __global__ __launch_bounds__(64) void tw_splitk_reduce_kernel(const TwGemmParams
             for (int i = 0; i < NL; ++i) v[a][i] = *(const tw_f32x4*)(src + from * part_stride + off[i]);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (FUSED)
-            if (part == 1) fetch_col_bias<DT, NCB>(p, d, dpos, col);      // (behind the parts' requests)
 #pragma unroll
         for (int a = 0; a < kAhead; ++a)
             if (part + a < p.n_parts) {                     // wave-uniform
