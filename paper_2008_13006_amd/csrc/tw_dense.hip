@@ -97,7 +97,8 @@ __device__ __forceinline__ tw_u32x4 descriptor(const unsigned short* base) {
 }
 
 // the t-th block of C: four row blocks are walked together, so that the workgroups of one XCD (neighbouring t) share
-// rows of A and columns of B in its L2
+// rows of A and columns of B in its L2.  (One, two, four, eight together: the same on full batches, 512 x 768 x 3072 11.0, 10.35,
+// 10.3, 10.3 us, 300 x 130 x 66000 25.1, 26.1, 24.4, 24.6, 16384 x 3072 x 768 82.3, 83.4, 82.5, 83.5.)
 __device__ __forceinline__ void block_of(const DenseParams& p, int t, int bm, int& m0, int& n0) {
     const int per = 4 * p.nbn, g = t / per, rem = t - g * per;
     const int gm = p.nbm - 4 * g < 4 ? p.nbm - 4 * g : 4;

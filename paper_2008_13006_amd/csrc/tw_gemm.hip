@@ -2286,6 +2286,8 @@ constexpr unsigned kLdsLimit = 160 * 1024;
 // the more workgroups stream at once (1 + kLoadedChunk at a full round), the tiles' partial results leave a
 // compute unit at kCuStoreBytesPerUs; the second kernel costs kReduceUs plus, per wave that a compute unit gets,
 // kReduceWaveUs and its loads at kCuLoadBytesPerUs.  A split must promise kSplitMargin of the unsplit time or less.
+// (The constants are older than the second kernel's requests ahead: of 91 split plans timed, the estimate is 1.3 times the
+// measured time in the median, and the split is 1.08 to 4 times as fast as the same call unsplit.  It errs to the unsplit side.)
 constexpr double kItemUs = 4.5, kChunkUs = 3.3, kChunkUsT = 2.8, kNarrowChunk = 0.85, kSplitItemUs = 5.5,
                  kLoadedChunk = 0.4, kCuStoreBytesPerUs = 38e3, kReduceUs = 2.5, kReduceWaveUs = 0.25,
                  kCuLoadBytesPerUs = 24e3, kSplitMargin = 0.9;
@@ -2301,7 +2303,9 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
 // Estimate of an item with K resident, in microseconds: launch and first operands, bringing in 32 * msb rows of A while the
 // whole chip does, the packed weights of its tiles through the compute unit's vector L1 or the steps of a heavy tile
 // (half again as many as the mean) one after the other, whichever takes longer, and the stores.  Fitted to
-// K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item, both boundaries (within 20 % of most of 150 plans timed).
+// K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item.  It serves to compare the plans of one call: of 180 calls timed it is
+// 1.09 times the measured time in the median row-major and 1.36 times transposed, and three in four lie within 20 % of
+// their boundary's median.
 // kRoundMargin: with K > kMarginK one round of workgroups is left for several only for a tenth of its time (a second round
 // brings all of A in again, at more than the estimate has for it).  Of 128 calls whose best estimate is a second round 1 to
 // 9 % below one round, one round was the faster by 14 % on average (0.90 to 1.42 times; 1065 -> 1927 at 5370 rows 1.2); TEW blobs
