@@ -2333,13 +2333,13 @@ double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
 // kTeamGeluUs for a shared GELU, against kTeamUs, more for two waves to a tile (they save the least) and with K > 768 (A then
 // comes in in larger batches, which a wave per tile does for every K).  Teams taken by this line or always, the calls are 1.15
 // us faster on average (1.18 with the faster kernel each time), but always taken some lose 1.6 us, by the line 0.9.
-// 997 -> 204 (G = 128) at 28 rows 9.0 us with a wave per tile, 9.8 with teams; 768 -> 768 (G = 128) at 256 rows 9.9 and 7.7.
+// 168 -> 3699 (G = 128) at 934 rows 9.8 us with a wave per tile, 10.6 with teams; 768 -> 768 (G = 128) at 256 rows 9.9 and 7.7.
 // The choice decides in which groups a result's products are summed, so it must not depend on the boundary nor on a bias
 // or ReLU: both boundaries give the same bits, and so do a fused and a separate ReLU.
 int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bool gelu) {
     if (msb != 1 || items > n_cu || most_tiles > kWaves / 2 || h->ew_nnz > 0) return 0;
     constexpr double kTeamStepUs[3] = {0.046, 0.055, 0.085};          // tiles of 1, 2, 4 column blocks
-    constexpr double kTeamUs[3] = {-0.1, 0.0, 0.2}, kTwoWavesUs[3] = {0.0, 0.1, 0.5}, kLongUs[3] = {0.5, 1.0, 1.0},
+    constexpr double kTeamUs[3] = {-0.1, 0.0, 0.2}, kTwoWavesUs[3] = {0.0, 0.1, 0.5}, kLongUs[3] = {0.3, 0.7, 0.5},
                      kTeamGeluUs[3] = {0.5, 0.8, 1.4};
     const int shift = most_tiles <= 1 ? 3 : most_tiles <= 2 ? 2 : 1;
     const int width = h->ncb >= 4 ? 2 : h->ncb - 1;

@@ -426,8 +426,8 @@ def test_plan_says_where_waves_share_tiles():
 
 # M, K, N, G, kept rows, waves to a tile: which was measured to be faster over both boundaries
 @pytest.mark.parametrize("case", [(1573, 75, 545, 128, 0.4, 1), (265, 86, 197, 128, 0.3, 1), (1673, 90, 64, 64, 0.2, 8), (1072, 141, 325, 64, 0.4, 8),
-                                  (112, 134, 481, 32, 0.4, 8), (2, 351, 293, 32, 0.4, 8), (28, 997, 204, 128, 0.2, 1), (28, 997, 204, 128, 0.4, 8),
-                                  (2600, 300, 1100, 128, 0.9, 2), (2600, 140, 1100, 128, 0.5, 1), (2, 1000, 96, 32, 0.1, 1), (2, 1000, 96, 32, 0.3, 8),
+                                  (112, 134, 481, 32, 0.4, 8), (2, 351, 293, 32, 0.4, 8), (28, 997, 204, 128, 0.1, 1), (28, 997, 204, 128, 0.2, 8),
+                                  (2600, 300, 1100, 128, 0.9, 2), (2600, 140, 1100, 128, 0.5, 1), (2, 1000, 96, 32, 0.05, 1), (2, 1000, 96, 32, 0.1, 8),
                                   (256, 768, 768, 128, 0.5, 8), (1, 768, 768, 128, 0.4, 8), (100, 1500, 800, 128, 0.5, 8)],
                          ids=lambda c: "x".join(map(str, c[:4])))
 def test_plan_gives_teams_to_tiles_of_many_steps(case):
