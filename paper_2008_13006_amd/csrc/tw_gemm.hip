@@ -2301,11 +2301,13 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
 }
 
 // Estimate of an item with K resident, in microseconds: launch and first operands, bringing in 32 * msb rows of A while the
-// whole chip does, the packed weights of its tiles through the compute unit's vector L1 or the steps of a heavy tile
-// (half again as many as the mean) one after the other, whichever takes longer, and the stores.  Fitted to
-// K = 300 .. 1400, G = 32 .. 128, 1 to 119 tiles per item.  It serves to compare the plans of one call: of 180 calls timed it is
-// 1.09 times the measured time in the median row-major and 1.36 times transposed, and three in four lie within 20 % of
-// their boundary's median.
+// whole chip does, and then whichever takes longer: the packed weights of its tiles through the compute unit's vector L1
+// and the stores; or a wave's tiles one after the other, each with the steps of a heavy tile (half again as many as the
+// mean) and an epilogue, which GELU lengthens.  It serves to compare the plans of one call.  On 640 calls (64 to 900 columns of
+// A, 700 to 8192 rows) timed with 32-row and with 64-row blocks in one round, its choice takes 0.8 % more than the faster one
+// on average, more than a tenth in 2 % of them; without the epilogue in the chain it was 2.3 % and 7 % (320 -> 3381, G =
+// 32, GELU, at 989 rows: 13.6 us with 64-row blocks and seven tiles for eight waves, 15.5 with 32 rows and thirteen).  What it
+// does not see is a heavy tile among many light ones: 256 -> 3008 at 4096 tokens, transposed, takes 12.6 us by it, 10.9 with 64 rows.
 // kRoundMargin: with K > kMarginK one round of workgroups is left for several only for a tenth of its time (a second round
 // brings all of A in again, at more than the estimate has for it).  Of 128 calls whose best estimate is a second round 1 to
 // 9 % below one round, one round was the faster by 14 % on average (0.90 to 1.42 times; 1065 -> 1927 at 5370 rows 1.2); TEW blobs
@@ -2316,13 +2318,14 @@ unsigned lds_need(int msb, int k_chunk, int buffers) {
 constexpr double kRoundMargin = 0.9;
 constexpr int kMarginK = 768;
 
-double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift) {
-    constexpr double kStartUs = 5.0, kStageBytesPerUs = 20e3, kWeightBytesPerUs = 70e3, kStepUs = 0.1, kStoreBytesPerUs = 32e3;
+double resident_item_us(const TwHeader* h, int msb, int tiles, int team_shift, bool gelu) {
+    constexpr double kStartUs = 5.0, kStageBytesPerUs = 20e3, kWeightBytesPerUs = 70e3, kStoreBytesPerUs = 32e3, kStepUs = 0.1,
+                     kEpilogueUs = 1.5, kGeluUs = 2.0, kTallEpilogue = 1.4;
     const double steps = (double)h->total_steps / h->T;
-    const double weights = tiles * steps * h->ncb * 1024.0 / kWeightBytesPerUs;
-    const double chain = 1.5 * steps * kStepUs * ((tiles + kWaves - 1) / kWaves) / (1 << team_shift);
-    return kStartUs + 64.0 * msb * h->K / kStageBytesPerUs + (weights > chain ? weights : chain) +
-           tiles * 64.0 * msb * h->G / kStoreBytesPerUs;
+    const double through = tiles * (steps * h->ncb * 1024.0 / kWeightBytesPerUs + 64.0 * msb * h->G / kStoreBytesPerUs);
+    const double epilogue = (kEpilogueUs + (gelu ? kGeluUs * h->G / 128.0 : 0.0)) * (msb > 1 ? kTallEpilogue : 1.0);
+    const double chain = ((tiles + kWaves - 1) / kWaves) * (1.5 * steps * kStepUs / (1 << team_shift) + epilogue);
+    return kStartUs + 64.0 * msb * h->K / kStageBytesPerUs + (through > chain ? through : chain);
 }
 
 // K resident, 32-row blocks, one round of workgroups with at most four tiles each: teams of waves may share the tiles
@@ -2391,7 +2394,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                 for (int sg = 1; sg <= most_segs;) {
                     const int tiles = (T + sg - 1) / sg;
                     const long rounds = (blocks * sg + n_cu - 1) / n_cu;
-                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, gelu));
+                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, gelu), gelu);
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
                     if (rounds == 1 && (one_round == 0.0 || cost < one_round)) { one_round = cost; one_msb = m; one_segs = sg; }
                     if (tiles == 1) break;

@@ -489,6 +489,16 @@ def test_plan_search_is_short():
     assert us(wide) < 4 * us(narrow)
 
 
+def test_plan_counts_a_waves_epilogues():
+    """Short tiles with GELU, a few hundred rows: 64-row blocks with a tile per wave, not 32-row blocks with two (the estimate
+    is for the plain product here, whose epilogue counts as well)."""
+    w = W.generate(W.small_spec("plan_epi", M=8, K=320, N=3381, G=32, dtype="bf16", col_prune=0.046, keep=("const", 0.167), seed_offset=5), with_A=False)
+    blob = tw.tw_pack(w.B, w.mask, 32, "bf16")
+    for tr in (False, True):
+        pl = tw.tw_gemm_plan(blob, 989, n_cu=256, transposed=tr)
+        assert pl["n_items"] <= 256 and -(-tw.tw_info(blob)["T"] // pl["n_sets"]) <= 8, pl
+
+
 def test_plan_prices_teams_only_where_they_run():
     """One narrow tile with many steps and more 32-row blocks than compute units: in several rounds nothing shares a tile, so
     one round of 64-row blocks is the faster plan (two rounds with a wave per tile take 1.7 times as long)."""
