@@ -170,7 +170,10 @@ typedef struct tw_plan_t {
     int32_t team_waves;      /* mode 0: waves of a workgroup that share a tile, each with a part of its K steps (8, 4 or 2);
                                 1: a wave has a tile to itself.  (Without GELU: a GELU, which the waves of a team share,
                                 makes teams pay for tiles of fewer steps as well.) */
-    int32_t reserved[5];
+    int32_t tile_items;      /* tw_gemm_t: > 0: a kernel with a workgroup for every tile of every block of 128 (G = 128) or 256
+                                tokens runs in place of the plan above, this many workgroups.  (Without GELU, which
+                                weighs in that choice where they are few.) */
+    int32_t reserved[4];
 } tw_plan_t;
 /* Errors: TW_ERR_ARG (null pointer, negative M, n_cu <= 0), TW_ERR_BUF (not a blob of this format version),
  * TW_ERR_UNSUPPORTED (what tw_gemm / tw_gemm_t would refuse for this blob and M).  M = 0 or a blob without

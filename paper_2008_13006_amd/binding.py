@@ -48,7 +48,8 @@ class TwPlan(ctypes.Structure):
     _fields_ = [("mode", ctypes.c_int32), ("rows_per_block", ctypes.c_int32), ("tiles_per_set", ctypes.c_int32),
                 ("n_row_blocks", ctypes.c_int32), ("n_sets", ctypes.c_int32), ("n_items", ctypes.c_int32),
                 ("grid", ctypes.c_int32), ("lds_bytes", ctypes.c_uint32), ("row_lists", ctypes.c_int32),
-                ("k_parts", ctypes.c_int32), ("team_waves", ctypes.c_int32), ("reserved", ctypes.c_int32 * 5)]
+                ("k_parts", ctypes.c_int32), ("team_waves", ctypes.c_int32), ("tile_items", ctypes.c_int32),
+                ("reserved", ctypes.c_int32 * 4)]
 
 
 def _load() -> ctypes.CDLL:

@@ -71,23 +71,8 @@ __device__ __forceinline__ int fresh(int x) {
 constexpr unsigned kRange = 0x80000000u;
 __device__ const unsigned tw_dense_zeros[4] = {0u, 0u, 0u, 0u};
 
-// 64 x 16 bytes from memory straight to 1 KB of LDS at `lds` (lane l's piece at lds + 16 l).  Written as assembly: the
-// compiler orders every later LDS read behind the completion of the builtin's load, whichever buffer it
-// fills.  There are no output registers; lds_wait() is the wait.  (m0 needs a wait state before its use.)
-template <bool NT>
-__device__ __forceinline__ void load_lds(tw_u32x4 srd, unsigned voff, unsigned lds) {
-    if constexpr (NT)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" :: "s"(lds), "v"(voff), "s"(srd) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(voff), "s"(srd) : "memory", "m0");
-}
 __device__ __forceinline__ void load_lds_wide(const void* src, unsigned lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "memory", "m0");
-}
-// At most N of this wave's vector memory requests outstanding, no LDS request; then the workgroup meets.
-template <int N>
-__device__ __forceinline__ void lds_wait() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
 }
 __device__ __forceinline__ void lds_meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -267,12 +252,12 @@ __global__ __launch_bounds__(kThreads) void tw_dense_kernel(const DenseParams p)
 #pragma unroll
             for (int i = 0; i < MSW; ++i) {
                 const int r = ra + 64 * i;
-                load_lds<NTA>(da, 64 * i < am ? (unsigned)r * lda2 + ua * 16 : kRange, dst + (unsigned)(wave + 8 * i) * 1024u);
+                tw_load_lds<NTA>(da, 64 * i < am ? (unsigned)r * lda2 + ua * 16 : kRange, dst + (unsigned)(wave + 8 * i) * 1024u);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int r = rb + 16 * i;
-                load_lds<false>(db, 16 * i < bm ? (unsigned)r * ldb2 + ub * 16 : kRange, dst + A_BYTES + (unsigned)(wave + 8 * i) * 1024u);
+                tw_load_lds<false>(db, 16 * i < bm ? (unsigned)r * ldb2 + ub * 16 : kRange, dst + A_BYTES + (unsigned)(wave + 8 * i) * 1024u);
             }
         }
         if (++ck == nk) {
@@ -347,7 +332,7 @@ __global__ __launch_bounds__(kThreads) void tw_dense_kernel(const DenseParams p)
     int pos = 0;                                             // buffer of the current step
     int m0, n0;                                              // block of C
     block_of(p, bid, BM, m0, n0);
-    lds_wait<(NST - 1) * kLoads>();
+    tw_lds_wait<(NST - 1) * kLoads>();
     mend_ends(smem, 0, m0, n0);
     fetch(0, smem, 0);
     for (int t = bid; t < total; t += grid) {
@@ -371,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void tw_dense_kernel(const DenseParams p)
             if (kt + 1 == nk) break;
             // the next step has landed and every wave has read this one: its buffer takes the step after the ring's last
             // (the operands are read before the requests' address arithmetic, not behind it: 36.1 -> 31.6 us on 2048 x 3072 x 768)
-            lds_wait<(NST - 2) * kLoads>();
+            tw_lds_wait<(NST - 2) * kLoads>();
             mend_ends(nxt, kt + 1, m0, n0);
             fetch(0, nxt, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -389,7 +374,7 @@ __global__ __launch_bounds__(kThreads) void tw_dense_kernel(const DenseParams p)
         if (p.bias != nullptr && elane < width) own_bias = p.bias[col0 + elane];
         __builtin_amdgcn_sched_barrier(0);
         multiply(1);
-        lds_wait<(NST - 2) * kLoads>();
+        tw_lds_wait<(NST - 2) * kLoads>();
         // epilogue through per-wave staging areas in the buffer of the last step; the next block's first steps are landing in the others
         {
             unsigned char* stage = smem + pos * BUF_BYTES + wave * kDenseStage;

@@ -110,3 +110,19 @@ __device__ __forceinline__ T* tw_opaque(T* p) {
 __device__ __forceinline__ tw_u32x4 tw_load16_stream(const void* p) {
     return __builtin_nontemporal_load((const tw_u32x4*)p);
 }
+
+// 64 x 16 bytes from memory straight to 1 KB of LDS at `lds` (lane l's piece at lds + 16 l).  Written as assembly: the
+// compiler orders every later LDS read behind the completion of the builtin's load, whichever buffer it
+// fills.  There are no output registers; tw_lds_wait() is the wait.  (m0 needs a wait state before its use.)
+template <bool NT>
+__device__ __forceinline__ void tw_load_lds(tw_u32x4 srd, unsigned voff, unsigned lds) {
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" :: "s"(lds), "v"(voff), "s"(srd) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds), "v"(voff), "s"(srd) : "memory", "m0");
+}
+// At most N of this wave's vector memory requests outstanding, no LDS request; then the workgroup meets.
+template <int N>
+__device__ __forceinline__ void tw_lds_wait() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}

@@ -79,6 +79,7 @@ struct TwGemmParams {
     int n_parts, chunks_per_part;
     float* partials;
     int team_shift;             // tw_team_kernel: log2 of the waves that share a tile (8, 4 or 2)
+    int rows_group;             // tw_rows_kernel: token blocks that are walked together (see there)
 };
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -855,9 +856,10 @@ __device__ __forceinline__ void stage_commit(const TwGemmParams& p, const ARegs<
 template <int DT, int MS, int NCB, bool FUSED, bool PART = false>
 __device__ __forceinline__ void store_tile_t(const TwGemmParams& p, const TileU& d, tw_f32x16 (&acc)[MS][NCB],
                                              unsigned char* stage, const unsigned (&dpos)[NCB], int m0, int lane_in,
-                                             int cb0 = 0, int cb1 = NCB, const unsigned short* xbuf = nullptr) {
+                                             int cb0 = 0, int cb1 = NCB, const unsigned short* xbuf = nullptr,
+                                             bool zeros = true) {
     // (cb0, cb1: the column blocks to store, all by default; the lines of zeros go with column block 0.  The
-    // second kernel of a split-K product gives a wave one column block of a tile.)
+    // second kernel of a split-K product gives a wave one column block of a tile.  zeros: whether this wave writes them.)
     constexpr int PPR = 4 * MS, RPI = 64 / PPR, PITCH = 64 * MS + 8;
     static_assert(32 * PITCH <= (int)kStageBytes, "transposed staging fits the wave's area");
     const int lane = fresh(lane_in);
@@ -912,7 +914,7 @@ __device__ __forceinline__ void store_tile_t(const TwGemmParams& p, const TileU&
         }
     }
     tw_compiler_fence();
-    if (cb0 != 0) return;
+    if (cb0 != 0 || !zeros) return;
     // lines of zeros for the pruned columns of the span
     const int* zp = (const int*)(p.blob + p.off_zero_ptr);
     const int* zc = (const int*)(p.blob + p.off_zero_cols);
@@ -1949,6 +1951,184 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
     else store_tile<DT, MS, NCB, FUSED, true>(p, d, acc, stage, dpos, row0, lane, nullptr, nullptr, u0, u1);
 }
 
+// ---- transposed boundary, one tile of one block of tokens per workgroup ----
+// The kernels above bring a block of At into LDS once and gather from it for every tile; what a compute unit then streams is
+// the packed weights of ALL tiles per 64 tokens.  With the activations transposed there is another way: the K rows that ONE tile
+// keeps are whole rows of the block (256 or 512 bytes), so they can be fetched straight into LDS in the order of the tile's
+// contraction slots, and the product of a tile and a token block is an ordinary dense one: nothing is staged through
+// registers, no row that the tile does not keep is read, and the main loop reads LDS at fixed addresses.
+//
+// A workgroup is four waves, its block 128 tokens (tiles of four column blocks, two waves side by side) or 256 (narrower tiles); a
+// wave multiplies 64 tokens x 64 (32) columns in the order of the tile's steps, which is the order of the kernels above: both
+// boundaries give the same bits.  A ring of kRowsStages stages of one step (16 slots) is filled by direct loads.  Four workgroups fit a compute unit (at most 40 KB of LDS and 128 registers), so one's first
+// loads and stores pass while others multiply.
+//
+// LDS row r of a stage is slot position r of the step's list (off_goff); its 16-byte pieces are kept at piece ^ 4 * (r / 2 % 4): a
+// transposing read takes four rows r, r + 2, r + 4, r + 6 at the same tokens, which then lie in different banks.
+// Padded slots, tokens past M and steps past the end are offsets out of the descriptor's range: they fetch zeros.
+//
+// What bounds it: full batches the compute unit's loads (8 KB a step, about 110 ns with four workgroups in their main loops, 67 of
+// them the vector L1's rate), two workgroups or fewer the latency of a stage, 170 ns a step with four stages on their way,
+// 125 with eight.  What the compiler loads itself is consumed before the first direct load: its waits do not know of those, and a
+// wait for one of its own behind them drained the ring (16384 tokens of 768 -> 3072 41.2 us, now 34.0).
+// Before (a resident or streamed block of 64 tokens, all tiles) -> now: 16384 tokens of 768 -> 3072 39.3 -> 34.0 us, 8192 of
+// 4096 -> 1024, skewed 42.2 -> 28.1 (its heaviest tile has 159 steps), 84745 of 1152 -> 130 (G = 32) 105 -> 34, 54959 of
+// 576 -> 201 51 -> 14.
+//
+// Workgroups of one XCD (ids equal modulo 8) share its L2: the token blocks are dealt out to the XCDs, rows_group blocks at a
+// time, as many as leave the rows of those of one XCD in its L2; within a group the heaviest tiles go first.
+template <int NCB> constexpr int rows_bt() { return NCB == 4 ? 128 : 256; }
+template <int NCB> constexpr int rows_stage_bytes() { return rows_bt<NCB>() * 32 + NCB * 1024; }
+constexpr unsigned kRowsRange = 0x40000000u;               // (twice that is out of range as well)
+constexpr int kRowsStoreArea = 32 * (64 * 2 + 8);
+static_assert(4 * kRowsStoreArea <= 4 * rows_stage_bytes<4>() && 4 * kRowsStoreArea <= 4 * rows_stage_bytes<1>(),
+              "the epilogue's staging areas lie over the ring");
+
+template <int DT, int NCB, bool FUSED, int kRowsStages>
+__global__ __launch_bounds__(256, kRowsStages == 4 ? 4 : 2) void tw_rows_kernel(const TwGemmParams p) {
+    constexpr int BT = rows_bt<NCB>(), CB = NCB == 4 ? 2 : NCB, IA = BT / 128, STAGE = rows_stage_bytes<NCB>(), A_BYTES = BT * 32;
+    constexpr int kLoads = IA + 1;                           // requests of a wave per stage
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uni(tid >> 6);
+    const int wt = NCB == 4 ? wave >> 1 : wave, wc = NCB == 4 ? wave & 1 : 0;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+
+    // the item: tile number t (0: the heaviest), token block mb
+    const int per = p.rows_group * p.T, g = (int)blockIdx.x / per, rem = (int)blockIdx.x - g * per;
+    const int left = p.n_mblocks - g * p.rows_group, width = left < p.rows_group ? left : p.rows_group;
+    const int t = rem / width, m0 = (g * p.rows_group + rem - t * width) * BT;
+    // (with K resident the dispatch order puts the lightest kWaves tiles, lightest first, in front of the others)
+    const bool light_first = p.n_chunks == 1 && p.T > kWaves;
+    const TileU d = fetch_tile(p, !light_first ? t : t < p.T - kWaves ? t + kWaves : p.T - 1 - t);
+
+    auto descriptor = [](const void* base, unsigned bytes) {
+        const uint64_t b = (uint64_t)base;
+        return tw_u32x4{(unsigned)uni((int)(unsigned)b), (unsigned)uni((int)(unsigned)(b >> 32)) & 0xFFFFu, bytes, 0x00020000u};
+    };
+    const tw_u32x4 da = descriptor(p.A + m0, kRowsRange);
+    const tw_u32x4 db = descriptor(p.blob + p.off_bvals + (long)d.first_step * NCB * 1024, (unsigned)d.nsteps * (NCB * 1024u));
+    const unsigned lda2 = 2u * (unsigned)p.lda;
+
+    // What this lane fetches: request n of a stage brings row 4*wave + 2*n + its share of the wave's 4 / IA rows, and of that
+    // row the 16-byte piece that belongs at its place in LDS.
+    constexpr int kSlots = BT / 8;                           // pieces of a row
+    const int frow = 4 * wave + lane / kSlots;
+    auto swz = [](int r) { return ((r >> 1) & 3) << 2; };
+    unsigned a_off[IA];
+#pragma unroll
+    for (int n = 0; n < IA; ++n) {
+        const int piece = (lane % kSlots) ^ swz(frow + 2 * n);
+        a_off[n] = m0 + piece * 8 < p.M ? (unsigned)piece * 16u : kRowsRange;
+    }
+    const bool b_lane = lane < NCB * 16;
+    unsigned b_off = (unsigned)(wave * NCB * 256 + (lane & (NCB * 16 - 1)) * 16);   // of the step the cursor stands on
+    // Where the rows of the tile's slots lie: byte offset in At, kRowsRange for a padded slot and behind the last step.  The list
+    // waits in LDS behind the ring; the lanes work out those of the first stages themselves.
+    const unsigned short* goff = (const unsigned short*)(p.blob + p.off_goff + (long)d.first_step * 32);
+    unsigned* const list = (unsigned*)(smem + kRowsStages * STAGE);
+    int ends = 0;                                            // K streamed: lane l holds where chunk l's steps end
+    if (p.n_chunks > 1) ends = ((const int*)(p.blob + p.off_step_ptr))[d.step_ptr + 1 + (lane < p.n_chunks ? lane : p.n_chunks - 1)];
+    unsigned short first[kRowsStages][IA];
+#pragma unroll
+    for (int i = 0; i < kRowsStages; ++i)
+#pragma unroll
+        for (int n = 0; n < IA; ++n) first[i][n] = goff[(i < d.nsteps ? i : d.nsteps - 1) * 16 + frow + 2 * n];
+    const int n_list = 16 * (d.nsteps + kRowsStages + 1);    // (what is read of it: one step past the end)
+    auto slot_row = [&](int i) { return goff[i < 16 * d.nsteps ? i : 0]; };
+    unsigned short ahead[2];                                 // two slots of a thread cover 32 steps
+#pragma unroll
+    for (int n = 0; n < 2; ++n) ahead[n] = slot_row(16 * kRowsStages + tid + 256 * n);
+    unsigned dpos[CB];
+    {
+        const unsigned* dp = (const unsigned*)(p.blob + p.off_dpos) + ((long)d.tile * 32 + (lane & 31)) * NCB + wc * CB;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) dpos[cb] = dp[cb];
+    }
+    auto row_of = [&](int step, unsigned k) {                // k: chunk-local row as the blob has it
+        unsigned base = 0;
+        for (int c = 0; c + 1 < p.n_chunks; ++c) base += step >= __builtin_amdgcn_readlane(ends, c) ? (unsigned)p.k_chunk : 0u;
+        return step < d.nsteps && k != (unsigned)p.k_chunk ? __umul24(base + k, lda2) : kRowsRange;
+    };
+    auto issue = [&](unsigned buf, const unsigned (&row)[IA]) {     // buf: LDS address of the stage
+#pragma unroll
+        for (int n = 0; n < IA; ++n) tw_load_lds<false>(da, row[n] + a_off[n], buf + (unsigned)(wave * IA + n) * 1024u);
+        if (NCB == 4 || b_lane) tw_load_lds<false>(db, b_off, buf + A_BYTES + (unsigned)(wave * NCB) * 256u);
+        b_off += NCB * 1024u;
+    };
+    // (in front of the direct loads: the compiler does not count those and would wait for them with its own)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int i = 16 * kRowsStages + tid + 256 * n;
+        if (i < n_list) list[i] = row_of(i >> 4, ahead[n]);
+    }
+    unsigned kk[IA];
+#pragma unroll
+    for (int i = 0; i < kRowsStages; ++i) {
+#pragma unroll
+        for (int n = 0; n < IA; ++n) kk[n] = row_of(i, first[i][n]);
+        issue(lds0 + i * STAGE, kk);
+    }
+    for (int i = 16 * kRowsStages + 512 + tid; i < n_list; i += 256) list[i] = row_of(i >> 4, slot_row(i));
+    const unsigned* rows = list + 16 * kRowsStages + frow;   // of the step the cursor stands on
+    EpiBias<CB> eb;
+    if constexpr (FUSED) fetch_col_bias<DT, CB>(p, d, dpos, eb.col);
+
+    // where this lane's operands lie in a stage (see run_steps for the lanes of a transposing read)
+    const int h = lane >> 5, j = lane & 15, q = j >> 2;
+    const unsigned oa = (unsigned)(8 * h + 2 * q) * (BT * 2) +
+                        (unsigned)(((wt * 8 + ((lane >> 4) & 1) * 2 + ((j & 3) >> 1)) ^ (q << 2)) * 16 + (j & 1) * 8);
+    const unsigned ob = (unsigned)(A_BYTES + wc * CB * 1024 + lane * 16);
+    tw_f32x16 acc[2][CB];
+    zero_acc<2, CB>(acc);
+    tw_u16x8 a[2][2], b[2][CB];
+    auto fetch = [&](int slot, int cur) {                    // operands of the step in stage `cur` (constants)
+        const unsigned char* st = smem + cur * STAGE;
+#pragma unroll
+        for (int ms = 0; ms < 2; ++ms) {
+            const tw_i16x4 lo = tw_lds_read_tr(st + (oa ^ (unsigned)(ms * 64)));
+            const tw_i16x4 hi = tw_lds_read_tr(st + (oa ^ (unsigned)(ms * 64)) + BT * 2);
+            a[slot][ms] = tw_u16x8{(unsigned short)lo[0], (unsigned short)lo[1], (unsigned short)lo[2], (unsigned short)lo[3],
+                                   (unsigned short)hi[0], (unsigned short)hi[1], (unsigned short)hi[2], (unsigned short)hi[3]};
+        }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) b[slot][cb] = *(const tw_u16x8*)(st + ob + cb * 1024);
+    };
+    auto fetch_rows = [&] {
+#pragma unroll
+        for (int n = 0; n < IA; ++n) kk[n] = rows[2 * n];
+        rows += 16;
+    };
+    // A step: when the next step's stage has landed and every wave has this step's operands in registers, this step's stage is
+    // refilled and the next operands are read, behind this step's products.
+    auto step = [&](int cur) {                               // stage `cur` of the ring (a constant)
+        tw_lds_wait<(kRowsStages - 2) * kLoads>();
+        issue(lds0 + (unsigned)cur * STAGE, kk);
+        fetch((cur + 1) & 1, (cur + 1) % kRowsStages);
+        fetch_rows();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int ms = 0; ms < 2; ++ms) acc[ms][cb] = tw_mfma<DT>(a[cur & 1][ms], b[cur & 1][cb], acc[ms][cb]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    tw_lds_wait<(kRowsStages - 1) * kLoads>();
+    fetch(0, 0);
+    fetch_rows();
+    int s = 0;
+    for (; s + kRowsStages <= d.nsteps; s += kRowsStages) {
+#pragma unroll
+        for (int i = 0; i < kRowsStages; ++i) step(i);
+    }
+#pragma unroll
+    for (int i = 0; i < kRowsStages - 1; ++i)
+        if (s + i < d.nsteps) step(i);
+    tw_lds_wait<0>();                                        // nothing on its way into the ring any more: the staging areas lie over it
+    if constexpr (FUSED) apply_bias_act<2, CB>(acc, eb, p.act);
+    store_tile_t<DT, 2, CB, FUSED, true>(p, d, acc, smem + wave * kRowsStoreArea, dpos, m0 + wt * 64, lane, 0, CB, nullptr, wc == 0);
+}
+
 }  // namespace
 
 // ---- kernel tables
@@ -1962,6 +2142,7 @@ template <int DT, bool FUSED, bool EW> const void* pick_mode(int mode, int ms, i
 template <int DT, bool FUSED, bool EW> const void* pick_mode_t(int mode, int ms, int ncb, bool nta);   // transposed boundary
 template <int DT, bool FUSED> const void* pick_reduce(int ncb, bool transposed);               // second kernel of split K
 template <int DT, bool FUSED> const void* pick_team(int ncb, bool transposed);                 // teams of waves per tile
+template <int DT, bool FUSED> const void* pick_rows(int ncb, int stages);                                  // a tile of a token block per workgroup
 }  // namespace tw_parts
 
 #if !defined(TW_PART) || TW_PART != 0
@@ -2010,6 +2191,15 @@ const void* pick_reduce(int ncb, bool transposed) {
     }
 }
 template <int DT, bool FUSED>
+const void* pick_rows(int ncb, int stages) {
+    switch (ncb) {
+        case 1: return stages == 4 ? (const void*)tw_rows_kernel<DT, 1, FUSED, 4> : (const void*)tw_rows_kernel<DT, 1, FUSED, 8>;
+        case 2: return stages == 4 ? (const void*)tw_rows_kernel<DT, 2, FUSED, 4> : (const void*)tw_rows_kernel<DT, 2, FUSED, 8>;
+        case 4: return stages == 4 ? (const void*)tw_rows_kernel<DT, 4, FUSED, 4> : (const void*)tw_rows_kernel<DT, 4, FUSED, 8>;
+        default: return nullptr;
+    }
+}
+template <int DT, bool FUSED>
 const void* pick_team(int ncb, bool transposed) {
     switch (ncb) {
         case 1: return transposed ? (const void*)tw_team_kernel<DT, 1, FUSED, true> : (const void*)tw_team_kernel<DT, 1, FUSED, false>;
@@ -2027,7 +2217,8 @@ const void* pick_team(int ncb, bool transposed) {
     KW template const void* tw_parts::pick_mode_t<DT, FUSED, EW>(int, int, int, bool);
 #define TW_TABLES_REDUCE(KW, DT, FUSED)                                           \
     KW template const void* tw_parts::pick_reduce<DT, FUSED>(int, bool);          \
-    KW template const void* tw_parts::pick_team<DT, FUSED>(int, bool);
+    KW template const void* tw_parts::pick_team<DT, FUSED>(int, bool);            \
+    KW template const void* tw_parts::pick_rows<DT, FUSED>(int, int);
 #define TW_TABLES_ALL(KW, DT, FUSED) TW_TABLES_EW(KW, DT, FUSED, false) TW_TABLES_EW(KW, DT, FUSED, true) TW_TABLES_REDUCE(KW, DT, FUSED)
 #if TW_PART == 0
 TW_TABLES_ALL(extern, TW_F16, false) TW_TABLES_ALL(extern, TW_F16, true) TW_TABLES_ALL(extern, TW_BF16, false) TW_TABLES_ALL(extern, TW_BF16, true)
@@ -2272,6 +2463,9 @@ struct Plan {
     unsigned xbuf_off;   // row-major boundary, K resident, TEW blob with residual-only columns: LDS offset of the waves' areas for them
     int n_parts, chunks_per_part;   // split K (see TwGemmParams); n_parts = 1: none
     int team_shift;                 // log2 of the waves that share a tile (tw_team_kernel), 0: none
+    int rows_group;                 // tw_rows_kernel: token blocks walked together, 0: another kernel runs
+    int rows_stages;                // and the depth of its ring
+    unsigned rows_lds;              // and its on-chip memory per workgroup
     size_t partial_bytes;           // workspace the parts' fp32 results take, behind the counters
 };
 
@@ -2522,6 +2716,41 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     return TW_OK;
 }
 
+// Whether tw_gemm_t runs tw_rows_kernel instead of the plan's kernel (pl.rows_group, 0: no).
+// Not for plans that share a tile's K steps out (split K, teams of waves: other groups of sums), not for TEW blobs.  Otherwise
+// the workgroups of that kernel are many and short, and it is the faster one wherever its longest workgroup (kRowsUs and kRowsStepUs
+// for each step of the heaviest tile, kRowsCrowdUs with four workgroups to a compute unit) is expected to take less time
+// than the plan's kernel as a whole.  Of 70 random calls with more than 300 tokens it took 38, 1.09 to 3.7 times as fast
+// (54959 tokens of 576 -> 201 13.9 us, 50.9 before), one 3 % slower; the heaviest tile of 6400 tokens of 3133 -> 256 has 196
+// steps, 36.6 us, and stays with the streamed kernel's 33.4.
+void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu) {
+    constexpr double kRowsUs = 6.5, kRowsStepUs = 0.14, kRowsCrowdUs = 0.18, kRowsGeluUs = 2.0, kTileStepUs = 0.15;
+    constexpr long kRowsL2 = 3400 * 1024;                    // of an XCD's 4 MiB, for rows of At
+    pl.rows_group = 0;
+    if (pl.n_parts > 1 || pl.team_shift > 0 || h->ew_nnz > 0 || h->n_chunks > 64) return;
+    // (offsets below kRowsRange, products of 24-bit factors)
+    if ((unsigned long)h->K * (unsigned long)lda * 2 >= kRowsRange || lda >= (1 << 23) || h->K >= (1 << 24)) return;
+    const unsigned char* blob = (const unsigned char*)h;
+    const int heaviest = ((const TwTileDesc*)(blob + h->off_tile_desc))[*(const int32_t*)(blob + h->off_sched_order)].nsteps;
+    const int bt = h->ncb == 4 ? rows_bt<4>() : rows_bt<1>();
+    const long blocks = ((long)M + bt - 1) / bt, items = blocks * h->T;
+    if (items >= 0x7fffffffL) return;
+    // two workgroups or fewer to a compute unit: a deeper ring takes the place of the others
+    pl.rows_stages = items <= 2L * n_cu ? 8 : 4;
+    const unsigned ring = pl.rows_stages * (h->ncb == 4 ? rows_stage_bytes<4>() : h->ncb == 2 ? rows_stage_bytes<2>() : rows_stage_bytes<1>());
+    pl.rows_lds = ring + (unsigned)(heaviest + pl.rows_stages + 1) * 64u;
+    if (pl.rows_lds > (pl.rows_stages == 8 ? kLdsLimit : 64u * 1024u)) return;
+    const double rounds = (double)((pl.n_items + n_cu - 1) / n_cu);
+    const double chunks_us = h->n_chunks * kChunkUsT * (h->ncb <= 2 ? kNarrowChunk : 1.0), tile_us = heaviest * (h->ncb <= 2 ? kTileStepUs : 1.5 * kTileStepUs);
+    const double plan_us = rounds * (h->n_chunks == 1 ? resident_item_us(h, pl.ms, (h->T + pl.n_seg - 1) / pl.n_seg, 0, gelu)
+                                                      : kItemUs + (chunks_us > tile_us ? chunks_us : tile_us));   // (a tile is one wave's there)
+    const double rows_us = kRowsUs + heaviest * (pl.rows_stages == 8 ? kRowsStepUs : kRowsCrowdUs) + (gelu && items < n_cu ? kRowsGeluUs : 0.0);
+    if (rows_us >= plan_us) return;
+    const long bytes = (long)h->K * bt * 2;
+    const long group = 8 * (bytes < kRowsL2 ? kRowsL2 / bytes : 1);
+    pl.rows_group = (int)(group < blocks ? group : blocks);
+}
+
 // the kernel for (dtype, mode, MS, NCB, fused epilogue): a host-side address for hipLaunchKernel and hipFuncSetAttribute
 template <bool EW>
 const void* pick_kernel_t_of(int dt, int mode, int ms, int ncb, bool fused, bool nta) {
@@ -2546,6 +2775,11 @@ const void* pick_team_kernel(int dt, int ncb, bool fused, bool transposed) {
     using namespace tw_parts;
     if (fused) return dt == TW_F16 ? pick_team<TW_F16, true>(ncb, transposed) : pick_team<TW_BF16, true>(ncb, transposed);
     return dt == TW_F16 ? pick_team<TW_F16, false>(ncb, transposed) : pick_team<TW_BF16, false>(ncb, transposed);
+}
+const void* pick_rows_kernel(int dt, int ncb, bool fused, int stages) {
+    using namespace tw_parts;
+    if (fused) return dt == TW_F16 ? pick_rows<TW_F16, true>(ncb, stages) : pick_rows<TW_BF16, true>(ncb, stages);
+    return dt == TW_F16 ? pick_rows<TW_F16, false>(ncb, stages) : pick_rows<TW_BF16, false>(ncb, stages);
 }
 const void* pick_reduce_kernel(int dt, int ncb, bool fused, bool transposed) {
     using namespace tw_parts;
@@ -2626,6 +2860,10 @@ extern "C" int tw_gemm_plan(const void* blob_host, int M, int n_cu, int transpos
     plan->row_lists = pl.urow_off != 0;
     plan->k_parts = pl.n_parts;
     plan->team_waves = 1 << pl.team_shift;
+    if (transposed) {
+        plan_rows(h, M, ((long)M + 7) / 8 * 8, n_cu, pl, false);
+        if (pl.rows_group > 0) plan->tile_items = (int32_t)(((long)M + (h->ncb == 4 ? 127 : 255)) / (h->ncb == 4 ? 128 : 256) * h->T);
+    }
     return TW_OK;
 }
 
@@ -2823,6 +3061,7 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     Plan pl;
     int rc = make_plan(h, M, n_cu, pl, /*transposed=*/true, ws_bytes, act == TW_ACT_GELU);
     if (rc) return rc;
+    plan_rows(h, M, ldat, n_cu, pl, act == TW_ACT_GELU);
     const bool split = pl.n_parts > 1;
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's
     const bool nta = pl.mode == 0 || pl.n_seg == 1;
@@ -2867,6 +3106,17 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     const unsigned lds_bytes = pl.lds_bytes;
     const int grid = pl.n_items < n_cu ? pl.n_items : n_cu;
     void* args[] = {(void*)&p};
+    if (pl.rows_group > 0) {
+        const int bt = h->ncb == 4 ? rows_bt<4>() : rows_bt<1>();
+        p.n_mblocks = (M + bt - 1) / bt; p.rows_group = pl.rows_group;
+        const void* fr = pick_rows_kernel(h->dtype, h->ncb, fused, pl.rows_stages);
+        if (!fr) return TW_ERR_UNSUPPORTED;
+        if (pl.rows_stages == 8) {
+            rc = ensure_lds(dev, 480 + (fused ? 6 : 0) + (h->dtype == TW_F16 ? 0 : 3) + (h->ncb >> 1), fr);
+            if (rc) return rc;
+        }
+        return hipLaunchKernel(fr, dim3((unsigned)(p.n_mblocks * h->T)), dim3(256), args, pl.rows_lds, stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
+    }
     if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
     if (split) {
         const long units = (long)pl.n_mblocks * h->T * h->ncb;            // a wave per column block of a tile

@@ -345,6 +345,42 @@ def test_dense_gemm_of_buffers_without_a_last_pitch(tw, case):
                    post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "relu"))
 
 
+# name, M, K, N, G, type, keep, column pruning: a workgroup per tile and block of tokens.  All widths of a tile; one and several K chunks, chunks
+# without a step, fewer steps than the ring has stages, K no multiple of anything; more and fewer than two workgroups to a compute
+# unit (two depths of the ring); a last block of one token and of every part of 64 tokens; tokens no multiple of 8; wide spans.
+ROWS = [("wide", 16385, 300, 700, 128, "f16", ("upow", 0.05, 0.9), 0.05), ("two_blocks", 8201, 1000, 333, 64, "bf16", ("upow", 0.1, 0.6), 0.05),
+        ("narrow", 20031, 200, 250, 32, "f16", ("upow", 0.02, 0.9), 0.1), ("streamed", 8190, 3100, 520, 128, "bf16", ("upow", 0.001, 0.3), 0.1),
+        ("streamed_narrow", 6300, 1543, 300, 32, "f16", ("upow", 0.003, 0.5), 0.05), ("one_step", 40000, 40, 300, 128, "bf16", ("const", 0.2), 0.0),
+        ("one_tile", 30001, 776, 128, 128, "f16", ("const", 0.3), 0.0), ("many_tiles", 2490, 640, 2900, 64, "f16", ("upow", 0.05, 0.5), 0.3)]
+
+
+@pytest.mark.parametrize("case", ROWS, ids=[c[0] for c in ROWS])
+def test_a_tile_of_a_token_block_per_workgroup(tw, case):
+    """tw_gemm_t where a workgroup has one tile: every element, plain and fused, the same bits as tw_gemm, nothing written
+    outside Ct, and activations that no tile keeps do not matter, whatever they are."""
+    name, M, K, N, G, dtype, keep, cp = case
+    w = W.generate(W.small_spec("rows_" + name, M=M, K=K, N=N, G=G, dtype=dtype, col_prune=cp, keep=keep, seed_offset=6600 + sum(map(ord, name))))
+    wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count, transposed=True)
+    _say(f"tile per workgroup {name} M={M} K={K} N={N} G={G} {dtype} T={wt.info['T']} {pl}")
+    assert pl["tile_items"] == -(-M // (128 if G == 128 else 256)) * wt.info["T"]
+    C = tw.tw_gemm(wt, _device_A(tw, w.A, dtype))
+    At = torch.full((K, (M + 7) // 8 * 8 + 8), float("inf"), dtype=C.dtype, device="cuda:0")[:, :M]
+    At.copy_(tw.bits_to_tensor(w.A, dtype).t())
+    At[torch.as_tensor(np.flatnonzero(~w.mask.any(axis=1)), device="cuda:0")] = float("nan")
+    bbits = _bias_bits(N, dtype, 23)
+    outs = [torch.full((N, (M + 7) // 8 * 8 + 64), float("nan"), dtype=C.dtype, device="cuda:0") for _ in range(2)]
+    tw.tw_gemm_t(wt, At, outs[0][:, :M])
+    tw.tw_gemm_t_bias_act(wt, At, tw.bits_to_tensor(bbits, dtype), "gelu", outs[1][:, :M])
+    torch.cuda.synchronize()
+    _compare_whole(outs[0][:, :M], w.A, w.B, w.mask, dtype, transposed=True, what=name)
+    assert torch.equal(outs[0][:, :M].T.contiguous(), C), "the two boundaries differ in some bit"
+    _compare_whole(outs[1][:, :M], w.A, w.B, w.mask, dtype, transposed=True, what=name + " fused",
+                   post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "gelu"))
+    for o in outs:
+        assert bool(torch.isnan(o[:, M:].float()).all().item()), "wrote outside Ct"
+
+
 # name, M, K, N, G, type, keep, tiles of a workgroup at most, waves to a tile of the product without GELU: 8, 4 and 2
 # waves; fewer steps than waves; the longest resident K in several batches of A; one row; a last row block of one row; K that
 # is no multiple of 8.  Wide tiles of few steps take a wave each, and a team with GELU.
