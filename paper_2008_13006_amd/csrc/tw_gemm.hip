@@ -2129,6 +2129,128 @@ __global__ __launch_bounds__(256, kRowsStages == 4 ? 4 : 2) void tw_rows_kernel(
     store_tile_t<DT, 2, CB, FUSED, true>(p, d, acc, smem + wave * kRowsStoreArea, dpos, m0 + wt * 64, lane, 0, CB, nullptr, wc == 0);
 }
 
+// ---- row-major boundary, K streamed, at most four tiles of a row block per workgroup ----
+// As MODE 2 above: four waves multiply, four bring in chunks of 384 columns of 64 rows, K-major and double-buffered, one barrier per
+// chunk.  The loading waves hold nothing in registers: direct loads bring windows of 64 columns into a ring of kWindows
+// windows as they lie in memory, always that many on their way, into the next item too; a wave turns the 16 rows of a window that it
+// has asked for itself (no barrier there) with transposing LDS reads, 4 rows x 16 columns a quarter wave, and writes the four
+// rows of a column in one piece.  MODE 2 keeps a chunk in registers and writes every value by itself (96 2-byte
+// writes of a wave for a chunk, 24 8-byte ones here).
+// The barriers are the instruction itself: __syncthreads() would also wait for the packed weights asked for ahead.
+//
+// 16-byte piece c of row r of a window lies at slot c ^ (r % 8) of the row.
+constexpr int kStreamChunk = TW_K_STREAM_CHUNK, kWindow = 64, kWindows = 4, kStreamLoaders = 4, kStreamTiles = 4;
+constexpr unsigned kWindowBytes = 64 * kWindow * 2;
+constexpr unsigned kStreamRange = 0x80000000u;
+static_assert(kStreamChunk % kWindow == 0, "whole windows");
+
+template <int DT, int NCB, bool FUSED>
+__global__ __launch_bounds__(kThreads) void tw_stream_kernel(const TwGemmParams p) {
+    constexpr unsigned PITCH = at_pitch_of<2>();
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uni(tid >> 6);
+    const int grid = (int)gridDim.x;
+
+    if (wave >= kStreamTiles) {
+        const int lw = wave - kStreamTiles;                  // rows 16 lw .. of a block
+        unsigned char* const ring = smem + p.urow_off + lw * 2048;
+        const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
+        const unsigned lda2 = 2u * (unsigned)p.lda;
+        if (lw == 0) {                                       // what padded slots read: row k_chunk of both buffers
+            if (lane < 32) *(unsigned*)(smem + (unsigned)kStreamChunk * PITCH + lane * 4) = 0u;
+            else *(unsigned*)(smem + p.abuf_bytes + (unsigned)kStreamChunk * PITCH + (lane - 32) * 4) = 0u;
+        }
+        // the request cursor: window cw of chunk cc of item ci, into slot cq of the ring; windows on their way
+        int ci = (int)blockIdx.x, cc = 0, cw = 0, cq = 0, ahead = 0;
+        const int frow = 16 * lw + (lane >> 3), piece = (lane & 7) ^ (lane >> 3);
+        const unsigned foff = (unsigned)frow * lda2 + (unsigned)piece * 16u;
+        auto issue = [&] {
+            if (ci >= p.n_items) return;
+            const int set = ci / p.n_mblocks, row0 = (ci - set * p.n_mblocks) * p.row_step, col0 = cc * kStreamChunk + cw * kWindow;
+            const uint64_t base = (uint64_t)(p.A + (long)row0 * p.lda + col0);
+            const tw_u32x4 da{(unsigned)uni((int)(unsigned)base), (unsigned)uni((int)(unsigned)(base >> 32)) & 0xFFFFu, kStreamRange, 0x00020000u};
+            const int rows = block_end(p, row0) - row0;
+            const bool col = col0 + piece * 8 < p.K;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const unsigned off = col && frow + 8 * i < rows ? foff + (unsigned)(8 * i) * lda2 : kStreamRange;
+                const unsigned to = lds0 + (unsigned)cq * kWindowBytes + (unsigned)i * 1024u;
+                if (p.n_seg == 1) tw_load_lds<true>(da, off, to);    // (streaming where nobody else reads these rows: see load_a16)
+                else tw_load_lds<false>(da, off, to);
+            }
+            cq = (cq + 1) & (kWindows - 1);
+            ++ahead;
+            if (++cw == kStreamChunk / kWindow || col0 + kWindow >= p.K) {
+                cw = 0;
+                if (++cc == p.n_chunks) { cc = 0; ci += grid; }
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < kWindows; ++i) issue();
+        const int grp = lane >> 4, j = lane & 15, trow = 4 * grp + (j >> 2);
+        const unsigned from = (unsigned)(trow * 128 + ((((j & 3) >> 1) ^ (trow & 7)) << 4) + (j & 1) * 8);
+        const unsigned to = (unsigned)j * PITCH + (unsigned)(16 * lw + 4 * grp) * 2u;
+        int q = 0;
+        unsigned buf = 0;
+        for (int item = (int)blockIdx.x; item < p.n_items; item += grid) {
+            for (int c = 0; c < p.n_chunks; ++c) {
+                const int width = p.K - c * kStreamChunk, windows = width >= kStreamChunk ? kStreamChunk / kWindow : (width + kWindow - 1) / kWindow;
+                for (int w = 0; w < windows; ++w) {
+                    if (ahead == kWindows) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (kWindows - 1)) : "memory");
+                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    const unsigned char* src = ring + (unsigned)q * kWindowBytes;
+                    unsigned char* dst = smem + buf + to + (unsigned)(w * kWindow) * PITCH;
+                    tw_i16x4 v[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[t] = tw_lds_read_tr(src + (from ^ (unsigned)(t << 5)));
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) *(tw_u32x2*)(dst + t * 16 * PITCH) = __builtin_bit_cast(tw_u32x2, v[t]);
+                    q = (q + 1) & (kWindows - 1);
+                    --ahead;
+                    issue();                                 // (the reads of this slot are over: their values have been written)
+                }
+                tw_lds_wait<63>();                           // the chunk is there
+                buf = buf == 0 ? p.abuf_bytes : 0u;
+            }
+        }
+        return;
+    }
+
+    unsigned char* stage = smem + p.stage_off + wave * kStageBytes;
+    unsigned buf = 0;
+    for (int item = (int)blockIdx.x; item < p.n_items; item += grid) {
+        const int set = item / p.n_mblocks, row0 = (item - set * p.n_mblocks) * p.row_step;
+        const int ti = set * p.tiles_per_set + wave;
+        const bool active = wave < p.tiles_per_set && ti < p.T;              // wave-uniform
+        const TileU d = fetch_tile(p, active ? ti : 0);
+        const int* sp = (const int*)(p.blob + p.off_step_ptr) + d.step_ptr;
+        unsigned dpos[NCB];
+        {
+            const unsigned* dp = (const unsigned*)(p.blob + p.off_dpos) + ((long)d.tile * 32 + (lane & 31)) * NCB;
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) dpos[cb] = dp[cb];
+        }
+        tw_f32x16 acc[2][NCB];
+        zero_acc<2, NCB>(acc);
+        const unsigned char* gt = p.blob + p.off_goff + (long)d.first_step * 32;
+        const unsigned char* bt = p.blob + p.off_bvals + (long)d.first_step * NCB * 1024;
+        int s0 = 0, s1 = fetch_int(sp, 1), s2 = fetch_int(sp, p.n_chunks < 2 ? p.n_chunks : 2);
+        for (int c = 0; c < p.n_chunks; ++c) {
+            const bool steps = active && s0 < s1;
+            StepRegs<NCB> rg;
+            if (steps) prefetch_first_steps<NCB>(rg, gt, bt, s0, s1, lane);
+            tw_lds_wait<63>();
+            if (steps) run_steps<DT, 2, NCB>(acc, rg, smem + buf, PITCH, gt, bt, s0, s1, lane);
+            s0 = s1;
+            s1 = s2;
+            s2 = fetch_int(sp, c + 3 < p.n_chunks ? c + 3 : p.n_chunks);
+            buf = buf == 0 ? p.abuf_bytes : 0u;
+        }
+        if (active) store_tile<DT, 2, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane);
+    }
+}
+
 }  // namespace
 
 // ---- kernel tables
@@ -2142,6 +2264,7 @@ template <int DT, bool FUSED, bool EW> const void* pick_mode(int mode, int ms, i
 template <int DT, bool FUSED, bool EW> const void* pick_mode_t(int mode, int ms, int ncb, bool nta);   // transposed boundary
 template <int DT, bool FUSED> const void* pick_reduce(int ncb, bool transposed);               // second kernel of split K
 template <int DT, bool FUSED> const void* pick_team(int ncb, bool transposed);                 // teams of waves per tile
+template <int DT, bool FUSED> const void* pick_stream(int ncb);                     // K streamed, row-major
 template <int DT, bool FUSED> const void* pick_rows(int ncb, int stages);                                  // a tile of a token block per workgroup
 }  // namespace tw_parts
 
@@ -2191,6 +2314,15 @@ const void* pick_reduce(int ncb, bool transposed) {
     }
 }
 template <int DT, bool FUSED>
+const void* pick_stream(int ncb) {
+    switch (ncb) {
+        case 1: return (const void*)tw_stream_kernel<DT, 1, FUSED>;
+        case 2: return (const void*)tw_stream_kernel<DT, 2, FUSED>;
+        case 4: return (const void*)tw_stream_kernel<DT, 4, FUSED>;
+        default: return nullptr;
+    }
+}
+template <int DT, bool FUSED>
 const void* pick_rows(int ncb, int stages) {
     switch (ncb) {
         case 1: return stages == 4 ? (const void*)tw_rows_kernel<DT, 1, FUSED, 4> : (const void*)tw_rows_kernel<DT, 1, FUSED, 8>;
@@ -2218,7 +2350,8 @@ const void* pick_team(int ncb, bool transposed) {
 #define TW_TABLES_REDUCE(KW, DT, FUSED)                                           \
     KW template const void* tw_parts::pick_reduce<DT, FUSED>(int, bool);          \
     KW template const void* tw_parts::pick_team<DT, FUSED>(int, bool);            \
-    KW template const void* tw_parts::pick_rows<DT, FUSED>(int, int);
+    KW template const void* tw_parts::pick_rows<DT, FUSED>(int, int);            \
+    KW template const void* tw_parts::pick_stream<DT, FUSED>(int);
 #define TW_TABLES_ALL(KW, DT, FUSED) TW_TABLES_EW(KW, DT, FUSED, false) TW_TABLES_EW(KW, DT, FUSED, true) TW_TABLES_REDUCE(KW, DT, FUSED)
 #if TW_PART == 0
 TW_TABLES_ALL(extern, TW_F16, false) TW_TABLES_ALL(extern, TW_F16, true) TW_TABLES_ALL(extern, TW_BF16, false) TW_TABLES_ALL(extern, TW_BF16, true)
@@ -2466,6 +2599,7 @@ struct Plan {
     int rows_group;                 // tw_rows_kernel: token blocks walked together, 0: another kernel runs
     int rows_stages;                // and the depth of its ring
     unsigned rows_lds;              // and its on-chip memory per workgroup
+    int stream_items;               // tw_stream_kernel: its items, 0: another kernel runs
     size_t partial_bytes;           // workspace the parts' fp32 results take, behind the counters
 };
 
@@ -2751,6 +2885,13 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
     pl.rows_group = (int)(group < blocks ? group : blocks);
 }
 
+// Whether tw_gemm runs tw_stream_kernel instead of the plan's kernel (pl.stream_items).
+void plan_stream(const TwHeader* h, int M, long lda, Plan& pl) {
+    pl.stream_items = 0;
+    if (pl.mode != 2 || pl.n_parts > 1 || h->k_chunk != kStreamChunk || h->ew_nnz > 0 || lda >= (1 << 23)) return;
+    pl.stream_items = pl.n_items;
+}
+
 // the kernel for (dtype, mode, MS, NCB, fused epilogue): a host-side address for hipLaunchKernel and hipFuncSetAttribute
 template <bool EW>
 const void* pick_kernel_t_of(int dt, int mode, int ms, int ncb, bool fused, bool nta) {
@@ -2775,6 +2916,11 @@ const void* pick_team_kernel(int dt, int ncb, bool fused, bool transposed) {
     using namespace tw_parts;
     if (fused) return dt == TW_F16 ? pick_team<TW_F16, true>(ncb, transposed) : pick_team<TW_BF16, true>(ncb, transposed);
     return dt == TW_F16 ? pick_team<TW_F16, false>(ncb, transposed) : pick_team<TW_BF16, false>(ncb, transposed);
+}
+const void* pick_stream_kernel(int dt, int ncb, bool fused) {
+    using namespace tw_parts;
+    if (fused) return dt == TW_F16 ? pick_stream<TW_F16, true>(ncb) : pick_stream<TW_BF16, true>(ncb);
+    return dt == TW_F16 ? pick_stream<TW_F16, false>(ncb) : pick_stream<TW_BF16, false>(ncb);
 }
 const void* pick_rows_kernel(int dt, int ncb, bool fused, int stages) {
     using namespace tw_parts;
@@ -2807,7 +2953,7 @@ int device_cus(int dev) {
 }
 
 // The dynamic-LDS limit of a kernel is raised to the hardware maximum once per (device, kernel).
-constexpr int kMaxKernels = 512;
+constexpr int kMaxKernels = 544;
 std::atomic<unsigned> g_lds_set[kMaxDevices][kMaxKernels];
 
 int ensure_lds(int dev, int kernel_id, const void* fn) {
@@ -2966,6 +3112,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     Plan pl;
     int rc = make_plan(h, M, n_cu, pl, false, ws_bytes, act == TW_ACT_GELU);
     if (rc) return rc;
+    plan_stream(h, M, lda, pl);
     const bool split = pl.n_parts > 1;
     const bool fused_epilogue = bias != nullptr || act != TW_ACT_NONE;
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's
@@ -3010,6 +3157,14 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     p.partials = (float*)((unsigned char*)workspace + 256);
     const int grid = pl.n_items < n_cu ? pl.n_items : n_cu;
     void* args[] = {(void*)&p};
+    if (pl.stream_items > 0) {
+        const void* fs = pick_stream_kernel(h->dtype, h->ncb, fused);
+        if (!fs) return TW_ERR_UNSUPPORTED;
+        rc = ensure_lds(dev, 492 + (h->dtype == TW_F16 ? 0 : 6) + (fused ? 3 : 0) + (h->ncb >> 1), fs);
+        if (rc) return rc;
+        p.urow_off = p.stage_off + kStreamTiles * kStageBytes;    // the ring
+        return hipLaunchKernel(fs, dim3(grid), dim3(kThreads), args, p.urow_off + kWindows * kWindowBytes, stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
+    }
     if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, pl.lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
     if (split) {
         const long units = (long)pl.n_mblocks * h->T * 8;                 // a wave per pass of a tile
