@@ -381,6 +381,41 @@ def test_a_tile_of_a_token_block_per_workgroup(tw, case):
         assert bool(torch.isnan(o[:, M:].float()).all().item()), "wrote outside Ct"
 
 
+# M, K, N, G, type, keep: four multiplying and four loading waves.  A last chunk of one column, of less than a window, of several windows
+# and a part; K a multiple of eight and not; one to four tiles a workgroup, one set of tiles and several; chunks in which a tile keeps
+# nothing; more and fewer items than compute units, last blocks of one row and of a part; row blocks lower than 64 rows.
+STREAM = [(16385, 1537, 300, 128, "f16", ("upow", 0.05, 0.6)), (17000, 1544, 100, 32, "bf16", ("upow", 0.001, 0.4)), (8513, 2310, 190, 64, "f16", ("upow", 0.1, 0.9)),
+          (4127, 1990, 868, 128, "bf16", ("upow", 0.002, 0.5)), (33001, 1600, 250, 64, "f16", ("const", 0.3)), (16384, 2304, 128, 128, "bf16", ("const", 0.4))]
+
+
+@pytest.mark.parametrize("case", STREAM, ids=lambda c: "x".join(map(str, c[:4])))
+def test_streamed_rows_are_turned_in_lds(tw, case):
+    """tw_gemm with a streamed K and few tiles: every element, plain and fused, the bits of tw_gemm_t, nothing written beside C, and
+    activations that no tile keeps (and what lies behind a row's end) do not matter, whatever they are."""
+    M, K, N, G, dtype, keep = case
+    w = W.generate(W.small_spec("stream", M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.05, keep=keep, seed_offset=5500 + M + K))
+    wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
+    _say(f"streamed rows M={M} K={K} N={N} G={G} {dtype} T={wt.info['T']} {pl}")
+    assert pl["mode"] == 2 and pl["k_parts"] == 1
+    A = torch.full((M, (K + 7) // 8 * 8 + 8), float("inf"), dtype=wt.torch_dtype, device="cuda:0")[:, :K]
+    A.copy_(tw.bits_to_tensor(w.A, dtype))
+    A[:, torch.as_tensor(np.flatnonzero(~w.mask.any(axis=1)), device="cuda:0")] = float("nan")
+    bbits = _bias_bits(N, dtype, 29)
+    outs = [torch.full((M, N + 5), float("nan"), dtype=A.dtype, device="cuda:0") for _ in range(2)]
+    tw.tw_gemm(wt, A, outs[0][:, :N])
+    tw.tw_gemm_bias_act(wt, A, tw.bits_to_tensor(bbits, dtype), "relu", outs[1][:, :N])
+    Ct = tw.tw_gemm_t(wt, _device_At(tw, w.A, dtype))
+    torch.cuda.synchronize()
+    _compare_whole(outs[0][:, :N], w.A, w.B, w.mask, dtype, what="streamed rows")
+    assert torch.equal(Ct.T.contiguous(), outs[0][:, :N].contiguous()), "the two boundaries differ in some bit"
+    _compare_whole(outs[1][:, :N], w.A, w.B, w.mask, dtype, what="streamed rows, fused",
+                   post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "relu"))
+    for o in outs:
+        assert bool(torch.isnan(o[:, N:].float()).all().item()), "wrote beside C"
+    assert wt.workspace.view(torch.int32)[:4].cpu().tolist() == [0, 0, 0, 0]
+
+
 # name, M, K, N, G, type, keep, tiles of a workgroup at most, waves to a tile of the product without GELU: 8, 4 and 2
 # waves; fewer steps than waves; the longest resident K in several batches of A; one row; a last row block of one row; K that
 # is no multiple of 8.  Wide tiles of few steps take a wave each, and a team with GELU.
