@@ -5,6 +5,7 @@ dominates, fp32 accumulation adds ~1e-6.  On top of that norm-wise bound every e
 its own bound (one rounding of the element plus a small share of the largest one), so that a single
 wrong small element cannot hide behind a large one.  Integer-valued inputs make every product and
 sum exact, so those cases are compared bit for bit, once per kernel mode and boundary."""
+import math
 import sys
 
 import numpy as np
@@ -379,6 +380,24 @@ def test_a_tile_of_a_token_block_per_workgroup(tw, case):
                    post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "gelu"))
     for o in outs:
         assert bool(torch.isnan(o[:, M:].float()).all().item()), "wrote outside Ct"
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_gelu_of_every_value(tw, dtype):
+    """GELU alone, of all finite values of the type: a weight without surviving columns gives act(bias).  Bound: the result's
+    rounding (half a unit in the last place, the type's smallest step below its normal range), the epilogue's 3.3e-7 and 5e-7 of the value (fp32)."""
+    bits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    bits = bits[np.isfinite(W.bits_to_f32(bits, dtype))]
+    N = bits.size
+    blob = tw.tw_pack(np.zeros((8, N), np.uint16), np.zeros((8, N), np.uint8), 32, dtype)
+    wt = tw.TwWeight(blob)
+    A = torch.zeros((1, 8), dtype=wt.torch_dtype, device="cuda:0")
+    got = _to_f64(tw.tw_gemm_bias_act(wt, A, tw.bits_to_tensor(bits, dtype), "gelu"))[0]
+    x = W.bits_to_f32(bits, dtype).astype(np.float64)
+    ref = np.array([v * 0.5 * math.erfc(-v / math.sqrt(2.0)) for v in x])
+    step = 2.0 ** -24 if dtype == "f16" else 0.0
+    bad = np.abs(got - ref) > ULP[dtype] * np.abs(ref) + step + 3.3e-7 + 5e-7 * np.abs(ref)
+    assert not bad.any(), (x[bad][:5], got[bad][:5], ref[bad][:5])
 
 
 # M, K, N, G, type, keep: four multiplying and four loading waves.  A last chunk of one column, of less than a window, of several windows
