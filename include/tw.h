@@ -160,7 +160,8 @@ typedef struct tw_plan_t {
     int32_t n_sets;          /* mode 0: workgroups that share the tiles of a row block; else sets of tiles */
     int32_t n_items;         /* work items = n_row_blocks * n_sets * k_parts */
     int32_t grid;            /* workgroups launched: min(n_items, n_cu), each pulls items until none is left */
-    uint32_t lds_bytes;      /* on-chip memory per workgroup */
+    uint32_t lds_bytes;      /* on-chip memory per workgroup (tw_gemm with mode 2: of the transposed kernel's layout without its row
+                                lists; its own kernel takes 155 KB whatever the weight) */
     int32_t row_lists;       /* tw_gemm_t, mode 2: the loading waves read only the K rows that the tiles keep */
     int32_t k_parts;         /* streamed K, few row blocks: the K chunks are split into this many parts, each a work item
                                 of its own (n_items = n_row_blocks * n_sets * k_parts) whose fp32 results go to the

@@ -423,6 +423,14 @@ constexpr int kWinCols = kWinLines * kLineCols;     // 256
 constexpr int kSpareOff = kWinCols * 8;             // spare slots behind the window of a plane
 constexpr int kPlaneBytes = kWinCols * 8 + 32 * 8 + 32;
 constexpr unsigned kStageBytes = 2 * kPlaneBytes;   // per wave
+// Windows of kNarrowLines lines, where LDS has no room for more beside 64 rows of A (K from about 910 to 1040).
+// (32 rows of A stream the packed weights twice as often.  Before -> now: 4321 x 1000 -> 1234 (G = 32) 27.1 -> 22.5 us, 14528 x 1024 -> 2188
+// (G = 32) 75 -> 50, 10752 x 960 -> 3328 with GELU 82 -> 60, 31710 x 1019 -> 1472 with GELU 106 -> 90.  A span wider than the window
+// takes several, which costs the wave its staging again.)
+constexpr int kNarrowLines = 2;
+template <int WL> constexpr int plane_bytes() { return WL * kLineCols * 8 + 32 * 8 + 32; }
+static_assert(plane_bytes<kWinLines>() == kPlaneBytes && plane_bytes<kNarrowLines>() % 16 == 0 && (plane_bytes<kNarrowLines>() / 4) % 16 == 8, "plane skew");
+constexpr unsigned kNarrowStageBytes = 2 * plane_bytes<kNarrowLines>();
 static_assert(kPlaneBytes % 16 == 0 && (kPlaneBytes / 4) % 16 == 8, "plane skew");
 
 __device__ __forceinline__ void tw_compiler_fence() { asm volatile("" ::: "memory"); }
@@ -525,7 +533,7 @@ __device__ __forceinline__ void apply_bias_act4(tw_f32x4 (&v)[NV], const float (
 // FUSED: the kernel variant with the fused epilogue (a bias and / or an activation); the plain variant
 // carries none of its code.  PART: a wave that stores a part of the tile; bias and activation have been applied (pruned
 // columns inside the span still take theirs here).
-template <int DT, int MS, int NCB, bool FUSED, bool PART = false>
+template <int DT, int MS, int NCB, bool FUSED, bool PART = false, int WL = kWinLines>
 __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d, tw_f32x16 (&acc)[MS][NCB],
                                            unsigned char* stage, const unsigned (&dpos)[NCB], int row0, int lane_in,
                                            unsigned short* xbuf = nullptr,
@@ -533,6 +541,7 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
                                            int pass0 = 0, int pass1 = 4 * MS) {
     // (pass0, pass1: the passes to run, each eight rows of the block; everything by default.  The second kernel
     // of a split-K product gives a wave one pass of a tile.)
+    constexpr int kCols = WL * kLineCols, kSpare = kCols * 8, kPlane = plane_bytes<WL>();
     const int lane = fresh(lane_in);
     constexpr bool fused = FUSED;
     // Residual-only columns of a TEW blob inside this tile's span (Sec. IV-A "Hybrid Pattern": weights restored in a
@@ -557,19 +566,19 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
     const unsigned shift = (unsigned)((S & ~7) - W0);       // dpos counts from S & ~7
     constexpr int NP = 4 * MS;
     const int rows_left = block_end(p, row0) - (row0 + orow);   // pass P stores this lane's row iff 8P < rows_left
-    for (int win0 = W0; win0 < E; win0 += kWinCols) {       // one window unless the span is very wide
+    for (int win0 = W0; win0 < E; win0 += kCols) {       // one window unless the span is very wide
         const int left = E - win0;
-        const int nl = left >= kWinCols ? kWinLines : (left + kLineCols - 1) / kLineCols;
+        const int nl = left >= kCols ? WL : (left + kLineCols - 1) / kLineCols;
         unsigned char* wpos[NCB];
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
             const unsigned rel = dpos[cb] + shift - (unsigned)(win0 - W0);   // wraps for columns left of the window
-            wpos[cb] = stage + h * kPlaneBytes + (rel < (unsigned)kWinCols ? rel * 8u : (unsigned)(kSpareOff + n * 8));
+            wpos[cb] = stage + h * kPlane + (rel < (unsigned)kCols ? rel * 8u : (unsigned)(kSpare + n * 8));
         }
-        const unsigned char* rpos = stage + in_rq * kPlaneBytes + (8 * in_piece + in_e) * 8;
-        bool okl[kWinLines], whole[kWinLines];
+        const unsigned char* rpos = stage + in_rq * kPlane + (8 * in_piece + in_e) * 8;
+        bool okl[WL], whole[WL];
 #pragma unroll
-        for (int l = 0; l < kWinLines; ++l) {
+        for (int l = 0; l < WL; ++l) {
             const int col = win0 + l * kLineCols + piece * 8;
             okl[l] = l < nl && col >= S && col + 8 <= E;
             // the span covers this line from end to end (wave-uniform): nobody else writes into it
@@ -579,11 +588,11 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
         // partial groups at the two ends of the span, if they lie in this window (window-relative index)
         int g_first = -1, g_last = -1;
         if ((S & 7) != 0 && win0 == W0) g_first = (S - win0) >> 3;
-        if ((E & 7) != 0 && left <= kWinCols) g_last = (E - 1 - win0) >> 3;
+        if ((E & 7) != 0 && left <= kCols) g_last = (E - 1 - win0) >> 3;
         const int colF = win0 + g_first * 8 + tg, colL = win0 + g_last * 8 + tg;   // this lane's element
         const bool inF = g_first >= 0 && colF >= S && colF < E;
         const bool inL = g_last >= 0 && colL >= S && colL < E;
-        const unsigned char* ragbase = stage + (trow >> 2) * kPlaneBytes + (trow & 3) * 2;
+        const unsigned char* ragbase = stage + (trow >> 2) * kPlane + (trow & 3) * 2;
         const unsigned char* ragF = ragbase + ((g_first < 0 ? 0 : g_first) * 8 + tg) * 8;
         const unsigned char* ragL = ragbase + ((g_last < 0 ? 0 : g_last) * 8 + tg) * 8;
         unsigned short* rptr = p.C + (long)(row0 + trow) * p.ldc;
@@ -597,7 +606,7 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
             const int j = 8 * g + (lane >> 3);
             if (j < nx) {
                 const unsigned rel = (unsigned)(xcols[g] - win0);
-                if (rel < (unsigned)kWinCols) xpos[g] = stage + ((lane >> 2) & 1) * kPlaneBytes + rel * 8u + (lane & 3) * 2;
+                if (rel < (unsigned)kCols) xpos[g] = stage + ((lane >> 2) & 1) * kPlane + rel * 8u + (lane & 3) * 2;
             }
         }
         tw_u32x4 xq[TW_XC_INLINE / 8];                       // this lane's row of its columns, all passes
@@ -630,18 +639,18 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
 #pragma unroll
             for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-                for (int i = 0; i < kWinCols * 8 / 1024; ++i)
-                    *(tw_u32x4*)(stage + pl * kPlaneBytes + i * 1024 + lane * 16) = tw_u32x4{0u, 0u, 0u, 0u};
+                for (int i = 0; i < kCols * 8 / 1024; ++i)
+                    *(tw_u32x4*)(stage + pl * kPlane + i * 1024 + lane * 16) = tw_u32x4{0u, 0u, 0u, 0u};
         } else {
 #pragma unroll
-            for (int l = 0; l < kWinLines; ++l) {
+            for (int l = 0; l < WL; ++l) {
                 const int c = win0 + l * kLineCols + lane;
                 float b = eb.fill[l];
                 if (win0 != W0) b = (p.bias != nullptr && c >= S && c < E) ? tw_to_f32<DT>(p.bias[c]) : 0.f;   // later windows: read here
                 const unsigned hv = (c >= S && c < E) ? (unsigned)tw_cvt<DT>(tw_activate(b, p.act)) : 0u;
                 const tw_u32x2 v{hv | (hv << 16), hv | (hv << 16)};
                 *(tw_u32x2*)(stage + (l * kLineCols + lane) * 8) = v;
-                *(tw_u32x2*)(stage + kPlaneBytes + (l * kLineCols + lane) * 8) = v;
+                *(tw_u32x2*)(stage + kPlane + (l * kLineCols + lane) * 8) = v;
             }
         }
         tw_compiler_fence();
@@ -652,9 +661,9 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
 #pragma unroll
         for (int P = 0; P < NP; ++P) {
             if (P < pass0 || P >= pass1) continue;               // wave-uniform
-            tw_i16x4 lo[kWinLines], hi[kWinLines];
+            tw_i16x4 lo[WL], hi[WL];
 #pragma unroll
-            for (int l = 0; l < kWinLines; ++l) {
+            for (int l = 0; l < WL; ++l) {
                 lo[l] = tw_lds_read_tr(rpos + l * (kLineCols * 8));
                 hi[l] = tw_lds_read_tr(rpos + l * (kLineCols * 8) + 32);
             }
@@ -664,7 +673,7 @@ __device__ __forceinline__ void store_tile(const TwGemmParams& p, const TileU& d
             if (P + 1 < NP && P + 1 < pass1) write_pass(P + 1);
             tw_compiler_fence();
 #pragma unroll
-            for (int l = 0; l < kWinLines; ++l) {
+            for (int l = 0; l < WL; ++l) {
                 if (okl[l] && 8 * P < rows_left) {
                     const tw_u32x2 a = __builtin_bit_cast(tw_u32x2, lo[l]), b = __builtin_bit_cast(tw_u32x2, hi[l]);
                     if (whole[l]) tw_store16_stream(cptr + (long)(8 * P) * p.ldc + l * kLineCols, tw_u32x4{a.x, a.y, b.x, b.y});
@@ -1262,7 +1271,8 @@ __device__ __forceinline__ void dump_partial(float* dst, const tw_f32x16 (&acc)[
 
 // EW: the variant for TEW blobs.  The code of the element-wise residual costs the kernels without it 1 to 2.5 %
 // (registers: the widest variants sit at the limit of 256), so blobs without a residual run kernels without it.
-template <int DT, int MS, int NCB, int MODE, bool FUSED, bool TRANS, bool NTA = true, bool EW = false>
+// WL: lines of the epilogue's staging windows.
+template <int DT, int MS, int NCB, int MODE, bool FUSED, bool TRANS, bool NTA = true, bool EW = false, int WL = kWinLines>
 __global__ __launch_bounds__(kThreads) void tw_gemm_kernel(const TwGemmParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const bool has_ew = EW && p.has_ew != 0;
@@ -1271,7 +1281,7 @@ __global__ __launch_bounds__(kThreads) void tw_gemm_kernel(const TwGemmParams p)
     constexpr int BM = 32 * MSB;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = uni(tid >> 6);
-    unsigned char* stage = smem + p.stage_off + wave * kStageBytes;
+    unsigned char* stage = smem + p.stage_off + wave * (2 * plane_bytes<WL>());
     volatile int* misc = (volatile int*)(smem + p.misc_off);
     const int* step_ptr = (const int*)(p.blob + p.off_step_ptr);
 
@@ -1346,7 +1356,7 @@ __global__ __launch_bounds__(kThreads) void tw_gemm_kernel(const TwGemmParams p)
                                            p.blob + p.off_bvals + (long)d.first_step * NCB * 1024, 0, d.nsteps, lane);
                 if (has_ew) add_ew_residual<DT, MS, NCB>(p, d.tile, 0, acc, smem, at_pitch_of<MS>(), lane);
                 if constexpr (TRANS) store_tile_t<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, 0, NCB, xbuf);
-                else store_tile<DT, MS, NCB, FUSED>(p, d, acc, stage, dpos, row0, lane, xbuf, xcols);
+                else store_tile<DT, MS, NCB, FUSED, false, WL>(p, d, acc, stage, dpos, row0, lane, xbuf, xcols);
             }
             __syncthreads();  // everyone is done with the LDS copy of A and with misc[]
         } else if constexpr (MODE == 2) {
@@ -2270,6 +2280,7 @@ template <int DT, bool FUSED, bool EW> const void* pick_mode(int mode, int ms, i
 template <int DT, bool FUSED, bool EW> const void* pick_mode_t(int mode, int ms, int ncb, bool nta);   // transposed boundary
 template <int DT, bool FUSED> const void* pick_reduce(int ncb, bool transposed);               // second kernel of split K
 template <int DT, bool FUSED> const void* pick_team(int ncb, bool transposed);                 // teams of waves per tile
+template <int DT, bool FUSED> const void* pick_narrow(int ncb);                                // K resident, 64 rows, narrow staging windows
 template <int DT, bool FUSED> const void* pick_stream(int ncb);                     // K streamed, row-major
 template <int DT, bool FUSED> const void* pick_rows(int ncb, int stages);                                  // a tile of a token block per workgroup
 }  // namespace tw_parts
@@ -2320,6 +2331,15 @@ const void* pick_reduce(int ncb, bool transposed) {
     }
 }
 template <int DT, bool FUSED>
+const void* pick_narrow(int ncb) {
+    switch (ncb) {
+        case 1: return (const void*)tw_gemm_kernel<DT, 2, 1, 0, FUSED, false, true, false, kNarrowLines>;
+        case 2: return (const void*)tw_gemm_kernel<DT, 2, 2, 0, FUSED, false, true, false, kNarrowLines>;
+        case 4: return (const void*)tw_gemm_kernel<DT, 2, 4, 0, FUSED, false, true, false, kNarrowLines>;
+        default: return nullptr;
+    }
+}
+template <int DT, bool FUSED>
 const void* pick_stream(int ncb) {
     switch (ncb) {
         case 1: return (const void*)tw_stream_kernel<DT, 1, FUSED>;
@@ -2357,6 +2377,7 @@ const void* pick_team(int ncb, bool transposed) {
     KW template const void* tw_parts::pick_reduce<DT, FUSED>(int, bool);          \
     KW template const void* tw_parts::pick_team<DT, FUSED>(int, bool);            \
     KW template const void* tw_parts::pick_rows<DT, FUSED>(int, int);            \
+    KW template const void* tw_parts::pick_narrow<DT, FUSED>(int);                \
     KW template const void* tw_parts::pick_stream<DT, FUSED>(int);
 #define TW_TABLES_ALL(KW, DT, FUSED) TW_TABLES_EW(KW, DT, FUSED, false) TW_TABLES_EW(KW, DT, FUSED, true) TW_TABLES_REDUCE(KW, DT, FUSED)
 #if TW_PART == 0
@@ -2605,6 +2626,7 @@ struct Plan {
     int rows_group;                 // tw_rows_kernel: token blocks walked together, 0: another kernel runs
     int rows_stages;                // and the depth of its ring
     unsigned rows_lds;              // and its on-chip memory per workgroup
+    bool narrow;                    // K resident, 64 rows: narrow staging windows
     int stream_items;               // tw_stream_kernel: its items, 0: another kernel runs
     size_t partial_bytes;           // workspace the parts' fp32 results take, behind the counters
 };
@@ -2633,6 +2655,13 @@ unsigned at_bytes(int msb, int k_chunk) {
 unsigned lds_need(int msb, int k_chunk, int buffers) {
     return buffers * at_bytes(msb, k_chunk) + kWaves * kStageBytes + 16u;
 }
+// steps of the heaviest tile
+int heaviest_steps(const TwHeader* h) {
+    const unsigned char* blob = (const unsigned char*)h;
+    return ((const TwTileDesc*)(blob + h->off_tile_desc))[*(const int32_t*)(blob + h->off_sched_order)].nsteps;
+}
+// 64 rows of a resident K beside narrow staging windows
+unsigned lds_need_narrow(int k) { return at_bytes(2, k) + kWaves * kNarrowStageBytes + 16u; }
 
 // Estimate of an item with K resident, in microseconds: launch and first operands, bringing in 32 * msb rows of A while the
 // whole chip does, and then whichever takes longer: the packed weights of its tiles through the compute unit's vector L1
@@ -2684,10 +2713,7 @@ int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bo
     if (shift == 1) cost += kTwoWavesUs[width];
     if (h->K > 768) cost += kLongUs[width] + (shift == 1 && width == 2 ? 0.9 : 0.0);
     if (gelu) cost -= kTeamGeluUs[width];
-    const unsigned char* blob = (const unsigned char*)h;
-    const int32_t first = *(const int32_t*)(blob + h->off_sched_order);
-    const int heaviest = ((const TwTileDesc*)(blob + h->off_tile_desc))[first].nsteps;
-    return kTeamStepUs[width] * heaviest > cost ? shift : 0;
+    return kTeamStepUs[width] * heaviest_steps(h) > cost ? shift : 0;
 }
 
 int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0,
@@ -2705,7 +2731,15 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     };
     int msb = 2, tpw = kWaves;
     int nmb, nseg;
-    if (lds_need(2, h->k_chunk, buffers) > kLdsLimit) msb = 1;
+    // 64 rows with narrow staging windows (K from about 910 to 1040; the row-major boundary's plain blobs): the packed weights of 64 rows are
+    // streamed once instead of twice.  Not where the heaviest tile has more than kSkew times the mean's steps: it is one wave's, with
+    // 64 rows twice as long (3025 x 1024 -> 1167, skewed, 22.3 us, 19.4 in 32 rows; 8192 x 1024 -> 4096, skewed, 2 % slower), and only for
+    // kNarrowCost less of the estimate, which does not see a wide tile's second window (which is all there is to few wide tiles of few
+    // steps: 49920 x 1035 -> 832, 8 steps a tile, 75.4 us, 72.2 in 32 rows).
+    constexpr double kSkew = 2.5, kNarrowCost = 1.06;
+    const bool narrow = resident && !transposed && h->ew_nnz == 0 && lds_need(2, h->k_chunk, 1) > kLdsLimit && lds_need_narrow(h->k_chunk) <= kLdsLimit &&
+                        (double)heaviest_steps(h) * T <= kSkew * (double)h->total_steps && (h->ncb < 4 || T > kWaves || h->total_steps >= 12L * T);
+    if (lds_need(2, h->k_chunk, buffers) > kLdsLimit && !narrow) msb = 1;
     pl.mode = resident ? 0 : 1;
     if (resident) {
         // 64-row blocks with all tiles when they give every compute unit an item.  With fewer the height of the row blocks
@@ -2717,7 +2751,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
         // 1400 -> 2000 at 3000 37 -> 20; 1000 -> 1234 (G = 32) at 4321 36.5 -> 25.3; transposed 768 -> 2304 at 6000 tokens
         // 35 -> 19.6, 500 -> 4000 (G = 32) at 5000 39 -> 23.0; 768 -> 3072 at 16384 and 17000 as before.
         const long nmb_full = (M + 32L * msb - 1) / (32 * msb);
-        if (nmb_full < n_cu || msb == 1) {
+        if (nmb_full < n_cu || msb == 1 || narrow) {
             // (only shares that give a workgroup fewer tiles than the one before: about 2 sqrt(T) of them)
             double best = 0.0, one_round = 0.0;
             int one_msb = msb, one_segs = 1;
@@ -2728,7 +2762,7 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
                 for (int sg = 1; sg <= most_segs;) {
                     const int tiles = (T + sg - 1) / sg;
                     const long rounds = (blocks * sg + n_cu - 1) / n_cu;
-                    const double cost = rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, gelu), gelu);
+                    const double cost = (narrow && m == 2 ? kNarrowCost : 1.0) * rounds * resident_item_us(h, m, tiles, team_of(h, m, tiles, blocks * sg, n_cu, gelu), gelu);
                     if (best == 0.0 || cost < best) { best = cost; msb = m; segs = sg; }
                     if (rounds == 1 && (one_round == 0.0 || cost < one_round)) { one_round = cost; one_msb = m; one_segs = sg; }
                     if (tiles == 1) break;
@@ -2782,7 +2816,8 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     pl.at_pitch = 64u * msb + 8u;
     pl.abuf_bytes = at_bytes(msb, h->k_chunk);
     pl.stage_off = buffers * pl.abuf_bytes;
-    pl.misc_off = pl.stage_off + kWaves * kStageBytes;
+    pl.narrow = narrow && msb == 2;
+    pl.misc_off = pl.stage_off + kWaves * (pl.narrow ? kNarrowStageBytes : kStageBytes);
     pl.lds_bytes = pl.misc_off + 16u;
     pl.tiles_per_set = resident ? 0 : tpw;
     // Transposed boundary, at most four tiles, streamed: the loading waves read only the K rows the tiles keep,
@@ -2870,8 +2905,7 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
     if (pl.n_parts > 1 || pl.team_shift > 0 || h->ew_nnz > 0 || h->n_chunks > 64) return;
     // (offsets below kRowsRange, products of 24-bit factors)
     if ((unsigned long)h->K * (unsigned long)lda * 2 >= kRowsRange || lda >= (1 << 23) || h->K >= (1 << 24)) return;
-    const unsigned char* blob = (const unsigned char*)h;
-    const int heaviest = ((const TwTileDesc*)(blob + h->off_tile_desc))[*(const int32_t*)(blob + h->off_sched_order)].nsteps;
+    const int heaviest = heaviest_steps(h);
     const int bt = h->ncb == 4 ? rows_bt<4>() : rows_bt<1>();
     const long blocks = ((long)M + bt - 1) / bt, items = blocks * h->T;
     if (items >= 0x7fffffffL) return;
@@ -2924,6 +2958,11 @@ const void* pick_team_kernel(int dt, int ncb, bool fused, bool transposed) {
     using namespace tw_parts;
     if (fused) return dt == TW_F16 ? pick_team<TW_F16, true>(ncb, transposed) : pick_team<TW_BF16, true>(ncb, transposed);
     return dt == TW_F16 ? pick_team<TW_F16, false>(ncb, transposed) : pick_team<TW_BF16, false>(ncb, transposed);
+}
+const void* pick_narrow_kernel(int dt, int ncb, bool fused) {
+    using namespace tw_parts;
+    if (fused) return dt == TW_F16 ? pick_narrow<TW_F16, true>(ncb) : pick_narrow<TW_BF16, true>(ncb);
+    return dt == TW_F16 ? pick_narrow<TW_F16, false>(ncb) : pick_narrow<TW_BF16, false>(ncb);
 }
 const void* pick_stream_kernel(int dt, int ncb, bool fused) {
     using namespace tw_parts;
@@ -3011,10 +3050,6 @@ extern "C" int tw_gemm_plan(const void* blob_host, int M, int n_cu, int transpos
     plan->n_items = pl.n_items;
     plan->grid = pl.n_items < n_cu ? pl.n_items : n_cu;
     plan->lds_bytes = pl.lds_bytes;
-    if (!transposed) {
-        plan_stream(h, M, h->K, pl);
-        if (pl.stream_items > 0) plan->lds_bytes = stream_lds_bytes();
-    }
     plan->row_lists = pl.urow_off != 0;
     plan->k_parts = pl.n_parts;
     plan->team_waves = 1 << pl.team_shift;
@@ -3132,7 +3167,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     const bool nta = pl.mode == 0 || pl.n_seg == 1;
     const int kmode = split ? 3 : pl.mode;             // the kernel's MODE
     const bool team = pl.team_shift > 0;
-    const void* fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, false) : pick_kernel(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+    const void* fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, false) : pl.narrow ? pick_narrow_kernel(h->dtype, h->ncb, fused) : pick_kernel(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
     if (!fn) return TW_ERR_UNSUPPORTED;
     const void* fn_reduce = nullptr;
     if (split) {
@@ -3140,7 +3175,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
         if (!fn_reduce) return TW_ERR_UNSUPPORTED;
     }
     const int variant = team ? 8 : kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..8
-    const int kernel_id = (h->ew_nnz > 0 ? 240 : 0) + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant + (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
+    const int kernel_id = pl.narrow ? 516 + (h->dtype == TW_F16 ? 0 : 6) + (fused ? 3 : 0) + (h->ncb >> 1) : (h->ew_nnz > 0 ? 240 : 0) + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant + (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
     rc = ensure_lds(dev, kernel_id, fn);
     if (rc) return rc;
 

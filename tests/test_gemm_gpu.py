@@ -400,6 +400,36 @@ def test_gelu_of_every_value(tw, dtype):
     assert not bad.any(), (x[bad][:5], got[bad][:5], ref[bad][:5])
 
 
+# M, K, N, G, type, keep, column pruning: K resident, blocks of 64 rows, windows of two lines.  The shortest and the longest such K, tiles of
+# all widths, spans of one window and of several, with and without columns pruned in them, a last block of one row and of a part.
+NARROW = [(8193, 921, 700, 128, "f16", ("upow", 0.1, 0.6), 0.05), (4321, 1040, 1234, 32, "bf16", ("upow", 0.05, 0.4), 0.03), (9000, 1000, 900, 64, "f16", ("const", 0.3), 0.6),
+          (12001, 1024, 1300, 128, "bf16", ("const", 0.2), 0.7)]
+
+
+@pytest.mark.parametrize("case", NARROW, ids=lambda c: "x".join(map(str, c[:4])))
+def test_64_rows_beside_narrow_windows(tw, case):
+    """Every element, plain and with bias and GELU, the bits of tw_gemm_t, nothing written beside C."""
+    M, K, N, G, dtype, keep, cp = case
+    w = W.generate(W.small_spec("narrow", M=M, K=K, N=N, G=G, dtype=dtype, col_prune=cp, keep=keep, seed_offset=5600 + M + K))
+    wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
+    _say(f"narrow windows M={M} K={K} N={N} G={G} {dtype} T={wt.info['T']} {pl}")
+    assert pl["mode"] == 0 and pl["rows_per_block"] == 64 and pl["lds_bytes"] <= 160 * 1024 < (K + 9) * 136 + 8 * 4672
+    A = _device_A(tw, w.A, dtype)
+    bbits = _bias_bits(N, dtype, 31)
+    outs = [torch.full((M, N + 3), float("nan"), dtype=A.dtype, device="cuda:0") for _ in range(2)]
+    tw.tw_gemm(wt, A, outs[0][:, :N])
+    tw.tw_gemm_bias_act(wt, A, tw.bits_to_tensor(bbits, dtype), "gelu", outs[1][:, :N])
+    Ct = tw.tw_gemm_t(wt, _device_At(tw, w.A, dtype))
+    torch.cuda.synchronize()
+    _compare_whole(outs[0][:, :N], w.A, w.B, w.mask, dtype, what="narrow windows")
+    assert torch.equal(Ct.T.contiguous(), outs[0][:, :N].contiguous()), "the two boundaries differ in some bit"
+    _compare_whole(outs[1][:, :N], w.A, w.B, w.mask, dtype, what="narrow windows, fused",
+                   post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "gelu"))
+    for o in outs:
+        assert bool(torch.isnan(o[:, N:].float()).all().item()), "wrote beside C"
+
+
 # M, K, N, G, type, keep: four multiplying and four loading waves.  A last chunk of one column, of less than a window, of several windows
 # and a part; K a multiple of eight and not; one to four tiles a workgroup, one set of tiles and several; chunks in which a tile keeps
 # nothing; more and fewer items than compute units, last blocks of one row and of a part; row blocks lower than 64 rows.
