@@ -292,10 +292,10 @@ struct StepRegs {
 };
 
 // Requests the packed B of step s (clamped to `last`) of a tile into slot `slot`.
-template <int NCB>
+template <int NCB, int STRIDE = NCB>
 __device__ __forceinline__ void issue_b(StepRegs<NCB>& rg, int slot, const unsigned char* bl, int s, int last) {
     s = s < last ? s : last;
-    const unsigned char* b = bl + ((long)s * NCB) * 1024;
+    const unsigned char* b = bl + ((long)s * STRIDE) * 1024;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
         rg.bq[slot][cb] = *(const tw_u16x8*)(b + cb * 1024);
@@ -308,8 +308,9 @@ __device__ __forceinline__ void issue_k(StepRegs<NCB>& rg, int slot, const unsig
     rg.kk[slot] = *(const unsigned*)(gk + (long)s * 32);
 }
 
-// Requests the first steps of a tile; the range [s0, s1) must not be empty.
-template <int NCB>
+// Requests the first steps of a tile; the range [s0, s1) must not be empty.  (STRIDE: column blocks of the tile, where the wave takes
+// NCB of them.)
+template <int NCB, int STRIDE = NCB>
 __device__ __forceinline__ void prefetch_first_steps(StepRegs<NCB>& rg, const unsigned char* goff_tile,
                                                      const unsigned char* bvals_tile, int s0, int s1, int lane_in) {
     const int lane = fresh(lane_in);
@@ -318,7 +319,7 @@ __device__ __forceinline__ void prefetch_first_steps(StepRegs<NCB>& rg, const un
 #pragma unroll
     for (int i = 0; i < kIdxAhead; ++i) issue_k<NCB>(rg, i, gk, s0 + i, s1 - 1);
 #pragma unroll
-    for (int i = 0; i < prefetch_depth<NCB>(); ++i) issue_b<NCB>(rg, i, bl, s0 + i, s1 - 1);
+    for (int i = 0; i < prefetch_depth<NCB>(); ++i) issue_b<NCB, STRIDE>(rg, i, bl, s0 + i, s1 - 1);
 }
 
 // Steps [s0, s1) (not empty) of one tile for this wave: gather A from LDS, stream packed B from global, MFMA.
@@ -327,7 +328,7 @@ __device__ __forceinline__ void prefetch_first_steps(StepRegs<NCB>& rg, const un
 // is issued before the MFMAs of step s, so both latencies hide behind MFMAs.  The loop body has no branches
 // except its exits (requests past the last step are clamped to the last step and never used), which
 // keeps the compiler's wait counts exact.
-template <int DT, int MS, int NCB>
+template <int DT, int MS, int NCB, int STRIDE = NCB>
 __device__ __forceinline__ void run_steps(tw_f32x16 (&acc)[MS][NCB], StepRegs<NCB>& rg, const unsigned char* at,
                                           unsigned at_pitch, const unsigned char* goff_tile,
                                           const unsigned char* bvals_tile, int s0, int s1, int lane_in) {
@@ -371,7 +372,7 @@ __device__ __forceinline__ void run_steps(tw_f32x16 (&acc)[MS][NCB], StepRegs<NC
         // the request for a column block of step s+kPrefetch follows the MFMAs that read its registers:
         // the requests reach the memory pipeline spread over the step instead of in a burst
         const int sb = (s + kPrefetch) < last ? (s + kPrefetch) : last;
-        const unsigned char* bnext = bl + ((long)sb * NCB) * 1024;
+        const unsigned char* bnext = bl + ((long)sb * STRIDE) * 1024;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
@@ -2267,6 +2268,89 @@ __global__ __launch_bounds__(kThreads) void tw_stream_kernel(const TwGemmParams 
     }
 }
 
+// First kernel of a split-K product, row-major boundary (MODE 3 above for everything else): a workgroup has one item (part, tile set, row
+// block) and few chunks, so nothing overlaps its first operands and few tiles leave waves without work.  All eight waves
+// bring in A: direct loads put chunks as they lie in memory into two buffers, both on their way at once; a wave turns the eight rows that it
+// has asked for itself into the K-major copy, as in tw_stream_kernel (8 rows x 32 columns a reading instruction).  And a tile has 8 / tiles
+// of the waves: two row halves (H = 2, up to four tiles) and two column halves (CG = 2, up to two tiles of 64 or 128 columns).
+// The results are those of MODE 3, bit for bit.
+// What bounds it is the chain of one part: launch, a chunk's latency, the heaviest tile's steps, the dump (32 KB a tile and part).  MODE 3
+// -> this kernel, whole calls: 2048 x 3072 -> 768 23.6 -> 22.6 us, 1745 x 3441 -> 477 26.6 -> 21.7, 348 x 2002 -> 746 16.0 -> 13.6,
+// 64 x 2593 -> 1549 with GELU 14.8 -> 12.4; 60 random split calls 1.0 to 1.27 times as fast.
+template <int DT, int NCB, int H, int CG>
+__global__ __launch_bounds__(kThreads) void tw_part_kernel(const TwGemmParams p) {
+    constexpr unsigned PITCH = at_pitch_of<2>(), RAW = 64 * kStreamChunk * 2, WIN = 1024;      // a wave's window: 8 rows x 64 columns
+    constexpr int kWin = kStreamChunk / kWindow, MS = 2 / H, NC = NCB / CG;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uni(tid >> 6);
+    const int item = (int)blockIdx.x;
+    const int sp_item = item / p.n_mblocks, mb = item - sp_item * p.n_mblocks;
+    const int part = sp_item / p.n_seg, set = sp_item - part * p.n_seg;
+    const int c_first = part * p.chunks_per_part;
+    const int n_loc = (p.n_chunks - c_first) < p.chunks_per_part ? (p.n_chunks - c_first) : p.chunks_per_part;
+    const int row0 = mb * 64;
+
+    unsigned char* const raw = smem + p.abuf_bytes + wave * (kWin * WIN);                      // this wave's rows of buffer 0
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)raw;
+    const unsigned lda2 = 2u * (unsigned)p.lda;
+    const int frow = 8 * wave + (lane >> 3), piece = (lane & 7) ^ (lane >> 3);
+    auto issue = [&](int j) {                                // chunk j of the part
+        const int col0 = (c_first + j) * kStreamChunk;
+        const uint64_t base = (uint64_t)(p.A + (long)row0 * p.lda + col0);
+        const tw_u32x4 da{(unsigned)uni((int)(unsigned)base), (unsigned)uni((int)(unsigned)(base >> 32)) & 0xFFFFu, kStreamRange, 0x00020000u};
+        const bool row = row0 + frow < p.M;
+#pragma unroll
+        for (int w = 0; w < kWin; ++w)
+            tw_load_lds<false>(da, row && col0 + w * kWindow + piece * 8 < p.K ? (unsigned)frow * lda2 + (unsigned)(w * 128 + piece * 16) : kStreamRange,
+                               lds0 + (unsigned)(j & 1) * RAW + (unsigned)w * WIN);
+    };
+    const int slot = wave / (H * CG), half = wave % H, cg = (wave / H) % CG;
+    const int ti = set * p.tiles_per_set + slot;
+    const bool active = slot < p.tiles_per_set && ti < p.T;
+    issue(0);
+    if (n_loc > 1) issue(1);
+    const TileU d = fetch_tile(p, active ? ti : 0);
+    const int* sp = (const int*)(p.blob + p.off_step_ptr) + d.step_ptr + c_first;
+    const unsigned char* gt = p.blob + p.off_goff + (long)d.first_step * 32;
+    const unsigned char* bt = p.blob + p.off_bvals + ((long)d.first_step * NCB + cg * NC) * 1024;
+    if (tid < 32) *(unsigned*)(smem + (unsigned)kStreamChunk * PITCH + tid * 4) = 0u;
+    int s0 = fetch_int(sp, 0), s1 = fetch_int(sp, 1);
+    tw_f32x16 acc[MS][NC];
+    zero_acc<MS, NC>(acc);
+    // turning: group lane / 16: rows 4 * (group % 2) .. + 3, columns 16 * (group / 2) .. + 15 of 32
+    const int j16 = lane & 15, trow = 4 * ((lane >> 4) & 1) + (j16 >> 2), tcol = 16 * (lane >> 5);
+    const unsigned from = (unsigned)(trow * 128 + ((((tcol >> 3) + ((j16 & 3) >> 1)) ^ trow) << 4) + (j16 & 1) * 8);
+    unsigned char* const to = smem + (unsigned)(tcol + j16) * PITCH + (unsigned)(8 * wave + 4 * ((lane >> 4) & 1)) * 2u;
+    for (int j = 0; j < n_loc; ++j) {
+        if (j + 1 < n_loc) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kWin) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const unsigned char* src = raw + (unsigned)(j & 1) * RAW;
+#pragma unroll
+        for (int w = 0; w < kWin; ++w) {
+            tw_i16x4 v[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) v[t] = tw_lds_read_tr(src + w * WIN + (from ^ (unsigned)(t << 6)));
+#pragma unroll
+            for (int t = 0; t < 2; ++t) *(tw_u32x2*)(to + (unsigned)(w * kWindow + 32 * t) * PITCH) = __builtin_bit_cast(tw_u32x2, v[t]);
+        }
+        const bool steps = active && s0 < s1;
+        StepRegs<NC> rg;
+        if (steps) prefetch_first_steps<NC, NCB>(rg, gt, bt, s0, s1, lane);
+        if (j + 2 < n_loc) issue(j + 2);
+        tw_lds_wait<63>();                                   // the chunk is there
+        if (steps) run_steps<DT, MS, NC, NCB>(acc, rg, smem + half * 64, PITCH, gt, bt, s0, s1, lane);
+        s0 = s1;
+        s1 = fetch_int(sp, j + 2 <= n_loc ? j + 2 : n_loc);
+        if (j + 1 < n_loc) tw_lds_wait<63>();                // everyone is done with it
+    }
+    if (active) {
+        float* dst = p.partials + ((((long)part * p.n_mblocks + mb) * p.T + ti) * 2 + half) * (long)(NCB * 1024) + cg * (NC * 1024);
+        if constexpr (H == 2) dump_partial<1, NC>(dst, acc, lane);
+        else dump_partial<2, NC>(dst, acc, lane);
+    }
+}
+
 }  // namespace
 
 // ---- kernel tables
@@ -2281,6 +2365,7 @@ template <int DT, bool FUSED, bool EW> const void* pick_mode_t(int mode, int ms,
 template <int DT, bool FUSED> const void* pick_reduce(int ncb, bool transposed);               // second kernel of split K
 template <int DT, bool FUSED> const void* pick_team(int ncb, bool transposed);                 // teams of waves per tile
 template <int DT, bool FUSED> const void* pick_narrow(int ncb);                                // K resident, 64 rows, narrow staging windows
+template <int DT> const void* pick_part(int ncb, int tiles);                                    // split K, row-major
 template <int DT, bool FUSED> const void* pick_stream(int ncb);                     // K streamed, row-major
 template <int DT, bool FUSED> const void* pick_rows(int ncb, int stages);                                  // a tile of a token block per workgroup
 }  // namespace tw_parts
@@ -2339,6 +2424,15 @@ const void* pick_narrow(int ncb) {
         default: return nullptr;
     }
 }
+template <int DT>
+const void* pick_part(int ncb, int tiles) {
+    switch (ncb) {
+        case 1: return tiles <= 4 ? (const void*)tw_part_kernel<DT, 1, 2, 1> : (const void*)tw_part_kernel<DT, 1, 1, 1>;
+        case 2: return tiles <= 2 ? (const void*)tw_part_kernel<DT, 2, 2, 2> : tiles <= 4 ? (const void*)tw_part_kernel<DT, 2, 2, 1> : (const void*)tw_part_kernel<DT, 2, 1, 1>;
+        case 4: return tiles <= 2 ? (const void*)tw_part_kernel<DT, 4, 2, 2> : tiles <= 4 ? (const void*)tw_part_kernel<DT, 4, 2, 1> : (const void*)tw_part_kernel<DT, 4, 1, 1>;
+        default: return nullptr;
+    }
+}
 template <int DT, bool FUSED>
 const void* pick_stream(int ncb) {
     switch (ncb) {
@@ -2380,14 +2474,16 @@ const void* pick_team(int ncb, bool transposed) {
     KW template const void* tw_parts::pick_narrow<DT, FUSED>(int);                \
     KW template const void* tw_parts::pick_stream<DT, FUSED>(int);
 #define TW_TABLES_ALL(KW, DT, FUSED) TW_TABLES_EW(KW, DT, FUSED, false) TW_TABLES_EW(KW, DT, FUSED, true) TW_TABLES_REDUCE(KW, DT, FUSED)
+#define TW_TABLES_PART(KW, DT) KW template const void* tw_parts::pick_part<DT>(int, int);
 #if TW_PART == 0
+TW_TABLES_PART(extern, TW_F16) TW_TABLES_PART(extern, TW_BF16)
 TW_TABLES_ALL(extern, TW_F16, false) TW_TABLES_ALL(extern, TW_F16, true) TW_TABLES_ALL(extern, TW_BF16, false) TW_TABLES_ALL(extern, TW_BF16, true)
 #elif TW_PART == 1
-TW_TABLES_EW(, TW_F16, false, false) TW_TABLES_REDUCE(, TW_F16, false)
+TW_TABLES_EW(, TW_F16, false, false) TW_TABLES_REDUCE(, TW_F16, false) TW_TABLES_PART(, TW_F16)
 #elif TW_PART == 2
 TW_TABLES_EW(, TW_F16, true, false) TW_TABLES_REDUCE(, TW_F16, true)
 #elif TW_PART == 3
-TW_TABLES_EW(, TW_BF16, false, false) TW_TABLES_REDUCE(, TW_BF16, false)
+TW_TABLES_EW(, TW_BF16, false, false) TW_TABLES_REDUCE(, TW_BF16, false) TW_TABLES_PART(, TW_BF16)
 #elif TW_PART == 4
 TW_TABLES_EW(, TW_BF16, true, false) TW_TABLES_REDUCE(, TW_BF16, true)
 #elif TW_PART == 5
@@ -3000,7 +3096,7 @@ int device_cus(int dev) {
 }
 
 // The dynamic-LDS limit of a kernel is raised to the hardware maximum once per (device, kernel).
-constexpr int kMaxKernels = 544;
+constexpr int kMaxKernels = 560;
 std::atomic<unsigned> g_lds_set[kMaxDevices][kMaxKernels];
 
 int ensure_lds(int dev, int kernel_id, const void* fn) {
@@ -3212,7 +3308,16 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
         p.urow_off = p.stage_off + kStreamTiles * kStageBytes;    // the ring
         return hipLaunchKernel(fs, dim3(grid), dim3(kThreads), args, stream_lds_bytes(), stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
     }
-    if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, pl.lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
+    unsigned lds_bytes = pl.lds_bytes;
+    if (split && h->ew_nnz == 0 && h->k_chunk == kStreamChunk && lda < (1 << 23)) {
+        fn = h->dtype == TW_F16 ? tw_parts::pick_part<TW_F16>(h->ncb, pl.tiles_per_set) : tw_parts::pick_part<TW_BF16>(h->ncb, pl.tiles_per_set);
+        if (!fn) return TW_ERR_UNSUPPORTED;
+        const int shape = pl.tiles_per_set <= 2 ? 0 : pl.tiles_per_set <= 4 ? 3 : 6;
+        rc = ensure_lds(dev, 528 + (h->dtype == TW_F16 ? 0 : 9) + shape + (h->ncb >> 1), fn);
+        if (rc) return rc;
+        lds_bytes = at_bytes(2, kStreamChunk) + 2 * 64 * kStreamChunk * 2;
+    }
+    if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
     if (split) {
         const long units = (long)pl.n_mblocks * h->T * 8;                 // a wave per pass of a tile
         if (hipLaunchKernel(fn_reduce, dim3((unsigned)units), dim3(64), args, 0, stream) != hipSuccess) return TW_ERR_HIP;

@@ -430,6 +430,32 @@ def test_64_rows_beside_narrow_windows(tw, case):
         assert bool(torch.isnan(o[:, N:].float()).all().item()), "wrote beside C"
 
 
+# M, K, N, G, type, keep, tiles a workgroup at most: split K row-major.  One and two tiles a workgroup (column halves), up to four (row
+# halves), more; parts of one chunk and of up to four; a last chunk of one column; one row, blocks of one row and of a part.
+PARTS = [(1, 2305, 128, 128, "f16", ("const", 0.4), 2), (130, 3100, 300, 128, "bf16", ("upow", 0.002, 0.6), 2), (449, 3000, 1250, 128, "f16", ("upow", 0.05, 0.5), 4),
+         (1153, 3072, 768, 128, "bf16", ("upow", 0.1, 0.5), 8), (65, 1600, 120, 64, "f16", ("upow", 0.1, 0.9), 2), (700, 2800, 700, 64, "bf16", ("upow", 0.01, 0.5), 8),
+         (4614, 3648, 192, 128, "f16", ("const", 0.3), 8), (33, 2689, 64, 32, "f16", ("const", 0.3), 2), (500, 2900, 600, 32, "bf16", ("upow", 0.05, 0.5), 8)]
+
+
+@pytest.mark.parametrize("case", PARTS, ids=lambda c: "x".join(map(str, c[:4])))
+def test_parts_of_a_split_k(tw, case):
+    """Every element of a split product, and (K rows that no tile keeps, whatever they hold) nothing else."""
+    M, K, N, G, dtype, keep, most = case
+    w = W.generate(W.small_spec("parts", M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.04, keep=keep, seed_offset=5700 + M + K))
+    wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
+    _say(f"parts M={M} K={K} N={N} G={G} {dtype} T={wt.info['T']} {pl}")
+    assert pl["k_parts"] > 1 and pl["tiles_per_set"] <= most
+    A = torch.full((M, (K + 7) // 8 * 8), float("inf"), dtype=wt.torch_dtype, device="cuda:0")[:, :K]
+    A.copy_(tw.bits_to_tensor(w.A, dtype))
+    A[:, torch.as_tensor(np.flatnonzero(~w.mask.any(axis=1)), device="cuda:0")] = float("nan")
+    C = torch.full((M, N + 1), float("nan"), dtype=A.dtype, device="cuda:0")
+    tw.tw_gemm(wt, A, C[:, :N])
+    torch.cuda.synchronize()
+    _compare_whole(C[:, :N], w.A, w.B, w.mask, dtype, what="parts")
+    assert bool(torch.isnan(C[:, N:].float()).all().item()), "wrote beside C"
+
+
 # M, K, N, G, type, keep: four multiplying and four loading waves.  A last chunk of one column, of less than a window, of several windows
 # and a part; K a multiple of eight and not; one to four tiles a workgroup, one set of tiles and several; chunks in which a tile keeps
 # nothing; more and fewer items than compute units, last blocks of one row and of a part; row blocks lower than 64 rows.
