@@ -1250,6 +1250,8 @@ __device__ __forceinline__ void xc_finish(const TwGemmParams& p, const TileU& d,
 //         (Six multiplying and two loading waves were tried for weights of five or six tiles: the two
 //         loading waves cannot keep up with the transposing LDS writes of the row-major boundary, 9 % slower
 //         than MODE 1 on the FFN-down of BERT-base, and no gain on the transposed boundary.)
+//         Row-major it serves TEW blobs and pitches from 2^23 elements; tw_stream_kernel has the rest.
+// MODE 3: split K (below).  Row-major likewise: tw_part_kernel has the rest.
 // Split K: a wave's fp32 results of its part of the K chunks, as they lie in the registers: piece (ms, cb, q) of
 // lane l (registers 4q .. 4q+3 of acc[ms][cb]) at float offset (((ms * NCB + cb) * 4 + q) * 64 + l) * 4, so that
 // every instruction writes (reads) 1 KB of consecutive memory.  32 KB per tile and part with 128-column tiles.
@@ -1987,7 +1989,9 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
 // 576 -> 201 51 -> 14.
 //
 // Workgroups of one XCD (ids equal modulo 8) share its L2: the token blocks are dealt out to the XCDs, rows_group blocks at a
-// time, as many as leave the rows of those of one XCD in its L2; within a group the heaviest tiles go first.
+// time, as many as leave the rows of those of one XCD in its L2; within a group the heaviest tiles go first.  A group is a multiple of
+// eight blocks, so that a block stays with its XCD from tile to tile (77 blocks in one group, 19648 tokens of 571 -> 2289, G = 32:
+// 112 us); up to seven blocks that are left over go first, whichever XCDs they meet.
 template <int NCB> constexpr int rows_bt() { return NCB == 4 ? 128 : 256; }
 template <int NCB> constexpr int rows_stage_bytes() { return rows_bt<NCB>() * 32 + NCB * 1024; }
 constexpr unsigned kRowsRange = 0x40000000u;               // (twice that is out of range as well)
@@ -2006,9 +2010,11 @@ __global__ __launch_bounds__(256, kRowsStages == 4 ? 4 : 2) void tw_rows_kernel(
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     // the item: tile number t (0: the heaviest), token block mb
-    const int per = p.rows_group * p.T, g = (int)blockIdx.x / per, rem = (int)blockIdx.x - g * per;
-    const int left = p.n_mblocks - g * p.rows_group, width = left < p.rows_group ? left : p.rows_group;
-    const int t = rem / width, m0 = (g * p.rows_group + rem - t * width) * BT;
+    const int odd = p.n_mblocks & 7, id = (int)blockIdx.x - odd * p.T;       // (id < 0: one of the odd blocks)
+    const int per = p.rows_group * p.T, g = id < 0 ? 0 : id / per, rem = id < 0 ? (int)blockIdx.x : id - g * per;
+    const int block0 = id < 0 ? 0 : odd + g * p.rows_group, left = p.n_mblocks - block0;
+    const int width = id < 0 ? odd : left < p.rows_group ? left : p.rows_group;
+    const int t = rem / width, m0 = (block0 + rem - t * width) * BT;
     // (with K resident the dispatch order puts the lightest kWaves tiles, lightest first, in front of the others)
     const bool light_first = p.n_chunks == 1 && p.T > kWaves;
     const TileU d = fetch_tile(p, !light_first ? t : t < p.T - kWaves ? t + kWaves : p.T - 1 - t);
@@ -2989,13 +2995,18 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
 
 // Whether tw_gemm_t runs tw_rows_kernel instead of the plan's kernel (pl.rows_group, 0: no).
 // Not for plans that share a tile's K steps out (split K, teams of waves: other groups of sums), not for TEW blobs.  Otherwise
-// the workgroups of that kernel are many and short, and it is the faster one wherever its longest workgroup (kRowsUs and kRowsStepUs
-// for each step of the heaviest tile, kRowsCrowdUs with four workgroups to a compute unit) is expected to take less time
-// than the plan's kernel as a whole.  Of 70 random calls with more than 300 tokens it took 38, 1.09 to 3.7 times as fast
-// (54959 tokens of 576 -> 201 13.9 us, 50.9 before), one 3 % slower; the heaviest tile of 6400 tokens of 3133 -> 256 has 196
-// steps, 36.6 us, and stays with the streamed kernel's 33.4.
+// the workgroups of that kernel are many and short, and it is the faster one wherever two things take less time than the plan's
+// kernel as a whole: its longest workgroup (kRowsUs and kRowsStepUs for each step of the heaviest tile, kRowsCrowdUs with four workgroups to
+// a compute unit, kRowsFar times that where fewer than eight token blocks leave the rows of all of them to every XCD and its L2 does not
+// hold them), and what a compute unit puts through with all its workgroups (kRowsFullStepUs a step, 8 to 10 KB of rows and weights whatever the
+// tile's width, and the stores).  The second decides on many narrow tiles: 16384 tokens of 768 -> 3072 (75 %) with G = 32 take 57 us here and 46 with
+// the block of 64 tokens resident, with G = 64 43 and 43, with G = 128 39 and 44.  The plan's estimate, made to compare plans, is corrected by kPlan:
+// of 95 random calls (600 tokens and more) its measured time is 0.68 to 0.88 of it with tiles of 32 columns, 1.06 to 1.17
+// resident with 128.  On those calls this kernel is taken 80 times, 1.7 times as fast in the geometric mean; the choice is more than 5 % behind
+// the faster one in seven, at most 15 %.
 void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu) {
-    constexpr double kRowsUs = 6.5, kRowsStepUs = 0.14, kRowsCrowdUs = 0.18, kRowsGeluUs = 2.0, kTileStepUs = 0.15;
+    constexpr double kRowsUs = 6.5, kRowsStepUs = 0.14, kRowsCrowdUs = 0.18, kRowsGeluUs = 2.0, kTileStepUs = 0.15,
+                     kRowsFullUs = 4.0, kRowsFullStepUs = 0.105, kRowsStoreBytesPerUs = 18e3, kRowsFar = 1.35;
     constexpr long kRowsL2 = 3400 * 1024;                    // of an XCD's 4 MiB, for rows of At
     pl.rows_group = 0;
     if (pl.n_parts > 1 || pl.team_shift > 0 || h->ew_nnz > 0 || h->n_chunks > 64) return;
@@ -3005,20 +3016,25 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
     const int bt = h->ncb == 4 ? rows_bt<4>() : rows_bt<1>();
     const long blocks = ((long)M + bt - 1) / bt, items = blocks * h->T;
     if (items >= 0x7fffffffL) return;
-    // two workgroups or fewer to a compute unit: a deeper ring takes the place of the others
-    pl.rows_stages = items <= 2L * n_cu ? 8 : 4;
-    const unsigned ring = pl.rows_stages * (h->ncb == 4 ? rows_stage_bytes<4>() : h->ncb == 2 ? rows_stage_bytes<2>() : rows_stage_bytes<1>());
-    pl.rows_lds = ring + (unsigned)(heaviest + pl.rows_stages + 1) * 64u;
+    // two workgroups or fewer to a compute unit: a deeper ring takes the place of the others.  (Where two such rings do not fit beside each
+    // other, tiles of 64 columns or long lists, one or fewer: a second round of workgroups costs as much as the first.)
+    const unsigned stage = h->ncb == 4 ? rows_stage_bytes<4>() : h->ncb == 2 ? rows_stage_bytes<2>() : rows_stage_bytes<1>();
+    auto lds_of = [&](int stages) { return stages * stage + (unsigned)(heaviest + stages + 1) * 64u; };
+    pl.rows_stages = items <= (2 * lds_of(8) <= kLdsLimit ? 2L : 1L) * n_cu ? 8 : 4;
+    pl.rows_lds = lds_of(pl.rows_stages);
     if (pl.rows_lds > (pl.rows_stages == 8 ? kLdsLimit : 64u * 1024u)) return;
     const double rounds = (double)((pl.n_items + n_cu - 1) / n_cu);
     const double chunks_us = h->n_chunks * kChunkUsT * (h->ncb <= 2 ? kNarrowChunk : 1.0), tile_us = heaviest * (h->ncb <= 2 ? kTileStepUs : 1.5 * kTileStepUs);
     const double plan_us = rounds * (h->n_chunks == 1 ? resident_item_us(h, pl.ms, (h->T + pl.n_seg - 1) / pl.n_seg, 0, gelu)
                                                       : kItemUs + (chunks_us > tile_us ? chunks_us : tile_us));   // (a tile is one wave's there)
-    const double rows_us = kRowsUs + heaviest * (pl.rows_stages == 8 ? kRowsStepUs : kRowsCrowdUs) + (gelu && items < n_cu ? kRowsGeluUs : 0.0);
-    if (rows_us >= plan_us) return;
     const long bytes = (long)h->K * bt * 2;
+    const double far = blocks < 8 && blocks * bytes > kRowsL2 ? kRowsFar : 1.0;
+    const double longest_us = kRowsUs + heaviest * far * (pl.rows_stages == 8 ? kRowsStepUs : kRowsCrowdUs) + (gelu && items < n_cu ? kRowsGeluUs : 0.0);
+    const double full_us = kRowsFullUs + ((double)blocks * h->total_steps * kRowsFullStepUs + (double)M * h->T * h->G * 2.0 / kRowsStoreBytesPerUs) / n_cu;
+    const double kPlan = h->ncb == 1 ? (h->n_chunks > 1 ? 0.8 : pl.ms > 1 ? 0.77 : 0.75) : h->ncb == 4 && h->n_chunks == 1 ? 1.15 : 1.0;
+    if ((longest_us > full_us ? longest_us : full_us) >= kPlan * plan_us) return;
     const long group = 8 * (bytes < kRowsL2 ? kRowsL2 / bytes : 1);
-    pl.rows_group = (int)(group < blocks ? group : blocks);
+    pl.rows_group = (int)(group < blocks ? group : blocks < 8 ? 8 : blocks & ~7L);
 }
 
 // Whether tw_gemm runs tw_stream_kernel instead of the plan's kernel (pl.stream_items): wherever the plan is MODE 2, but for TEW blobs
@@ -3308,6 +3324,8 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
         p.urow_off = p.stage_off + kStreamTiles * kStageBytes;    // the ring
         return hipLaunchKernel(fs, dim3(grid), dim3(kThreads), args, stream_lds_bytes(), stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
     }
+    // tw_part_kernel for every split, but for TEW blobs (their residual's steps are in MODE 3) and pitches whose rows lie too far apart for
+    // 32-bit offsets: on 60 random split calls it takes 1.0 to 1/1.27 of MODE 3's time, never more.
     unsigned lds_bytes = pl.lds_bytes;
     if (split && h->ew_nnz == 0 && h->k_chunk == kStreamChunk && lda < (1 << 23)) {
         fn = h->dtype == TW_F16 ? tw_parts::pick_part<TW_F16>(h->ncb, pl.tiles_per_set) : tw_parts::pick_part<TW_BF16>(h->ncb, pl.tiles_per_set);

@@ -352,7 +352,8 @@ def test_dense_gemm_of_buffers_without_a_last_pitch(tw, case):
 ROWS = [("wide", 16385, 300, 700, 128, "f16", ("upow", 0.05, 0.9), 0.05), ("two_blocks", 8201, 1000, 333, 64, "bf16", ("upow", 0.1, 0.6), 0.05),
         ("narrow", 20031, 200, 250, 32, "f16", ("upow", 0.02, 0.9), 0.1), ("streamed", 8190, 3100, 520, 128, "bf16", ("upow", 0.001, 0.3), 0.1),
         ("streamed_narrow", 6300, 1543, 300, 32, "f16", ("upow", 0.003, 0.5), 0.05), ("one_step", 40000, 40, 300, 128, "bf16", ("const", 0.2), 0.0),
-        ("one_tile", 30001, 776, 128, 128, "f16", ("const", 0.3), 0.0), ("many_tiles", 2490, 640, 2900, 64, "f16", ("upow", 0.05, 0.5), 0.3)]
+        ("one_tile", 30001, 776, 128, 128, "f16", ("const", 0.3), 0.0), ("many_tiles", 2490, 640, 2900, 64, "f16", ("upow", 0.05, 0.5), 0.3),
+        ("few_blocks", 1350, 1344, 2500, 32, "bf16", ("upow", 0.05, 0.3), 0.05), ("groups", 7900, 3100, 520, 64, "f16", ("upow", 0.001, 0.3), 0.1)]
 
 
 @pytest.mark.parametrize("case", ROWS, ids=[c[0] for c in ROWS])
