@@ -331,7 +331,7 @@ def main() -> int:
                                 "roofline": {"bound": "hbm", "achieved": res["tw_t_gbs"], "peak": HBM_PEAK_GBS,
                                              "unit": "GB/s", "frac": res["tw_t_hbm_frac"],
                                              "traffic": traffic_t, "traffic_source": traffic_t_note,
-                                             "kernel": "tw_gemm_kernel<f16, MS=2 (64 tokens), NCB=4, MODE 0, transposed>"}},
+                                             "kernel": "tw_rows_kernel<f16, NCB=4 (128 tokens x a tile), ring of 4>"}},
         "paper_context": PAPER_CONTEXT,
     }
     if not args.no_cpu_baseline:
