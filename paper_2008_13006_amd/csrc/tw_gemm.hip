@@ -3006,7 +3006,8 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
 // the faster one in seven, at most 15 %.
 void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu) {
     constexpr double kRowsUs = 6.5, kRowsStepUs = 0.14, kRowsCrowdUs = 0.18, kRowsGeluUs = 2.0, kTileStepUs = 0.15,
-                     kRowsFullUs = 4.0, kRowsFullStepUs = 0.105, kRowsStoreBytesPerUs = 18e3, kRowsFar = 1.35;
+                     kRowsFullUs = 4.0, kRowsFullStepUs = 0.105, kRowsStoreBytesPerUs = 18e3, kRowsFar = 1.35,
+                     kWeightBytesPerUs = 110e3;
     constexpr long kRowsL2 = 3400 * 1024;                    // of an XCD's 4 MiB, for rows of At
     pl.rows_group = 0;
     if (pl.n_parts > 1 || pl.team_shift > 0 || h->ew_nnz > 0 || h->n_chunks > 64) return;
@@ -3024,7 +3025,9 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
     pl.rows_lds = lds_of(pl.rows_stages);
     if (pl.rows_lds > (pl.rows_stages == 8 ? kLdsLimit : 64u * 1024u)) return;
     const double rounds = (double)((pl.n_items + n_cu - 1) / n_cu);
-    const double chunks_us = h->n_chunks * kChunkUsT * (h->ncb <= 2 ? kNarrowChunk : 1.0), tile_us = heaviest * (h->ncb <= 2 ? kTileStepUs : 1.5 * kTileStepUs);
+    // (a chunk's packed weights pass behind its rows of A: 590 steps, 22 us, of the 47.6 that 16384 tokens of 3072 -> 768 take there, 41.5 here)
+    const double weights_us = (double)h->total_steps / pl.n_seg * h->ncb * 1024.0 / kWeightBytesPerUs;
+    const double chunks_us = h->n_chunks * kChunkUsT * (h->ncb <= 2 ? kNarrowChunk : 1.0) + weights_us, tile_us = heaviest * (h->ncb <= 2 ? kTileStepUs : 1.5 * kTileStepUs);
     const double plan_us = rounds * (h->n_chunks == 1 ? resident_item_us(h, pl.ms, (h->T + pl.n_seg - 1) / pl.n_seg, 0, gelu)
                                                       : kItemUs + (chunks_us > tile_us ? chunks_us : tile_us));   // (a tile is one wave's there)
     const long bytes = (long)h->K * bt * 2;
