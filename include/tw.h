@@ -174,7 +174,8 @@ typedef struct tw_plan_t {
     int32_t tile_items;      /* tw_gemm_t: > 0: a kernel with a workgroup for every tile of every block of 128 (G = 128) or 256
                                 tokens runs in place of the plan above, this many workgroups.  (Without GELU, which
                                 weighs in that choice where they are few.) */
-    int32_t reserved[4];
+    uint32_t tile_lds_bytes; /* with tile_items: that kernel's on-chip memory per workgroup, else 0 */
+    int32_t reserved[3];
 } tw_plan_t;
 /* Errors: TW_ERR_ARG (null pointer, negative M, n_cu <= 0), TW_ERR_BUF (not a blob of this format version),
  * TW_ERR_UNSUPPORTED (what tw_gemm / tw_gemm_t would refuse for this blob and M).  M = 0 or a blob without

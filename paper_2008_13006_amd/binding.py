@@ -49,7 +49,7 @@ class TwPlan(ctypes.Structure):
                 ("n_row_blocks", ctypes.c_int32), ("n_sets", ctypes.c_int32), ("n_items", ctypes.c_int32),
                 ("grid", ctypes.c_int32), ("lds_bytes", ctypes.c_uint32), ("row_lists", ctypes.c_int32),
                 ("k_parts", ctypes.c_int32), ("team_waves", ctypes.c_int32), ("tile_items", ctypes.c_int32),
-                ("reserved", ctypes.c_int32 * 4)]
+                ("tile_lds_bytes", ctypes.c_uint32), ("reserved", ctypes.c_int32 * 3)]
 
 
 def _load() -> ctypes.CDLL:

@@ -1989,7 +1989,7 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
 // 576 -> 201 51 -> 14.
 //
 // Workgroups of one XCD (ids equal modulo 8) share its L2: the token blocks are dealt out to the XCDs, rows_group blocks at a
-// time, as many as leave the rows of those of one XCD in its L2; within a group the heaviest tiles go first.  A group is a multiple of
+// time, as many as leave the rows of those of one XCD in its L2; within a group the tiles that keep the most rows go first.  A group is a multiple of
 // eight blocks, so that a block stays with its XCD from tile to tile (77 blocks in one group, 19648 tokens of 571 -> 2289, G = 32:
 // 112 us); up to seven blocks that are left over go first, whichever XCDs they meet.
 template <int NCB> constexpr int rows_bt() { return NCB == 4 ? 128 : 256; }
@@ -2757,10 +2757,15 @@ unsigned at_bytes(int msb, int k_chunk) {
 unsigned lds_need(int msb, int k_chunk, int buffers) {
     return buffers * at_bytes(msb, k_chunk) + kWaves * kStageBytes + 16u;
 }
-// steps of the heaviest tile
+// Most steps that a tile has.  The tiles are ordered by kept rows; with several chunks each chunk's rows are rounded up to whole steps,
+// so a tile whose rows are spread can have more steps than one that keeps more of them (20 rows in 12 chunks: 12 steps; 21 in
+// one chunk: 2).
 int heaviest_steps(const TwHeader* h) {
     const unsigned char* blob = (const unsigned char*)h;
-    return ((const TwTileDesc*)(blob + h->off_tile_desc))[*(const int32_t*)(blob + h->off_sched_order)].nsteps;
+    const TwTileDesc* d = (const TwTileDesc*)(blob + h->off_tile_desc);
+    int most = d[*(const int32_t*)(blob + h->off_sched_order)].nsteps;
+    for (int t = 0; h->n_chunks > 1 && t < h->T; ++t) most = d[t].nsteps > most ? d[t].nsteps : most;
+    return most;
 }
 // 64 rows of a resident K beside narrow staging windows
 unsigned lds_need_narrow(int k) { return at_bytes(2, k) + kWaves * kNarrowStageBytes + 16u; }
@@ -3170,7 +3175,10 @@ extern "C" int tw_gemm_plan(const void* blob_host, int M, int n_cu, int transpos
     plan->team_waves = 1 << pl.team_shift;
     if (transposed) {
         plan_rows(h, M, ((long)M + 7) / 8 * 8, n_cu, pl, false);
-        if (pl.rows_group > 0) plan->tile_items = (int32_t)(((long)M + (h->ncb == 4 ? 127 : 255)) / (h->ncb == 4 ? 128 : 256) * h->T);
+        if (pl.rows_group > 0) {
+            plan->tile_items = (int32_t)(((long)M + (h->ncb == 4 ? 127 : 255)) / (h->ncb == 4 ? 128 : 256) * h->T);
+            plan->tile_lds_bytes = pl.rows_lds;
+        }
     }
     return TW_OK;
 }

@@ -383,6 +383,30 @@ def test_a_tile_of_a_token_block_per_workgroup(tw, case):
         assert bool(torch.isnan(o[:, M:].float()).all().item()), "wrote outside Ct"
 
 
+# M, K, N, G, type, rows: the first tile keeps rows + 1 rows, all in one place, the others `rows`, spread over all chunks: these have the
+# most steps though the first keeps the most rows.  Both depths of the ring, all widths of a tile.
+CLUSTERED = [(4100, 4608, 1024, 128, "f16", 20), (8200, 4608, 700, 64, "bf16", 30), (16385, 3100, 300, 32, "f16", 30), (16385, 12288, 512, 128, "bf16", 320)]
+
+
+@pytest.mark.parametrize("case", CLUSTERED, ids=lambda c: "x".join(map(str, c[:4])))
+def test_a_tile_with_more_steps_than_the_one_with_the_most_rows(tw, case):
+    """tw_gemm_t, a workgroup per tile and block of tokens: every tile's row list fits, every element is right and has the bits of tw_gemm."""
+    M, K, N, G, dtype, rows = case
+    w = W.generate(W.small_spec("clustered", M=M, K=K, N=N, G=G, dtype=dtype, keep=("const", 0.01), seed_offset=6900 + M + K))
+    mask = np.zeros((K, N), np.uint8)
+    mask[:rows + 1, :G] = 1
+    mask[np.arange(rows) * K // rows, G:] = 1
+    wt = tw.TwWeight.from_dense(w.B, mask, G, dtype)
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count, transposed=True)
+    _say(f"clustered M={M} K={K} N={N} G={G} {dtype} T={wt.info['T']} {pl}")
+    assert pl["tile_items"] > 0
+    C = tw.tw_gemm(wt, _device_A(tw, w.A, dtype))
+    Ct = tw.tw_gemm_t(wt, _device_At(tw, w.A, dtype))
+    torch.cuda.synchronize()
+    _compare_whole(Ct, w.A, w.B, mask, dtype, transposed=True, what="clustered")
+    assert torch.equal(Ct.T.contiguous(), C), "the two boundaries differ in some bit"
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_gelu_of_every_value(tw, dtype):
     """GELU alone, of all finite values of the type: a weight without surviving columns gives act(bias).  Bound: the result's

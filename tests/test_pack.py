@@ -550,6 +550,31 @@ def test_plan_limits_and_errors():
     assert e.value.status == -3                            # TW_ERR_BUF: not a blob
 
 
+def _steps(blob):
+    """Steps of every tile: each chunk's kept rows in sixteens."""
+    inf = tw.tw_info(blob)
+    table = lambda off, n: np.frombuffer(blob.tobytes(), np.int32, n, off)
+    ptr = table(inf["off_tile_row_ptr"], inf["T"] + 1)
+    rows = table(inf["off_row_idx"], ptr[-1])
+    return [int(sum(-(-np.bincount(rows[ptr[t]:ptr[t + 1]] // inf["k_chunk"]) // 16))) for t in range(inf["T"])]
+
+
+@pytest.mark.parametrize("K,N,G,rows", [(4608, 1024, 128, 20), (16384, 1024, 128, 320), (24576, 1024, 128, 200), (3100, 600, 64, 40), (3100, 300, 32, 30)])
+def test_plan_of_a_tile_per_workgroup_holds_every_tiles_rows(K, N, G, rows):
+    """The first tile keeps the most rows, all in one place, the others fewer, spread over all chunks: those have the most steps, and
+    the workgroups' row lists hold one 4-byte entry for every row of a step (and of the ring's stages and one step more)."""
+    mask = np.zeros((K, N), np.uint8)
+    mask[:rows + 1, :G] = 1
+    mask[np.arange(rows) * K // rows, G:] = 1
+    blob = tw.tw_pack(mask.astype(np.uint16) * 15360, mask, G, "f16")
+    steps = _steps(blob)
+    assert tw.tw_info(blob)["T"] == -(-N // G) and max(steps) > steps[0]
+    pl = tw.tw_gemm_plan(blob, 16384, n_cu=256, transposed=True)
+    assert pl["tile_items"] > 0
+    stage = 16 * 2 * (128 if G == 128 else 256) + G // 32 * 1024
+    assert pl["tile_lds_bytes"] in [n * stage + (max(steps) + n + 1) * 64 for n in (4, 8)], (pl, max(steps), steps[0])
+
+
 # ------------------------------------------------------------------ weights that a program copies
 def _host_weight(K, N, seed):
     """A TwWeight whose "device" copy is a host tensor: enough for everything that enqueues nothing."""
