@@ -161,7 +161,8 @@ typedef struct tw_plan_t {
     int32_t n_items;         /* work items = n_row_blocks * n_sets * k_parts */
     int32_t grid;            /* workgroups launched: min(n_items, n_cu), each pulls items until none is left */
     uint32_t lds_bytes;      /* on-chip memory per workgroup (tw_gemm with mode 2: of the transposed kernel's layout without its row
-                                lists; its own kernel takes 155 KB whatever the weight) */
+                                lists; its own kernel takes 155 KB whatever the weight.  tw_gemm with k_parts > 1: of the first kernel,
+                                for lda < 2^23; TEW blobs and rows further apart take another kernel with 141 KB) */
     int32_t row_lists;       /* tw_gemm_t, mode 2: the loading waves read only the K rows that the tiles keep */
     int32_t k_parts;         /* streamed K, few row blocks: the K chunks are split into this many parts, each a work item
                                 of its own (n_items = n_row_blocks * n_sets * k_parts) whose fp32 results go to the
@@ -173,7 +174,8 @@ typedef struct tw_plan_t {
                                 makes teams pay for tiles of fewer steps as well.) */
     int32_t tile_items;      /* tw_gemm_t: > 0: a kernel with a workgroup for every tile of every block of 128 (G = 128) or 256
                                 tokens runs in place of the plan above, this many workgroups.  (Without GELU, which
-                                weighs in that choice where they are few.) */
+                                weighs in that choice where they are few, and for the smallest pitch: where ldat >= 2^23 or
+                                K * ldat * 2 >= 2^30 the plan above runs.) */
     uint32_t tile_lds_bytes; /* with tile_items: that kernel's on-chip memory per workgroup, else 0 */
     int32_t reserved[3];
 } tw_plan_t;

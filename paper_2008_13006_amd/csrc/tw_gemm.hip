@@ -3047,12 +3047,20 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
 
 // Whether tw_gemm runs tw_stream_kernel instead of the plan's kernel (pl.stream_items): wherever the plan is MODE 2, but for TEW blobs
 // and pitches whose rows lie too far apart for 32-bit offsets.  (Measured on 90 random calls: 0.99 to 1.48 times as fast.)
+constexpr long kFarPitch = 1 << 23;
 unsigned stream_lds_bytes() { return 2 * at_bytes(2, kStreamChunk) + kStreamTiles * kStageBytes + kWindows * kWindowBytes; }
 void plan_stream(const TwHeader* h, int M, long lda, Plan& pl) {
     pl.stream_items = 0;
-    if (pl.mode != 2 || pl.n_parts > 1 || h->k_chunk != kStreamChunk || h->ew_nnz > 0 || lda >= (1 << 23)) return;
+    if (pl.mode != 2 || pl.n_parts > 1 || h->k_chunk != kStreamChunk || h->ew_nnz > 0 || lda >= kFarPitch) return;
     pl.stream_items = pl.n_items;
 }
+
+// Whether tw_gemm runs tw_part_kernel for a split's parts: for every split, but for TEW blobs (their residual's steps are in MODE 3) and those
+// pitches.  On 60 random split calls it takes 1.0 to 1/1.27 of MODE 3's time, never more.
+bool parts_by_direct_loads(const TwHeader* h, long lda, const Plan& pl) {
+    return pl.n_parts > 1 && h->ew_nnz == 0 && h->k_chunk == kStreamChunk && lda < kFarPitch;
+}
+unsigned part_lds_bytes() { return at_bytes(2, kStreamChunk) + 2 * 64 * kStreamChunk * 2; }
 
 // the kernel for (dtype, mode, MS, NCB, fused epilogue): a host-side address for hipLaunchKernel and hipFuncSetAttribute
 template <bool EW>
@@ -3169,7 +3177,7 @@ extern "C" int tw_gemm_plan(const void* blob_host, int M, int n_cu, int transpos
     plan->n_sets = pl.n_seg;
     plan->n_items = pl.n_items;
     plan->grid = pl.n_items < n_cu ? pl.n_items : n_cu;
-    plan->lds_bytes = pl.lds_bytes;
+    plan->lds_bytes = !transposed && parts_by_direct_loads(h, h->K, pl) ? part_lds_bytes() : pl.lds_bytes;
     plan->row_lists = pl.urow_off != 0;
     plan->k_parts = pl.n_parts;
     plan->team_waves = 1 << pl.team_shift;
@@ -3335,16 +3343,14 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
         p.urow_off = p.stage_off + kStreamTiles * kStageBytes;    // the ring
         return hipLaunchKernel(fs, dim3(grid), dim3(kThreads), args, stream_lds_bytes(), stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
     }
-    // tw_part_kernel for every split, but for TEW blobs (their residual's steps are in MODE 3) and pitches whose rows lie too far apart for
-    // 32-bit offsets: on 60 random split calls it takes 1.0 to 1/1.27 of MODE 3's time, never more.
     unsigned lds_bytes = pl.lds_bytes;
-    if (split && h->ew_nnz == 0 && h->k_chunk == kStreamChunk && lda < (1 << 23)) {
+    if (parts_by_direct_loads(h, lda, pl)) {
         fn = h->dtype == TW_F16 ? tw_parts::pick_part<TW_F16>(h->ncb, pl.tiles_per_set) : tw_parts::pick_part<TW_BF16>(h->ncb, pl.tiles_per_set);
         if (!fn) return TW_ERR_UNSUPPORTED;
         const int shape = pl.tiles_per_set <= 2 ? 0 : pl.tiles_per_set <= 4 ? 3 : 6;
         rc = ensure_lds(dev, 528 + (h->dtype == TW_F16 ? 0 : 9) + shape + (h->ncb >> 1), fn);
         if (rc) return rc;
-        lds_bytes = at_bytes(2, kStreamChunk) + 2 * 64 * kStreamChunk * 2;
+        lds_bytes = part_lds_bytes();
     }
     if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
     if (split) {

@@ -575,6 +575,21 @@ def test_plan_of_a_tile_per_workgroup_holds_every_tiles_rows(K, N, G, rows):
     assert pl["tile_lds_bytes"] in [n * stage + (max(steps) + n + 1) * 64 for n in (4, 8)], (pl, max(steps), steps[0])
 
 
+@pytest.mark.parametrize("K,N,G,M", [(3072, 768, 128, 2048), (2304, 300, 64, 100), (3000, 200, 32, 1)])
+def test_plan_reports_the_split_kernels_memory(K, N, G, M):
+    """A split on the row-major boundary: a K-major chunk of 384 + 9 columns of 64 rows, 136 bytes each, and two chunks as they lie in memory.  The
+    parts of a TEW blob and of the transposed boundary run a kernel with two K-major chunks and the waves' staging areas."""
+    w = W.generate(W.small_spec("plan_split", M=8, K=K, N=N, G=G, dtype="f16", col_prune=0.0, keep=("const", 0.3), seed_offset=11), with_A=False)
+    blob = tw.tw_pack(w.B, w.mask, G, "f16")
+    chunk = -(-(384 + 9) * 136 // 16) * 16
+    pl, plt = tw.tw_gemm_plan(blob, M), tw.tw_gemm_plan(blob, M, transposed=True)
+    assert pl["k_parts"] > 1 and pl["lds_bytes"] == chunk + 2 * 64 * 384 * 2, pl
+    assert plt["k_parts"] > 1 and 2 * chunk < plt["lds_bytes"] < pl["lds_bytes"], plt
+    tew = tw.tw_pack_tew(w.B, w.mask, tw.tw_restore_ew(w.B, w.mask, 0.01, "f16"), G, "f16")
+    ple = tw.tw_gemm_plan(tew, M)
+    assert ple["k_parts"] == 1 or ple["lds_bytes"] == plt["lds_bytes"], ple
+
+
 # ------------------------------------------------------------------ weights that a program copies
 def _host_weight(K, N, seed):
     """A TwWeight whose "device" copy is a host tensor: enough for everything that enqueues nothing."""
