@@ -3139,6 +3139,13 @@ int ensure_lds(int dev, int kernel_id, const void* fn) {
     return TW_OK;
 }
 
+// the numbers of the kernels that pick_kernel, pick_kernel_t and pick_team_kernel give
+int tile_kernel_id(const TwHeader* h, const Plan& pl, int kmode, bool fused, bool nta, bool transposed) {
+    const int variant = pl.team_shift > 0 ? 8 : kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..8
+    return (h->ew_nnz > 0 ? 240 : 0) + (transposed ? 120 : 0) + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant +
+           (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
+}
+
 }  // namespace
 
 extern "C" int tw_gemm_workspace(const void* blob_host, int M, size_t* ws_bytes) {
@@ -3297,16 +3304,33 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     // streamed K: the activations carry the streaming hint only when one workgroup reads a row block's rows
     const bool nta = pl.mode == 0 || pl.n_seg == 1;
     const int kmode = split ? 3 : pl.mode;             // the kernel's MODE
-    const bool team = pl.team_shift > 0;
-    const void* fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, false) : pl.narrow ? pick_narrow_kernel(h->dtype, h->ncb, fused) : pick_kernel(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+    const bool bf16 = h->dtype != TW_F16;
+    // the kernel that runs, its number among those whose on-chip memory limit is raised once, and its on-chip memory
+    const void* fn;
+    int kernel_id;
+    unsigned lds_bytes = pl.lds_bytes;
+    if (pl.stream_items > 0) {
+        fn = pick_stream_kernel(h->dtype, h->ncb, fused);
+        kernel_id = 492 + (bf16 ? 6 : 0) + (fused ? 3 : 0) + (h->ncb >> 1);
+        lds_bytes = stream_lds_bytes();
+    } else if (parts_by_direct_loads(h, lda, pl)) {
+        fn = bf16 ? tw_parts::pick_part<TW_BF16>(h->ncb, pl.tiles_per_set) : tw_parts::pick_part<TW_F16>(h->ncb, pl.tiles_per_set);
+        kernel_id = 528 + (bf16 ? 9 : 0) + (pl.tiles_per_set <= 2 ? 0 : pl.tiles_per_set <= 4 ? 3 : 6) + (h->ncb >> 1);
+        lds_bytes = part_lds_bytes();
+    } else if (pl.narrow) {
+        fn = pick_narrow_kernel(h->dtype, h->ncb, fused);
+        kernel_id = 516 + (bf16 ? 6 : 0) + (fused ? 3 : 0) + (h->ncb >> 1);
+    } else {
+        const bool team = pl.team_shift > 0;
+        fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, false) : pick_kernel(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+        kernel_id = tile_kernel_id(h, pl, kmode, fused, nta, false);
+    }
     if (!fn) return TW_ERR_UNSUPPORTED;
     const void* fn_reduce = nullptr;
     if (split) {
         fn_reduce = pick_reduce_kernel(h->dtype, h->ncb, fused_epilogue, false);
         if (!fn_reduce) return TW_ERR_UNSUPPORTED;
     }
-    const int variant = team ? 8 : kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..8
-    const int kernel_id = pl.narrow ? 516 + (h->dtype == TW_F16 ? 0 : 6) + (fused ? 3 : 0) + (h->ncb >> 1) : (h->ew_nnz > 0 ? 240 : 0) + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant + (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
     rc = ensure_lds(dev, kernel_id, fn);
     if (rc) return rc;
 
@@ -3325,7 +3349,8 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     p.off_sched_desc = h->off_sched_desc; p.off_step_ptr = h->off_step_ptr; p.off_goff = h->off_goff;
     p.off_dpos = h->off_dpos; p.off_bvals = h->off_bvals;
     p.off_zero_ptr = h->off_zero_ptr; p.off_zero_cols = h->off_zero_cols;
-    p.off_urow = h->off_urow; p.off_ucnt = h->off_ucnt; p.urow_off = 0;
+    p.off_urow = h->off_urow; p.off_ucnt = h->off_ucnt;
+    p.urow_off = pl.stream_items > 0 ? p.stage_off + kStreamTiles * kStageBytes : 0;   // tw_stream_kernel's ring
     p.off_ew_ptr = h->off_ew_ptr; p.off_ew_goff = h->off_ew_goff; p.off_ew_b = h->off_ew_b; p.has_ew = h->ew_nnz > 0;
     p.off_xm_ptr = h->off_xm_ptr; p.off_xm_goff = h->off_xm_goff; p.off_xm_b = h->off_xm_b; p.off_zero_xc = h->off_zero_xc;
     p.stream_stores = ((uintptr_t)C & 127) == 0 && (ldc & 63) == 0;
@@ -3335,23 +3360,6 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     p.partials = (float*)((unsigned char*)workspace + 256);
     const int grid = pl.n_items < n_cu ? pl.n_items : n_cu;
     void* args[] = {(void*)&p};
-    if (pl.stream_items > 0) {
-        const void* fs = pick_stream_kernel(h->dtype, h->ncb, fused);
-        if (!fs) return TW_ERR_UNSUPPORTED;
-        rc = ensure_lds(dev, 492 + (h->dtype == TW_F16 ? 0 : 6) + (fused ? 3 : 0) + (h->ncb >> 1), fs);
-        if (rc) return rc;
-        p.urow_off = p.stage_off + kStreamTiles * kStageBytes;    // the ring
-        return hipLaunchKernel(fs, dim3(grid), dim3(kThreads), args, stream_lds_bytes(), stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
-    }
-    unsigned lds_bytes = pl.lds_bytes;
-    if (parts_by_direct_loads(h, lda, pl)) {
-        fn = h->dtype == TW_F16 ? tw_parts::pick_part<TW_F16>(h->ncb, pl.tiles_per_set) : tw_parts::pick_part<TW_BF16>(h->ncb, pl.tiles_per_set);
-        if (!fn) return TW_ERR_UNSUPPORTED;
-        const int shape = pl.tiles_per_set <= 2 ? 0 : pl.tiles_per_set <= 4 ? 3 : 6;
-        rc = ensure_lds(dev, 528 + (h->dtype == TW_F16 ? 0 : 9) + shape + (h->ncb >> 1), fn);
-        if (rc) return rc;
-        lds_bytes = part_lds_bytes();
-    }
     if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
     if (split) {
         const long units = (long)pl.n_mblocks * h->T * 8;                 // a wave per pass of a tile
@@ -3408,17 +3416,24 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's
     const bool nta = pl.mode == 0 || pl.n_seg == 1;
     const int kmode = split ? 3 : pl.mode;             // the kernel's MODE
-    const bool team = pl.team_shift > 0;
-    const void* fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, true) : pick_kernel_t(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+    // the kernel that runs and its number among those whose on-chip memory limit is raised once
+    const void* fn;
+    int kernel_id;
+    if (pl.rows_group > 0) {
+        fn = pick_rows_kernel(h->dtype, h->ncb, fused, pl.rows_stages);
+        kernel_id = pl.rows_stages == 8 ? 480 + (fused ? 6 : 0) + (h->dtype == TW_F16 ? 0 : 3) + (h->ncb >> 1) : -1;   // (at most 64 KB with four)
+    } else {
+        const bool team = pl.team_shift > 0;
+        fn = team ? pick_team_kernel(h->dtype, h->ncb, fused, true) : pick_kernel_t(h->dtype, kmode, pl.ms, h->ncb, fused, nta, h->ew_nnz > 0);
+        kernel_id = tile_kernel_id(h, pl, kmode, fused, nta, true);
+    }
     if (!fn) return TW_ERR_UNSUPPORTED;
     const void* fn_reduce = nullptr;
     if (split) {
         fn_reduce = pick_reduce_kernel(h->dtype, h->ncb, fused_epilogue, true);
         if (!fn_reduce) return TW_ERR_UNSUPPORTED;
     }
-    const int variant = team ? 8 : kmode == 0 ? (pl.ms == 2 ? 0 : 1) : 2 * kmode + (nta ? 0 : 1);   // 0..8
-    const int kernel_id = (h->ew_nnz > 0 ? 240 : 0) + 120 + (fused ? 60 : 0) + (h->dtype == TW_F16 ? 0 : 30) + 3 * variant + (h->ncb == 4 ? 0 : h->ncb == 2 ? 1 : 2);
-    rc = ensure_lds(dev, kernel_id, fn);
+    if (kernel_id >= 0) rc = ensure_lds(dev, kernel_id, fn);
     if (rc) return rc;
 
     TwGemmParams p;
@@ -3451,13 +3466,7 @@ extern "C" int tw_gemm_t_bias_act(const void* blob_host, const void* blob_dev, c
     if (pl.rows_group > 0) {
         const int bt = h->ncb == 4 ? rows_bt<4>() : rows_bt<1>();
         p.n_mblocks = (M + bt - 1) / bt; p.rows_group = pl.rows_group;
-        const void* fr = pick_rows_kernel(h->dtype, h->ncb, fused, pl.rows_stages);
-        if (!fr) return TW_ERR_UNSUPPORTED;
-        if (pl.rows_stages == 8) {
-            rc = ensure_lds(dev, 480 + (fused ? 6 : 0) + (h->dtype == TW_F16 ? 0 : 3) + (h->ncb >> 1), fr);
-            if (rc) return rc;
-        }
-        return hipLaunchKernel(fr, dim3((unsigned)(p.n_mblocks * h->T)), dim3(256), args, pl.rows_lds, stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
+        return hipLaunchKernel(fn, dim3((unsigned)(p.n_mblocks * h->T)), dim3(256), args, pl.rows_lds, stream) == hipSuccess ? TW_OK : TW_ERR_HIP;
     }
     if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, lds_bytes, stream) != hipSuccess) return TW_ERR_HIP;
     if (split) {
