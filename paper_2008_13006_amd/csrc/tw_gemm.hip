@@ -3049,7 +3049,7 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
 // and pitches whose rows lie too far apart for 32-bit offsets.  (Measured on 90 random calls: 0.99 to 1.48 times as fast.)
 constexpr long kFarPitch = 1 << 23;
 unsigned stream_lds_bytes() { return 2 * at_bytes(2, kStreamChunk) + kStreamTiles * kStageBytes + kWindows * kWindowBytes; }
-void plan_stream(const TwHeader* h, int M, long lda, Plan& pl) {
+void plan_stream(const TwHeader* h, long lda, Plan& pl) {
     pl.stream_items = 0;
     if (pl.mode != 2 || pl.n_parts > 1 || h->k_chunk != kStreamChunk || h->ew_nnz > 0 || lda >= kFarPitch) return;
     pl.stream_items = pl.n_items;
@@ -3297,7 +3297,7 @@ extern "C" int tw_gemm_bias_act(const void* blob_host, const void* blob_dev, con
     Plan pl;
     int rc = make_plan(h, M, n_cu, pl, false, ws_bytes, act == TW_ACT_GELU);
     if (rc) return rc;
-    plan_stream(h, M, lda, pl);
+    plan_stream(h, lda, pl);
     const bool split = pl.n_parts > 1;
     const bool fused_epilogue = bias != nullptr || act != TW_ACT_NONE;
     const bool fused = fused_epilogue && !split;      // split K: the epilogue is the second kernel's

@@ -518,6 +518,47 @@ def test_streamed_rows_are_turned_in_lds(tw, case):
     assert wt.workspace.view(torch.int32)[:4].cpu().tolist() == [0, 0, 0, 0]
 
 
+# M, K, N, G, type, split: K streamed, on both sides of the pitch from which rows lie too far apart for 32-bit offsets and another kernel
+# runs.  All widths of a tile; K no multiple of eight; a block of one row and of a part; one set of tiles and several.
+FAR_ROWS = [(33, 2305, 300, 128, "f16", True), (65, 1600, 120, 64, "bf16", True), (3, 2689, 60, 32, "bf16", True),
+            (70, 1537, 300, 128, "bf16", False), (65, 2310, 190, 64, "f16", False), (1, 1993, 100, 32, "f16", False)]
+
+
+@pytest.mark.parametrize("case", FAR_ROWS, ids=lambda c: "x".join(map(str, c[:4])) + ("-split" if c[5] else ""))
+def test_streamed_rows_far_apart(tw, case):
+    """tw_gemm at a pitch of 2^23 elements, and of the last below: every element, plain and fused, and the bits of an ordinary pitch."""
+    M, K, N, G, dtype, split = case
+    w = W.generate(W.small_spec("far", M=M, K=K, N=N, G=G, dtype=dtype, col_prune=0.05, keep=("upow", 0.05, 0.6), seed_offset=5900 + M + K))
+    wt = tw.TwWeight.from_dense(w.B, w.mask, G, dtype)
+    if not split:
+        wt.ws_limit = 256
+    pl = tw.tw_gemm_plan(wt.blob, M, n_cu=torch.cuda.get_device_properties(0).multi_processor_count)
+    _say(f"far rows M={M} K={K} N={N} G={G} {dtype} split={split} T={wt.info['T']} {pl}")
+    assert pl["k_parts"] > 1
+    bbits = _bias_bits(N, dtype, 37)
+    bias = tw.bits_to_tensor(bbits, dtype)
+
+    def run(pitch):
+        A = torch.empty((M, pitch), dtype=wt.torch_dtype, device="cuda:0")
+        A[:, :(K + 7) // 8 * 8] = float("inf")
+        A[:, :K].copy_(tw.bits_to_tensor(w.A, dtype))
+        A[:, torch.as_tensor(np.flatnonzero(~w.mask.any(axis=1)), device="cuda:0")] = float("nan")
+        outs = [torch.full((M, N + 3), float("nan"), dtype=A.dtype, device="cuda:0") for _ in range(2)]
+        tw.tw_gemm(wt, A[:, :K], outs[0][:, :N])
+        tw.tw_gemm_bias_act(wt, A[:, :K], bias, "relu", outs[1][:, :N])
+        torch.cuda.synchronize()
+        for o in outs:
+            assert bool(torch.isnan(o[:, N:].float()).all().item()), "wrote beside C"
+        return [o[:, :N].contiguous() for o in outs]
+
+    want = run((K + 7) // 8 * 8)
+    _compare_whole(want[0], w.A, w.B, w.mask, dtype, what="ordinary pitch")
+    _compare_whole(want[1], w.A, w.B, w.mask, dtype, what="ordinary pitch, fused", post=lambda ref: tw_ref.bias_act(ref, tw_ref.decode(bbits, dtype), "relu"))
+    for pitch in ((1 << 23) - 8, 1 << 23):
+        for got, ref in zip(run(pitch), want):
+            assert torch.equal(got, ref), f"pitch {pitch}"
+
+
 # name, M, K, N, G, type, keep, tiles of a workgroup at most, waves to a tile of the product without GELU: 8, 4 and 2
 # waves; fewer steps than waves; the longest resident K in several batches of A; one row; a last row block of one row; K that
 # is no multiple of 8.  Wide tiles of few steps take a wave each, and a team with GELU.
