@@ -3006,30 +3006,44 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
 // hold them), and what a compute unit puts through with all its workgroups (kRowsFullStepUs a step, 8 to 10 KB of rows and weights whatever the
 // tile's width, and the stores).  The second decides on many narrow tiles: 16384 tokens of 768 -> 3072 (75 %) with G = 32 take 57 us here and 46 with
 // the block of 64 tokens resident, with G = 64 43 and 43, with G = 128 39 and 44.  The plan's estimate, made to compare plans, is corrected by kPlan:
-// of 95 random calls (600 tokens and more) its measured time is 0.68 to 0.88 of it with tiles of 32 columns, 1.06 to 1.17
-// resident with 128.  On those calls this kernel is taken 80 times, 1.7 times as fast in the geometric mean; the choice is more than 5 % behind
-// the faster one in seven, at most 15 %.
+// its measured time is 0.68 to 0.88 of it with tiles of 32 columns, 1.06 to 1.17 resident with 128.
+// Three kinds of calls keep the plan's kernel whatever the estimates, which do not see what is different there.  18300 random calls (16 to 200000
+// tokens, K = 64 .. 6000, all widths and skews, plain and fused) were timed both ways; of those that the estimates would take this kernel is the slower one in:
+// - one block of tokens, tiles of 64 columns, K resident: 17 of 23 (no load on the memory, the plan's kernel takes 5.4 to 6.5 us; 64 tokens of
+//   896 -> 1979 6.0 us, 7.4 here);
+// - tiles of 64 columns, K streamed in one round, a tile of more than 100 steps, at most 32 blocks: 70 of 104 (the wave that has the tile takes 0.14 us a step,
+//   a workgroup of this kernel's two to a compute unit 0.17; 2266 tokens of 5120 -> 704 47 us, 60 here);
+// - at most eight tiles of 32 columns, K streamed in full rounds, a tile of more than 180 steps: 41 of 47 (a compute unit holds two such lists,
+//   and every tile's rows come from memory again; 42298 tokens of 5760 -> 120 154 us, 232 here).
+// Of the 18300 calls this kernel is taken 15600 times, 1.61 times as fast in the geometric mean; 177 are slower than the plan's kernel by more than 2 %, 108 by
+// more than 5 %, 44 by more than 10 % (most of them 32 or 64 columns, K streamed, tiles of 150 steps and more; without those lines and with the
+// deeper ring for short tiles 419, 282 and 140).
 void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu) {
     constexpr double kRowsUs = 6.5, kRowsStepUs = 0.14, kRowsCrowdUs = 0.18, kRowsGeluUs = 2.0, kTileStepUs = 0.15,
                      kRowsFullUs = 4.0, kRowsFullStepUs = 0.105, kRowsStoreBytesPerUs = 18e3, kRowsFar = 1.35,
                      kWeightBytesPerUs = 110e3;
     constexpr long kRowsL2 = 3400 * 1024;                    // of an XCD's 4 MiB, for rows of At
+    constexpr int kDeepSteps = 24, kLongTile64 = 100, kLongTile32 = 180;
     pl.rows_group = 0;
     if (pl.n_parts > 1 || pl.team_shift > 0 || h->ew_nnz > 0 || h->n_chunks > 64) return;
-    // (offsets below kRowsRange, products of 24-bit factors)
+    // (offsets below kRowsRange, products of 24-bit factors: from 1 GiB of At on the plan's kernel runs, whatever the estimates)
     if ((unsigned long)h->K * (unsigned long)lda * 2 >= kRowsRange || lda >= (1 << 23) || h->K >= (1 << 24)) return;
     const int heaviest = heaviest_steps(h);
     const int bt = h->ncb == 4 ? rows_bt<4>() : rows_bt<1>();
     const long blocks = ((long)M + bt - 1) / bt, items = blocks * h->T;
-    if (items >= 0x7fffffffL) return;
+    if (items >= (1L << 24)) return;                         // (a launch holds 2^32 threads)
+    const long rounds = ((long)pl.n_items + n_cu - 1) / n_cu;
+    if (h->ncb == 2 && (h->n_chunks == 1 ? blocks == 1 : rounds == 1 && heaviest > kLongTile64 && blocks <= 32)) return;
+    if (h->ncb == 1 && h->n_chunks > 1 && heaviest > kLongTile32 && h->T <= 8 && 10L * pl.n_items > 7 * rounds * n_cu) return;
     // two workgroups or fewer to a compute unit: a deeper ring takes the place of the others.  (Where two such rings do not fit beside each
-    // other, tiles of 64 columns or long lists, one or fewer: a second round of workgroups costs as much as the first.)
+    // other, tiles of 64 columns or long lists, one or fewer: a second round of workgroups costs as much as the first.  Not for tiles of
+    // kDeepSteps or fewer, which end before it pays: in 4200 such calls the ring of four is 7 % faster in the median;
+    // with 25 to 64 steps 4 %, but up to 3 % slower in a tenth of them, and above 64 the deeper ring is the faster one.)
     const unsigned stage = h->ncb == 4 ? rows_stage_bytes<4>() : h->ncb == 2 ? rows_stage_bytes<2>() : rows_stage_bytes<1>();
     auto lds_of = [&](int stages) { return stages * stage + (unsigned)(heaviest + stages + 1) * 64u; };
-    pl.rows_stages = items <= (2 * lds_of(8) <= kLdsLimit ? 2L : 1L) * n_cu ? 8 : 4;
+    pl.rows_stages = heaviest > kDeepSteps && items <= (2 * lds_of(8) <= kLdsLimit ? 2L : 1L) * n_cu ? 8 : 4;
     pl.rows_lds = lds_of(pl.rows_stages);
     if (pl.rows_lds > (pl.rows_stages == 8 ? kLdsLimit : 64u * 1024u)) return;
-    const double rounds = (double)((pl.n_items + n_cu - 1) / n_cu);
     // (a chunk's packed weights pass behind its rows of A: 590 steps, 22 us, of the 47.6 that 16384 tokens of 3072 -> 768 take there, 41.5 here)
     const double weights_us = (double)h->total_steps / pl.n_seg * h->ncb * 1024.0 / kWeightBytesPerUs;
     const double chunks_us = h->n_chunks * kChunkUsT * (h->ncb <= 2 ? kNarrowChunk : 1.0) + weights_us, tile_us = heaviest * (h->ncb <= 2 ? kTileStepUs : 1.5 * kTileStepUs);

@@ -385,7 +385,8 @@ def test_a_tile_of_a_token_block_per_workgroup(tw, case):
 
 # M, K, N, G, type, rows: the first tile keeps rows + 1 rows, all in one place, the others `rows`, spread over all chunks: these have the
 # most steps though the first keeps the most rows.  Both depths of the ring, all widths of a tile.
-CLUSTERED = [(4100, 4608, 1024, 128, "f16", 20), (8200, 4608, 700, 64, "bf16", 30), (16385, 3100, 300, 32, "f16", 30), (16385, 12288, 512, 128, "bf16", 320)]
+CLUSTERED = [(4100, 4608, 1024, 128, "f16", 20), (8200, 4608, 700, 64, "bf16", 30), (16385, 3100, 300, 32, "f16", 30), (16385, 12288, 512, 128, "bf16", 320),
+             (8200, 12288, 512, 128, "f16", 320), (12000, 12288, 128, 64, "bf16", 320), (8200, 12288, 256, 32, "f16", 320)]
 
 
 @pytest.mark.parametrize("case", CLUSTERED, ids=lambda c: "x".join(map(str, c[:4])))

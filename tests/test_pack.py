@@ -575,6 +575,33 @@ def test_plan_of_a_tile_per_workgroup_holds_every_tiles_rows(K, N, G, rows):
     assert pl["tile_lds_bytes"] in [n * stage + (max(steps) + n + 1) * 64 for n in (4, 8)], (pl, max(steps), steps[0])
 
 
+def _even(K, N, G, steps):
+    """A weight whose tiles keep 16 * steps rows each, spread evenly (K up to 1536, or whole steps in every chunk of 384 rows)."""
+    mask = np.zeros((K, N), np.uint8)
+    mask[np.arange(16 * steps) * K // (16 * steps)] = 1
+    return tw.tw_pack(mask.astype(np.uint16) * 15360, mask, G, "f16")
+
+
+# K, N, G, steps, tokens: what one block of tokens, a long tile of 64 columns in few blocks, and few long narrow tiles run, and their neighbours
+@pytest.mark.parametrize("K,N,G,steps,M,taken", [
+    (1024, 640, 64, 8, 256, False), (1024, 640, 64, 8, 257, True), (1024, 640, 128, 8, 128, True),
+    (4608, 704, 64, 108, 2266, False), (4608, 704, 64, 96, 2266, True), (4608, 704, 64, 108, 8448, True),
+    (5760, 120, 32, 195, 42298, False), (5760, 120, 32, 180, 42298, True), (5760, 320, 32, 195, 42298, True), (5760, 120, 32, 195, 17000, True)])
+def test_plan_of_a_tile_per_workgroup_leaves_what_it_does_slower(K, N, G, steps, M, taken):
+    blob = _even(K, N, G, steps)
+    pl = tw.tw_gemm_plan(blob, M, n_cu=256, transposed=True)
+    assert max(_steps(blob)) == steps and pl["k_parts"] == 1 and pl["team_waves"] == 1, (pl, max(_steps(blob)))
+    assert (pl["tile_items"] > 0) == taken, pl
+
+
+@pytest.mark.parametrize("G,K,steps,ring", [(128, 1536, 24, 4), (128, 1536, 25, 8), (64, 1536, 24, 4), (64, 1536, 25, 8), (32, 1536, 24, 4), (32, 1536, 25, 8)])
+def test_plan_of_a_tile_per_workgroup_rings(G, K, steps, ring):
+    """One round of workgroups: tiles of few steps end before a deeper ring pays."""
+    pl = tw.tw_gemm_plan(_even(K, G, G, steps), 30000, n_cu=256, transposed=True)
+    stage = 16 * 2 * (128 if G == 128 else 256) + G // 32 * 1024
+    assert pl["tile_items"] > 0 and pl["tile_lds_bytes"] == ring * stage + (steps + ring + 1) * 64, pl
+
+
 @pytest.mark.parametrize("K,N,G,M", [(3072, 768, 128, 2048), (2304, 300, 64, 100), (3000, 200, 32, 1)])
 def test_plan_reports_the_split_kernels_memory(K, N, G, M):
     """A split on the row-major boundary: a K-major chunk of 384 + 9 columns of 64 rows, 136 bytes each, and two chunks as they lie in memory.  The
