@@ -2824,7 +2824,7 @@ int team_of(const TwHeader* h, int msb, int most_tiles, long items, int n_cu, bo
 }
 
 int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = false, size_t ws_avail = ~(size_t)0,
-              bool gelu = false) {
+              bool gelu = false, bool narrow_windows = true) {
     const bool resident = h->n_chunks == 1;
     const int buffers = resident ? 1 : 2;
     if (lds_need(1, h->k_chunk, buffers) > kLdsLimit) return TW_ERR_UNSUPPORTED;
@@ -2838,13 +2838,13 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
     };
     int msb = 2, tpw = kWaves;
     int nmb, nseg;
-    // 64 rows with narrow staging windows (K from about 910 to 1040; the row-major boundary's plain blobs): the packed weights of 64 rows are
+    // 64 rows with narrow staging windows (K from 921 to 1040; the row-major boundary's plain blobs): the packed weights of 64 rows are
     // streamed once instead of twice.  Not where the heaviest tile has more than kSkew times the mean's steps: it is one wave's, with
     // 64 rows twice as long (3025 x 1024 -> 1167, skewed, 22.3 us, 19.4 in 32 rows; 8192 x 1024 -> 4096, skewed, 2 % slower), and only for
     // kNarrowCost less of the estimate, which does not see a wide tile's second window (which is all there is to few wide tiles of few
     // steps: 49920 x 1035 -> 832, 8 steps a tile, 75.4 us, 72.2 in 32 rows).
     constexpr double kSkew = 2.5, kNarrowCost = 1.06;
-    const bool narrow = resident && !transposed && h->ew_nnz == 0 && lds_need(2, h->k_chunk, 1) > kLdsLimit && lds_need_narrow(h->k_chunk) <= kLdsLimit &&
+    const bool narrow = narrow_windows && resident && !transposed && h->ew_nnz == 0 && lds_need(2, h->k_chunk, 1) > kLdsLimit && lds_need_narrow(h->k_chunk) <= kLdsLimit &&
                         (double)heaviest_steps(h) * T <= kSkew * (double)h->total_steps && (h->ncb < 4 || T > kWaves || h->total_steps >= 12L * T);
     if (lds_need(2, h->k_chunk, buffers) > kLdsLimit && !narrow) msb = 1;
     pl.mode = resident ? 0 : 1;
@@ -2994,6 +2994,19 @@ int make_plan(const TwHeader* h, int M, int n_cu, Plan& pl, bool transposed = fa
             pl.partial_bytes = (size_t)pl.n_parts * nmb1 * T * tile_bytes;
             pl.lds_bytes = pl.misc_off + 16u;
         }
+    }
+    // What the narrow windows save is a round of workgroups.  Of 2809 random calls of such a K (1000 rows and more) that would take them, timed
+    // both ways, 2101 take fewer rounds with them, 1.23 times as fast, 47 slower by more than 2 %.  Not among these: wide tiles in two rounds
+    // instead of three (69 of 101 slower, 4 % on average: a wide tile has a second window).  And in one round either way 32 rows are ahead
+    // unless a wave has its fourth tile there: 204 of 286 calls slower by 64 rows, 8 % on average (2832 x 1027 -> 1522, G = 128, 18.8 us in 32
+    // rows, 27.5 in 64; 1693 x 1013 -> 3997 27 and 38); with more tiles 64 rows are 1.16 times as fast, 8 of 221 slower.
+    // Nor where 32 rows have teams of waves: these sum in other groups, and the transposed boundary, which has no such windows, would have them.
+    if (pl.narrow) {
+        Plan low;
+        if (make_plan(h, M, n_cu, low, transposed, ws_avail, gelu, false) != TW_OK) return TW_OK;
+        const int rounds = (pl.n_items + n_cu - 1) / n_cu, low_rounds = (low.n_items + n_cu - 1) / n_cu;
+        const int low_tiles = (T + low.n_seg - 1) / low.n_seg;
+        if (low.team_shift > 0 || (low_rounds == 1 && low_tiles <= 3 * kWaves) || (h->ncb == 4 && rounds == 2 && low_rounds == 3)) pl = low;
     }
     return TW_OK;
 }

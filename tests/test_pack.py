@@ -602,6 +602,25 @@ def test_plan_of_a_tile_per_workgroup_rings(G, K, steps, ring):
     assert pl["tile_items"] > 0 and pl["tile_lds_bytes"] == ring * stage + (steps + ring + 1) * 64, pl
 
 
+# K, N, G, steps, rows of A: K from 921 to 1040, where 64 rows fit beside narrow windows: one round either way with up to 24 tiles for a workgroup of 32
+# rows and with more, wide tiles in two rounds instead of three, narrower ones, fewer rounds
+@pytest.mark.parametrize("K,N,G,steps,M,rows", [
+    (1027, 1536, 128, 30, 2832, 32), (928, 1152, 128, 30, 3200, 32), (1013, 3840, 128, 24, 1693, 32), (1000, 768, 32, 20, 6000, 32), (1000, 3200, 32, 20, 8000, 64),
+    (1000, 1280, 128, 24, 24000, 32), (1000, 1280, 64, 24, 24000, 64), (1000, 1280, 128, 24, 16000, 64)])
+def test_plan_of_64_rows_beside_narrow_windows(K, N, G, steps, M, rows):
+    pl = tw.tw_gemm_plan(_even(K, N, G, steps), M, n_cu=256)
+    assert pl["rows_per_block"] == 32 if rows == 32 else pl["rows_per_block"] > 32, pl
+
+
+@pytest.mark.parametrize("K", [912, 921, 960, 1040, 1041])
+def test_plan_has_the_same_teams_on_both_boundaries(K):
+    """Teams of waves decide in which groups a result is summed, and one boundary alone has narrow windows."""
+    for i, (G, T) in enumerate([(32, 1), (32, 7), (32, 24), (64, 2), (64, 5), (64, 16), (128, 1), (128, 3), (128, 6), (128, 12), (128, 24)]):
+        blob = _even(K, G * T, G, 1 + (7 * i + K) % 50)
+        for M in (1, 33, 100, 257, 512, 800, 1100, 1500, 2048, 2700, 4096, 5000, 8192, 8200, 16384):
+            assert tw.tw_gemm_plan(blob, M)["team_waves"] == tw.tw_gemm_plan(blob, M, transposed=True)["team_waves"], (G, T, M)
+
+
 @pytest.mark.parametrize("K,N,G,M", [(3072, 768, 128, 2048), (2304, 300, 64, 100), (3000, 200, 32, 1)])
 def test_plan_reports_the_split_kernels_memory(K, N, G, M):
     """A split on the row-major boundary: a K-major chunk of 384 + 9 columns of 64 rows, 136 bytes each, and two chunks as they lie in memory.  The
