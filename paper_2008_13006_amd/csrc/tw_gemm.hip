@@ -424,7 +424,7 @@ constexpr int kWinCols = kWinLines * kLineCols;     // 256
 constexpr int kSpareOff = kWinCols * 8;             // spare slots behind the window of a plane
 constexpr int kPlaneBytes = kWinCols * 8 + 32 * 8 + 32;
 constexpr unsigned kStageBytes = 2 * kPlaneBytes;   // per wave
-// Windows of kNarrowLines lines, where LDS has no room for more beside 64 rows of A (K from about 910 to 1040).
+// Windows of kNarrowLines lines, where LDS has no room for more beside 64 rows of A (K from 921 to 1040).
 // (32 rows of A stream the packed weights twice as often.  Before -> now: 4321 x 1000 -> 1234 (G = 32) 27.1 -> 22.5 us, 14528 x 1024 -> 2188
 // (G = 32) 75 -> 50, 10752 x 960 -> 3328 with GELU 82 -> 60, 31710 x 1019 -> 1472 with GELU 106 -> 90.  A span wider than the window
 // takes several, which costs the wave its staging again.)
@@ -1973,16 +1973,19 @@ __global__ __launch_bounds__(kThreads) void tw_team_kernel(const TwGemmParams p)
 //
 // A workgroup is four waves, its block 128 tokens (tiles of four column blocks, two waves side by side) or 256 (narrower tiles); a
 // wave multiplies 64 tokens x 64 (32) columns in the order of the tile's steps, which is the order of the kernels above: both
-// boundaries give the same bits.  A ring of kRowsStages stages of one step (16 slots) is filled by direct loads.  Four workgroups fit a compute unit (at most 40 KB of LDS and 128 registers), so one's first
-// loads and stores pass while others multiply.
+// boundaries give the same bits.  A ring of kRowsStages stages of one step (16 slots) is filled by direct loads.  Several workgroups share a
+// compute unit, so one's first loads and stores pass while others multiply: with four stages four while LDS holds them (40 KB each: tiles
+// of up to 123 steps with G = 128 and up to 59 with G = 32), else three (G = 64, whose four stages alone take 40 KB, up to 208 steps; G = 128
+// up to 336, G = 32 up to 272), else two.  (Registers allow four.)
 //
 // LDS row r of a stage is slot position r of the step's list (off_goff); its 16-byte pieces are kept at piece ^ 4 * (r / 2 % 4): a
 // transposing read takes four rows r, r + 2, r + 4, r + 6 at the same tokens, which then lie in different banks.
 // Padded slots, tokens past M and steps past the end are offsets out of the descriptor's range: they fetch zeros.
 //
-// What bounds it: full batches the compute unit's loads (8 KB a step, about 110 ns with four workgroups in their main loops, 67 of
-// them the vector L1's rate), two workgroups or fewer the latency of a stage, 170 ns a step with four stages on their way,
-// 125 with eight.  What the compiler loads itself is consumed before the first direct load: its waits do not know of those, and a
+// What bounds it: full batches the compute unit's loads (8 KB a step, about 110 ns with four workgroups in their main loops, of which the 110 to
+// 120 KB/us that a compute unit reads from the L2 are 70; its address and data units are busy 53 and 64 % of 16384 x 768 -> 3072), two
+// workgroups or fewer the latency of a stage, 170 ns a step with four stages on their way, 125 with eight (8192 x 4096 -> 1024: no unit
+// is busy more than 36 % of the launch).  What the compiler loads itself is consumed before the first direct load: its waits do not know of those, and a
 // wait for one of its own behind them drained the ring (16384 tokens of 768 -> 3072 41.2 us, now 34.0).
 // Before (a resident or streamed block of 64 tokens, all tiles) -> now: 16384 tokens of 768 -> 3072 39.3 -> 34.0 us, 8192 of
 // 4096 -> 1024, skewed 42.2 -> 28.1 (its heaviest tile has 159 steps), 84745 of 1152 -> 130 (G = 32) 105 -> 34, 54959 of
@@ -2157,7 +2160,10 @@ __global__ __launch_bounds__(256, kRowsStages == 4 ? 4 : 2) void tw_rows_kernel(
 // What bounds it now are the multiplying waves.  100352 x 2304 -> 256 (G = 64, bias, ReLU) 151.6 -> 138 us; bringing A in and turning it
 // alone takes 73 (6.3 TB/s), with the epilogue 95, the steps and the epilogue alone 91: an item's heaviest tile is one wave's,
 // and the loading waves stop two chunks ahead of an epilogue.  28367 x 1576 -> 512 57 -> 42 us, 12658 x 2625 -> 960 67 -> 48,
-// 20335 x 4292 -> 256 87 -> 62, 7936 x 1668 -> 256 24.3 -> 16.4; 90 random calls with 1500 rows and more 1.11 times as fast on average.
+// 20335 x 4292 -> 256 87 -> 62, 7936 x 1668 -> 256 24.3 -> 16.4; 5400 random calls with 1500 rows and more 1.25 times as fast on average, 37
+// slower by more than 2 %, the worst by 9 % (three or four wide tiles; 77094 x 4957 -> 459 321 us before, 350 now).  (29 to 36 scalar registers
+// spill into vector ones: the loading and the multiplying waves' constants in one kernel.  The counters agree: a compute unit's queue of
+// misses is full for 44 % of the convolution's launch, the waves wait 14 % of their time.)
 // Tried without gain: two waves a tile with 32 rows each (155 us), first operands asked for across chunks (branches between
 // the steps cost more), row-major chunks with 2-byte gathers (171), four waves that share a tile in place of split K.
 //
@@ -2282,7 +2288,7 @@ __global__ __launch_bounds__(kThreads) void tw_stream_kernel(const TwGemmParams 
 // The results are those of MODE 3, bit for bit.
 // What bounds it is the chain of one part: launch, a chunk's latency, the heaviest tile's steps, the dump (32 KB a tile and part).  MODE 3
 // -> this kernel, whole calls: 2048 x 3072 -> 768 23.6 -> 22.6 us, 1745 x 3441 -> 477 26.6 -> 21.7, 348 x 2002 -> 746 16.0 -> 13.6,
-// 64 x 2593 -> 1549 with GELU 14.8 -> 12.4; 60 random split calls 1.0 to 1.27 times as fast.
+// 64 x 2593 -> 1549 with GELU 14.8 -> 12.4; 4990 random split calls 1.23 times as fast on average (0.95 to 1.5).
 template <int DT, int NCB, int H, int CG>
 __global__ __launch_bounds__(kThreads) void tw_part_kernel(const TwGemmParams p) {
     constexpr unsigned PITCH = at_pitch_of<2>(), RAW = 64 * kStreamChunk * 2, WIN = 1024;      // a wave's window: 8 rows x 64 columns
@@ -3073,7 +3079,7 @@ void plan_rows(const TwHeader* h, int M, long lda, int n_cu, Plan& pl, bool gelu
 }
 
 // Whether tw_gemm runs tw_stream_kernel instead of the plan's kernel (pl.stream_items): wherever the plan is MODE 2, but for TEW blobs
-// and pitches whose rows lie too far apart for 32-bit offsets.  (Measured on 90 random calls: 0.99 to 1.48 times as fast.)
+// and pitches whose rows lie too far apart for 32-bit offsets.  (5400 random calls: 1.25 times as fast on average, see there.)
 constexpr long kFarPitch = 1 << 23;
 unsigned stream_lds_bytes() { return 2 * at_bytes(2, kStreamChunk) + kStreamTiles * kStageBytes + kWindows * kWindowBytes; }
 void plan_stream(const TwHeader* h, long lda, Plan& pl) {
@@ -3083,7 +3089,7 @@ void plan_stream(const TwHeader* h, long lda, Plan& pl) {
 }
 
 // Whether tw_gemm runs tw_part_kernel for a split's parts: for every split, but for TEW blobs (their residual's steps are in MODE 3) and those
-// pitches.  On 60 random split calls it takes 1.0 to 1/1.27 of MODE 3's time, never more.
+// pitches.  (Of 4990 random split calls two are slower than with MODE 3 by more than 2 %, 1.23 times as fast on average.)
 bool parts_by_direct_loads(const TwHeader* h, long lda, const Plan& pl) {
     return pl.n_parts > 1 && h->ew_nnz == 0 && h->k_chunk == kStreamChunk && lda < kFarPitch;
 }
